@@ -22,12 +22,12 @@ struct GemmArgs {
 constexpr int DEC_MAX_ROWS = 2;
 enum { EPI_RESID = 0, EPI_QKV = 1, EPI_SWIGLU = 2 };
 struct DecArgs {
-    const uint16_t* xh; size_t x_plane;       // input planes [M][K] (hi; lo x_plane elements further); gemm_rows: [K/32][R][32], x_plane = R K, R = rows_tiled(M)
+    const uint16_t* xh; size_t x_plane;       // input planes [M][K] (hi; lo x_plane elements further); gemm_rows: tiled (xt_index), x_plane = R K, R = rows_tiled(M)
     const void* w[3]; int seg_rows[2];        // tiled matrices stacked along N (QKV), or gate and up (SWIGLU)
     int M, N, K;                              // N: output columns (per matrix for SWIGLU)
     const float* ssq_in; int ssq_tiles; float eps;     // input rows' partial sums of squares [M][ssq_tiles] (QKV, SWIGLU)
     float* x; const float* gain_next; uint16_t* out_planes; size_t out_plane; float* ssq_out;   // RESID; out_planes also SWIGLU
-    int out_tiled;                            // gemm_rows: R if the output planes are in the tiled layout [N/32][R][32] (out_plane = R N), else 0
+    int out_tiled;                            // gemm_rows: R = rows_tiled(M) if the output planes are tiled (xt_index; out_plane = R N), else 0
     const int32_t* pos; const float2* rope; int q_len, H, KVH, hd, cache_len;                    // QKV
     float* q_out; uint16_t* k_cache; uint16_t* v_cache;
     const float* att_part; int att_splits;    // RESID with the attention's per-split partials as input instead of planes (uses H, hd)
