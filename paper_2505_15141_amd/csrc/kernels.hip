@@ -1470,8 +1470,11 @@ struct AttnMerge {
     int32_t* status;             // bit 16: a poll ran out of patience
 };
 
-template <int HD, int NT, bool STREAM>
-__global__ __launch_bounds__(256) void attn_mfma_kernel(const float* __restrict__ q, const uint16_t* __restrict__ k_cache,
+// AHEAD (one row tile): the next block is requested into the registers of the block at hand as they become free.  For launches whose
+// wavefronts walk many blocks (launch_attention); a few blocks are not worth the larger kernel (batch 1, 1682 keys in 4 splits: 17.0 us
+// without, 17.7 with).
+template <int HD, int NT, bool STREAM, bool AHEAD>
+__global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_kernel(const float* __restrict__ q, const uint16_t* __restrict__ k_cache,
                                                         const uint16_t* __restrict__ v_cache,
                                                         const int32_t* __restrict__ pos, int q_len, int H, int KVH,
                                                         int cache_len, float scale, float* __restrict__ part, int n_splits,
@@ -1554,7 +1557,7 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const float* __restrict_
         // STREAM: K rows of 256 bytes and V are asked for as data nobody reads again (batch 16, 4096 keys, head_dim 128: 212
         // -> 179 us; V alone 192); rows of 128 bytes stay cached, both halves of a line are then served by one request
         // (head_dim 64: a step of the batch 919 -> 890 us)
-        auto fetch = [&](int blk, uint4 (&kf)[2][DS], uint4 (&vf)[DT]) {
+        auto fetch_k = [&](int blk, uint4 (&kf)[2][DS]) {
             const int key0 = blk * 32;
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
@@ -1562,13 +1565,18 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const float* __restrict_
 #pragma unroll
                 for (int ds = 0; ds < DS; ++ds) kf[t][ds] = ldg16_stream<STREAM && HD == 128>(kb + (size_t)krow * HD + ds * 32 + lq * 8);
             }
+        };
+        auto fetch_v = [&](int blk, uint4 (&vf)[DT]) {
 #pragma unroll
             for (int t = 0; t < DT; ++t) vf[t] = ldg16_stream<STREAM>(vb + ((size_t)blk * HD + t * 16 + li) * 32 + lq * 8);
         };
-        auto block = [&](int blk, uint4 (&kf)[2][DS], uint4 (&vf)[DT]) {
+        // more (one tile): the next block's keys and values are asked for as soon as their registers are free, under this block's
+        // softmax and products.  Four blocks before the end every key is visible to all of the at most 16 query positions (rows
+        // that do not exist have zero queries, and nobody reads their sums).  No branch around those loads: the compiler would have to wait for all of them at the next use.
+        auto block = [&](int blk, uint4 (&kf)[2][DS], uint4 (&vf)[DT], bool more) {
             const int key0 = blk * 32;
             // ---- values: keys past n_keys may hold anything, even NaN patterns: zero them ----
-            if (key0 + 32 > n_keys) {
+            if (!more && key0 + 32 > n_keys) {
 #pragma unroll
                 for (int t = 0; t < DT; ++t) {
                     uint32_t w[4] = {vf[t].x, vf[t].y, vf[t].z, vf[t].w};
@@ -1594,6 +1602,11 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const float* __restrict_
                         sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(bf16x8, ql[x][ds]), sc[t], 0, 0, 0);
                     }
                 }
+                if (more) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    fetch_k(blk + 4, kf);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
                 // lane holds S^T[key0 + 16t + 4lq + e][row li]
                 float sv[8];
                 float bm = -INFINITY;
@@ -1602,7 +1615,7 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const float* __restrict_
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int key = key0 + t * 16 + 4 * lq + e;
-                        const bool vis = rvalid[x] && key < n_keys && key <= row_pos[x];       // causal
+                        const bool vis = more || (rvalid[x] && key < n_keys && key <= row_pos[x]);       // causal
                         sv[t * 4 + e] = vis ? sc[t][e] : -INFINITY;
                         bm = fmaxf(bm, sv[t * 4 + e]);
                     }
@@ -1631,12 +1644,26 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const float* __restrict_
                     o[x][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(bf16x8, pl), o[x][t], 0, 0, 0);
                 }
             }
+            if (more) {
+                __builtin_amdgcn_sched_barrier(0);
+                fetch_v(blk + 4, vf);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         };
-        if constexpr (NT == 1) {
+        auto fetch = [&](int blk, uint4 (&kf)[2][DS], uint4 (&vf)[DT]) { fetch_k(blk, kf); fetch_v(blk, vf); };
+        if constexpr (NT == 1 && !AHEAD) {
             for (int blk = b_begin + wave; blk < b_end; blk += 4) {
                 uint4 kf[2][DS], vf[DT];
                 fetch(blk, kf, vf);
-                block(blk, kf, vf);
+                block(blk, kf, vf, false);
+            }
+        } else if constexpr (NT == 1) {
+            uint4 kf[2][DS], vf[DT];
+            int blk = b_begin + wave;
+            if (blk < b_end) {
+                fetch(blk, kf, vf);
+                for (; blk + 4 < b_end; blk += 4) block(blk, kf, vf, true);
+                block(blk, kf, vf, false);
             }
         } else if (b_begin + wave < b_end) {
             // a request past the wavefront's last block repeats that block: in bounds, never used
@@ -1645,10 +1672,10 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const float* __restrict_
             fetch(b_begin + wave, kf0, vf0);
             for (int blk = b_begin + wave; blk < b_end; blk += 8) {
                 fetch(min(blk + 4, blk_last), kf1, vf1);
-                block(blk, kf0, vf0);
+                block(blk, kf0, vf0, false);
                 if (blk + 4 >= b_end) break;
                 fetch(min(blk + 8, blk_last), kf0, vf0);
-                block(blk + 4, kf1, vf1);
+                block(blk + 4, kf1, vf1, false);
             }
         }
         // ---- combine the 4 wavefronts, one tile at a time: lane holds O^T[d = 16t + 4lq + e][row li] ----
@@ -1971,8 +1998,8 @@ size_t attn_cells_bytes(int rows, int H, int hd, int n_splits) {
 static size_t attn_resident_workgroups(int hd) {
     auto ask = [](bool wide) -> size_t {
         int per_cu = 0;
-        const hipError_t e = wide ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_mfma_kernel<128, 1, true>, 256, 0)
-                                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_mfma_kernel<64, 1, true>, 256, 0);
+        const hipError_t e = wide ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_mfma_kernel<128, 1, true, true>, 256, 0)
+                                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_mfma_kernel<64, 1, true, true>, 256, 0);
         const int cus = step_grid();
         return (e == hipSuccess && per_cu > 0 && cus > 0) ? (size_t)per_cu * cus : 1;   // 1: never enough, the merge kernel runs
     };
@@ -1986,6 +2013,17 @@ int attn_used_splits(int dtype, int B, int q_len, int H, int KVH, int hd, int n_
     if (dtype != BS_BF16) return n_splits;
     if (attn_prompt_applies(B, q_len, H, KVH, hd)) return 1;
     const int n_tiles = (H / KVH * q_len + 15) / 16, n_rt = n_tiles >= 2 ? (n_tiles + 1) / 2 : 1;
+    if (n_tiles <= 1) {
+        // Whole rounds of workgroups (2 per compute unit are resident at head_dim 128, 4 at 64): the fewest splits, up to the count asked
+        // for, with the least rounds per split.  A last round of a few workgroups costs as much as a full one, and a single split
+        // needs no merge kernel.  16 sequences, 4105 keys, 32 heads of 128: 2 splits 178.6 + 8.5 us (merge), 1 split with the next block
+        // ahead 168.0; 12 heads of 64: 6 splits (1152 workgroups) 36.5, 5 splits 35.2; 4 sequences, 2053 keys: 5 splits 29.0, 4 splits 28.1.
+        const long long units = (long long)B * KVH, slots = (hd == 128 ? 2 : 4) * 256;
+        int best = n_splits;
+        for (int s = n_splits - 1; s >= 1; --s)
+            if ((units * s + slots - 1) / slots * best <= (units * best + slots - 1) / slots * s) best = s;
+        return best;
+    }
     if (n_rt <= 1) return n_splits;
     const int want = (int)((1024 + (long long)B * KVH * n_rt - 1) / ((long long)B * KVH * n_rt));
     return want < n_splits ? want : n_splits;
@@ -2006,6 +2044,7 @@ int launch_attention(int dtype, const float* q, const void* k_cache, const void*
         // queries: 287 -> 225 us per layer at batch 32 / 8192 keys; prompt chunks of a batch: 7-10 % off the prompt pass)
         const int nt = (n_tiles >= 2) ? 2 : 1;
         const int n_rt = (n_tiles + nt - 1) / nt;
+        const size_t asked = (size_t)n_splits * KVH * B;           // in-kernel merging stays with the launches that fitted before the rounds are counted
         if (out) n_splits = attn_used_splits(dtype, B, q_len, H, KVH, hd, n_splits);
         const dim3 mgrid(n_splits * (out ? n_rt : 1), KVH, B);
         uint16_t* direct = (out && n_splits == 1) ? reinterpret_cast<uint16_t*>(out) : nullptr;     // no merge needed
@@ -2013,7 +2052,7 @@ int launch_attention(int dtype, const float* q, const void* k_cache, const void*
         AttnMerge mg = {};
         mg.tiled = out_tiled;
         if (cells && cells->buf && out && !direct && nt == 1 && n_rt == 1 && attn_cells_bytes(B * q_len, H, hd, n_splits) <= cells->bytes &&
-            (size_t)n_splits * KVH * B <= attn_resident_workgroups(hd)) {
+            asked <= (hd == 128 ? 512 : 1024) && (size_t)n_splits * KVH * B <= attn_resident_workgroups(hd)) {
             mg.cells = cells->buf; mg.out = reinterpret_cast<uint16_t*>(out); mg.plane = plane;
             mg.flag = cells->flag; mg.spin_limit = cells->spin_limit; mg.status = cells->status;
         }
@@ -2021,13 +2060,16 @@ int launch_attention(int dtype, const float* q, const void* k_cache, const void*
         { const int prc = prof_events(s, &e0, &e1); if (prc != BS_OK) return prc; }
         // with several groups of row tiles every group reads the keys again: those loads stay cached
         stream = stream && n_rt == 1;
-#define BS_ATTN_ST(HD, NT, ST) BS_LAUNCH_TIMED((attn_mfma_kernel<HD, NT, ST>), mgrid, block, 0, s, e0, e1, q, (const uint16_t*)k_cache, \
+#define BS_ATTN_ST(HD, NT, ST, AH) BS_LAUNCH_TIMED((attn_mfma_kernel<HD, NT, ST, AH>), mgrid, block, 0, s, e0, e1, q, (const uint16_t*)k_cache, \
                                         (const uint16_t*)v_cache, pos, q_len, H, KVH, max_len, scale, part, n_splits, direct, plane, mg)
-#define BS_ATTN(HD, NT) do { if (stream) BS_ATTN_ST(HD, NT, true); else BS_ATTN_ST(HD, NT, false); } while (0)
-        if (hd == 128) { if (nt == 2) BS_ATTN(128, 2); else BS_ATTN(128, 1); }
-        else if (hd == 64) { if (nt == 2) BS_ATTN(64, 2); else BS_ATTN(64, 1); }
+#define BS_ATTN(HD, NT, AH) do { if (stream) BS_ATTN_ST(HD, NT, true, AH); else BS_ATTN_ST(HD, NT, false, AH); } while (0)
+#define BS_ATTN_1(HD) do { if (ahead) BS_ATTN(HD, 1, true); else BS_ATTN(HD, 1, false); } while (0)
+        const bool ahead = max_len / n_splits >= 768;              // six blocks and more per wavefront of a full cache
+        if (hd == 128) { if (nt == 2) BS_ATTN(128, 2, false); else BS_ATTN_1(128); }
+        else if (hd == 64) { if (nt == 2) BS_ATTN(64, 2, false); else BS_ATTN_1(64); }
         else
             BS_FAIL(BS_ESHAPE, "attention: bf16 caches need head_dim 64 or 128, got %d", hd);
+#undef BS_ATTN_1
 #undef BS_ATTN_ST
 #undef BS_ATTN
         BS_LAUNCH_CHECK();
