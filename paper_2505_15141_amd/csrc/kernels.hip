@@ -181,6 +181,8 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(float* __restrict__ x, co
 // (x += sum of the pending split-K partials), writes the planes of gain .* x and ONE partial sum of squares per
 // 1024-column chunk; the projection's consumer (rope_kv, swiglu) multiplies by r.  grid (rows, ceil(d/1024)):
 // every row is spread over several compute units instead of one.
+// AHEAD: splits in flight at a time.  They were written by other dies a moment ago, so every turn of the loop is a trip to memory.
+template <int AHEAD>
 __global__ __launch_bounds__(256) void resid_sum_kernel(float* __restrict__ x, const float* __restrict__ pend, int pend_ks,
                                                         size_t pend_stride, const float* __restrict__ gain, int d, size_t plane,
                                                         uint16_t* __restrict__ out, float* __restrict__ ssq, int tiled) {
@@ -191,22 +193,22 @@ __global__ __launch_bounds__(256) void resid_sum_kernel(float* __restrict__ x, c
     if (i < d) {
         float* row = x + (size_t)r * d + i;
         float4 v = *reinterpret_cast<const float4*>(row);
+        const float4 g = *reinterpret_cast<const float4*>(gain + i);
         if (pend) {
             const float* prow = pend + (size_t)r * d + i;
-            for (int s0 = 0; s0 < pend_ks; s0 += 8) {
-                float4 p[8];
+            for (int s0 = 0; s0 < pend_ks; s0 += AHEAD) {
+                float4 p[AHEAD];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
+                for (int u = 0; u < AHEAD; ++u) {
                     p[u] = *reinterpret_cast<const float4*>(prow + (size_t)min(s0 + u, pend_ks - 1) * pend_stride);
                     if (s0 + u >= pend_ks) p[u] = make_float4(0.f, 0.f, 0.f, 0.f);
                 }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) { v.x += p[u].x; v.y += p[u].y; v.z += p[u].z; v.w += p[u].w; }
+                for (int u = 0; u < AHEAD; ++u) { v.x += p[u].x; v.y += p[u].y; v.z += p[u].z; v.w += p[u].w; }
             }
             *reinterpret_cast<float4*>(row) = v;
         }
         ss = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-        const float4 g = *reinterpret_cast<const float4*>(gain + i);
         store_planes4(out, plane, tiled ? xt_index(r, i, tiled) : (size_t)r * d + i, v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w);
     }
     ss = wsum(ss);
@@ -1968,8 +1970,13 @@ int launch_resid_sum(float* x, const float* pend, int pend_ks, size_t pend_strid
                      size_t plane, void* out, float* ssq, int tiled, hipStream_t s) {
     if (rows <= 0) return BS_OK;
     BS_REQUIRE(!tiled || (rows <= tiled && d % 32 == 0), BS_ESHAPE, "resid_sum: tiled planes hold at most %d rows (%d) of a multiple of 32 columns (%d)", tiled, rows, d);
-    hipLaunchKernelGGL(resid_sum_kernel, dim3(rows, norm_chunks(d)), dim3(256), 0, s, x, pend, pend_ks, pend_stride, gain, d, plane,
-                       (uint16_t*)out, ssq, tiled);
+    // as many splits in flight as there are, up to 16
+#define BS_RESID(AHEAD) hipLaunchKernelGGL(resid_sum_kernel<AHEAD>, dim3(rows, norm_chunks(d)), dim3(256), 0, s, x, pend, pend_ks, pend_stride, gain, d, plane, \
+                                           (uint16_t*)out, ssq, tiled)
+    if (!pend || pend_ks <= 4) BS_RESID(4);
+    else if (pend_ks <= 8) BS_RESID(8);
+    else BS_RESID(16);
+#undef BS_RESID
     BS_LAUNCH_CHECK();
     return BS_OK;
 }
