@@ -125,8 +125,8 @@ size_t attn_cells_bytes(int rows, int H, int hd, int n_splits);
 bool attn_prompt_applies(int B, int q_len, int H, int KVH, int hd);
 int launch_attn_prompt(const float* q, const uint16_t* k_cache, const uint16_t* v_cache, const int32_t* pos, int B, int q_len, int H, int KVH,
                        int hd, int cache_len, uint16_t* out, size_t plane, hipStream_t s);
-// key splits that the launch uses when it may use up to n_splits
-int attn_used_splits(int dtype, int B, int q_len, int H, int KVH, int hd, int n_splits);
+// key splits that the launch uses over a cache of cache_len rows when it may use up to n_splits
+int attn_used_splits(int dtype, int B, int q_len, int H, int KVH, int hd, int cache_len, int n_splits);
 int launch_attention(int dtype, const float* q, const void* k_cache, const void* v_cache, const int32_t* pos, int B,
                      int q_len, int H, int KVH, int hd, int max_len, int n_splits, float* part, size_t plane, void* out, int out_tiled, const AttnCells* cells,
                      bool stream, hipStream_t s);

@@ -2028,19 +2028,34 @@ static size_t attn_resident_workgroups(int hd) {
 
 // Many query rows per head group in a pass that is too small for attn_prompt_kernel: one workgroup per group of row tiles and
 // only as many key splits as it takes to reach about a thousand workgroups; a single group keeps all the splits.
-int attn_used_splits(int dtype, int B, int q_len, int H, int KVH, int hd, int n_splits) {
+int attn_used_splits(int dtype, int B, int q_len, int H, int KVH, int hd, int cache_len, int n_splits) {
     if (dtype != BS_BF16) return n_splits;
     if (attn_prompt_applies(B, q_len, H, KVH, hd)) return 1;
     const int n_tiles = (H / KVH * q_len + 15) / 16, n_rt = n_tiles >= 2 ? (n_tiles + 1) / 2 : 1;
     if (n_tiles <= 1) {
-        // Whole rounds of workgroups (2 per compute unit are resident at head_dim 128, 4 at 64): the fewest splits, up to the count asked
-        // for, with the least rounds per split.  A last round of a few workgroups costs as much as a full one, and a single split
-        // needs no merge kernel.  16 sequences, 4105 keys, 32 heads of 128: 2 splits 178.6 + 8.5 us (merge), 1 split with the next block
-        // ahead 168.0; 12 heads of 64: 6 splits (1152 workgroups) 36.5, 5 splits 35.2; 4 sequences, 2053 keys: 5 splits 29.0, 4 splits 28.1.
-        const long long units = (long long)B * KVH, slots = (hd == 128 ? 2 : 4) * 256;
+        // One row tile: fewer splits than asked for where that is no slower.
+        const long long units = (long long)B * KVH;
         int best = n_splits;
-        for (int s = n_splits - 1; s >= 1; --s)
-            if ((units * s + slots - 1) / slots * best <= (units * best + slots - 1) / slots * s) best = s;
+        if (hd != 128) {
+            // head_dim 64, 4 workgroups per compute unit resident: the fewest splits with the least rounds of 1024 workgroups per split (16
+            // sequences of 4097 keys, 12 heads: 6 splits, 1152 workgroups, 36.5 us; 5 splits 35.2; two or fewer workgroups per compute
+            // unit have too little in flight: 9 sequences of 8000 keys, 2 splits, a whole pass 8 % longer than with 9).
+            for (int s = n_splits - 1; s >= 1; --s)
+                if ((units * s + 1023) / 1024 * best <= (units * best + 1023) / 1024 * s) best = s;
+            return best;
+        }
+        // head_dim 128: the least estimated time.  A compute unit streams about 30 KB/us whether it holds one workgroup or two, so what counts
+        // is how evenly the workgroups fall on 256 compute units; all of them together get 6.4 TB/s, and the two bounds add like
+        // fourth powers; partials and their merge kernel cost 8 us.  16 sequences of 4105 keys, 32 heads: 2 splits 178.6 + 8.5 us, 1 split
+        // 168.0.  Whole passes of the 7B shape: 6 sequences of 3007 keys, 1 / 2 / 3 / 4 / 5 splits 6240 / 6505 / 6627 / 6408 / 6596 us;
+        // 10 of 6004 keys, 1 / 2 / 3 / 4 splits 11281 / 10266 / 9831 / 9760; 4 of 2053 keys 4378 / 4128 / 4267 / 4158.
+        const double unit_mb = 4e-6 * hd * cache_len, f = units * unit_mb / 6.4;
+        double best_us = 1e30;
+        for (int s = 1; s <= n_splits; ++s) {
+            const double c = (double)((units * s + 255) / 256) / s * unit_mb / 0.030;
+            const double us = sqrt(sqrt(c * c * c * c + f * f * f * f)) + (s > 1 ? 8.0 : 0.0);
+            if (us < 0.999 * best_us) { best = s; best_us = us; }
+        }
         return best;
     }
     if (n_rt <= 1) return n_splits;
@@ -2064,7 +2079,7 @@ int launch_attention(int dtype, const float* q, const void* k_cache, const void*
         const int nt = (n_tiles >= 2) ? 2 : 1;
         const int n_rt = (n_tiles + nt - 1) / nt;
         const size_t asked = (size_t)n_splits * KVH * B;           // in-kernel merging stays with the launches that fitted before the rounds are counted
-        if (out) n_splits = attn_used_splits(dtype, B, q_len, H, KVH, hd, n_splits);
+        if (out) n_splits = attn_used_splits(dtype, B, q_len, H, KVH, hd, max_len, n_splits);
         const dim3 mgrid(n_splits * (out ? n_rt : 1), KVH, B);
         uint16_t* direct = (out && n_splits == 1) ? reinterpret_cast<uint16_t*>(out) : nullptr;     // no merge needed
         // the splits combined inside the kernel: one row tile, exchange cells at hand, every workgroup resident at once

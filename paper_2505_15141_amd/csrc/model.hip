@@ -217,7 +217,7 @@ static FwdWs carve(const bs_model_cfg& c, int B, int q_len, int max_len, char* b
     w.part_gu = (float*)take(w.part_gu_bytes);
     w.part_d = (float*)take(w.part_d_bytes);
     const int splits = attn_splits(B, c.n_heads, max_len);         // one or two rows: all of them, the O projection merges
-    w.part_attn = (float*)take(M * c.n_heads * (M <= DEC_MAX_ROWS ? splits : attn_used_splits(c.dtype, B, q_len, c.n_heads, c.n_kv_heads, c.head_dim, splits)) *
+    w.part_attn = (float*)take(M * c.n_heads * (M <= DEC_MAX_ROWS ? splits : attn_used_splits(c.dtype, B, q_len, c.n_heads, c.n_kv_heads, c.head_dim, cache_rows(max_len), splits)) *
                                (size_t)(c.head_dim + 4) * 4);
     w.total = off;
     return w;

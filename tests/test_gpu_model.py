@@ -316,11 +316,10 @@ def test_one_and_two_rows_on_a_narrow_model_with_a_long_cache(B, n_prefix, q_len
         assert e1 < TOL["bf16"] and e2 < TOL["bf16"], (b, e1, e2)
 
 
-# 512 and 576 (sequence, head) pairs of 128: one split of the keys, and two in whole rounds; 192 pairs of 64: five splits and a merge
-# kernel, four with a single row per sequence
+# 512, 576 and 128 (sequence, head) pairs of 128: one split of the keys and several with a merge kernel; 192 pairs of 64: five splits
 @pytest.mark.parametrize("heads,hd,B,n_prefix,q_len,max_len", [
-    (32, 128, 16, 1000, 9, 1024), (32, 128, 16, 863, 1, 900), (36, 128, 16, 831, 2, 1700), (12, 64, 16, 2047, 1, 4200), (12, 64, 16, 1300, 3, 4200)])
-def test_key_splits_in_whole_rounds(heads, hd, B, n_prefix, q_len, max_len):
+    (32, 128, 16, 1000, 9, 1024), (32, 128, 16, 863, 1, 900), (36, 128, 16, 831, 2, 1700), (16, 128, 8, 1203, 5, 2400), (12, 64, 16, 2047, 1, 4200), (12, 64, 16, 1300, 3, 4200)])
+def test_key_splits_of_batches(heads, hd, B, n_prefix, q_len, max_len):
     """Sequences of different lengths, their new keys at different places of the last block; the wavefronts of a split walk
     from one to nine blocks, requested ahead."""
     c = synth.cfg(1, 256, heads, hd, 256, 512, dtype="bf16")
@@ -332,7 +331,7 @@ def test_key_splits_in_whole_rounds(heads, hd, B, n_prefix, q_len, max_len):
     q = torch.stack([dtoks[b, n:n + q_len] for b, n in enumerate(lens)]).contiguous()
     logits = bs().verify_forward(m, kv, q, torch.tensor(lens, dtype=torch.int32, device="cuda"))
     torch.cuda.synchronize()
-    for b in (0, 1, 7, B - 1):
+    for b in (0, 1, 6, B - 1):
         ref = forward(c, W, toks[b][:lens[b] + q_len], storage="bf16", last_rows=q_len)
         assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
 
