@@ -205,6 +205,38 @@ def test_every_way_of_finishing_split_items(c, n):
     assert np.max(np.abs(logits[0].cpu().numpy() - ref)) < TOL["bf16"]
 
 
+@pytest.mark.parametrize("heads,hd", [(16, 128), (32, 64)])
+def test_new_keys_of_many_rows_have_the_bits_of_the_written_rotation(heads, hd):
+    """Rows of +-1, one weight per key column and a norm_eps of 3 make every projected value exact (x w / 2), so the keys of a prompt
+    chunk of 4096 rows (whole items and split ones) must have the very bits of the rotation
+        r0 = fma(v0, cos, -(v1 sin)),  r1 = fma(v1, cos, v0 sin),
+    also the few that would round to the neighbouring bf16 value with the other product rounded first."""
+    c = dict(synth.cfg(1, 256, heads, hd, 256, 512), norm_eps=3.0)
+    d, n = c["d_model"], 4096
+    g = torch.Generator(device="cuda").manual_seed(5)
+    W = synth.make_weights_device(c, 5)
+    W["embed"] = (torch.randint(0, 2, (512, d), generator=g, device="cuda") * 2 - 1).bfloat16()
+    w = torch.randn(heads * hd, generator=g, device="cuda").bfloat16()
+    W["l0.wk"].zero_()
+    W["l0.wk"][torch.arange(heads * hd), torch.arange(heads * hd) % d] = w
+    m = bs().Model(c, W)
+    kv = bs().KV(m, 1, n)
+    toks = torch.randint(0, 512, (1, n), generator=g, device="cuda", dtype=torch.int32)
+    x = W["embed"][toks[0].long()].double()
+    bs().prefill(m, kv, toks, n, want_logits=False)
+    got = kv.buf.view(torch.bfloat16).view(2, heads, n, hd)[0].float()
+    v = (x[:, torch.arange(heads * hd, device="cuda") % d] * w.double() / 2).view(n, heads, hd).transpose(0, 1)
+    ang = torch.arange(n, device="cuda").double()[:, None] * c["rope_base"] ** (-2.0 * torch.arange(hd // 2, device="cuda").double() / hd)
+    cs, sn = torch.cos(ang).float().double(), torch.sin(ang).float().double()
+    v0, v1 = v[..., 0::2], v[..., 1::2]
+    f32 = lambda t: t.float().double()                       # a product of two float32 values and its sum with a third are near enough exact in 64 bits
+    key = lambda r0, r1: torch.stack((r0, r1), -1).flatten(-2).float().bfloat16().float()
+    want = key(v0 * cs - f32(v1 * sn), v1 * cs + f32(v0 * sn))
+    other = key(f32(v0 * cs) - v1 * sn, f32(v1 * cs) + v0 * sn)
+    assert int((want != other).sum()) >= 20
+    assert int((got != want).sum()) == 0
+
+
 # Row-major weights whose d_model or d_ff is no multiple of 32: QKV, gate/up, O and down then take different schedules, and the
 # sums of squares that one of them leaves are read by another.  O leaves 3, 2, 4 and 16 sums per row to a SwiGLU kernel, the
 # second model's down projection leaves 2 to a RoPE kernel.
