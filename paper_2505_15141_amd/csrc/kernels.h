@@ -69,6 +69,7 @@ int step_splits(const bs_model_cfg& c, int B, int max_len);
 // bytes of the exchange buffers X, Q, KVN, PA, ACT (each 256-byte aligned, in this order; off[i] = where buffer i starts)
 size_t step_exchange_bytes(const bs_model_cfg& c, int M, int splits, size_t off[5]);
 int step_grid();                         // workgroups of the resident kernel = compute units of the device
+int device_cus();                        // the same; without a device (sizes asked for ahead) those of a whole one
 int launch_step(const StepArgs& a, hipStream_t s);
 
 int gemm_splits(int dtype, int N, int K, int M);
@@ -125,8 +126,11 @@ size_t attn_cells_bytes(int rows, int H, int hd, int n_splits);
 bool attn_prompt_applies(int B, int q_len, int H, int KVH, int hd);
 int launch_attn_prompt(const float* q, const uint16_t* k_cache, const uint16_t* v_cache, const int32_t* pos, int B, int q_len, int H, int KVH,
                        int hd, int cache_len, uint16_t* out, size_t plane, hipStream_t s);
-// key splits that the launch uses over a cache of cache_len rows when it may use up to n_splits
-int attn_used_splits(int dtype, int B, int q_len, int H, int KVH, int hd, int cache_len, int n_splits);
+// key splits that a launch with `out` uses over a cache of cache_len rows when it may use up to n_splits, and whether its workgroups
+// combine them themselves (AttnCells) if the caller has cells
+constexpr int ATTN_CELL_ROWS = 16;
+struct AttnPlan { int splits; bool in_kernel; };
+AttnPlan attn_plan(int dtype, int B, int q_len, int H, int KVH, int hd, int cache_len, int n_splits);
 int launch_attention(int dtype, const float* q, const void* k_cache, const void* v_cache, const int32_t* pos, int B,
                      int q_len, int H, int KVH, int hd, int max_len, int n_splits, float* part, size_t plane, void* out, int out_tiled, const AttnCells* cells,
                      bool stream, hipStream_t s);

@@ -1474,7 +1474,7 @@ __global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, 
 // check): a workgroup hands its partial over in exchange cells instead of `part`, then the workgroup of split s combines,
 // for the rows r = S-1-s, 2S-1-s, ... of its head group (S splits; the last splits hold the fewest keys, often none), the
 // partials of all splits as they arrive (bounded polls) and writes the attention output planes -- the hand-over costs
-// about two microseconds where a merge kernel costs five.
+// about 0.5 us and 1.55 for each of these rows (attn_plan), where a merge kernel costs five.
 // The cells are all zero when the pass starts (prep kernel) and every layer hands over under its own flag.
 struct AttnMerge {
     void* cells;                 // [M][H][n_splits][HD + 4] cells: o[HD], max, sum, 2 pad
@@ -2013,54 +2013,72 @@ size_t attn_cells_bytes(int rows, int H, int hd, int n_splits) {
     return b < 2147483648.0 ? (size_t)b : 0;           // 32-bit cell offsets
 }
 
-// workgroups of the one-tile attention kernel that the device holds at the same time
+// workgroups of the one-tile attention kernel that the device holds at the same time; without a device (sizes asked for ahead)
+// those of a whole one, 2 and 4 a compute unit
 static size_t attn_resident_workgroups(int hd) {
     auto ask = [](bool wide) -> size_t {
         int per_cu = 0;
+        const int cus = step_grid();
+        if (cus <= 0) return (size_t)device_cus() * (wide ? 2 : 4);
         const hipError_t e = wide ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_mfma_kernel<128, 1, true, true>, 256, 0)
                                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_mfma_kernel<64, 1, true, true>, 256, 0);
-        const int cus = step_grid();
-        return (e == hipSuccess && per_cu > 0 && cus > 0) ? (size_t)per_cu * cus : 1;   // 1: never enough, the merge kernel runs
+        return (e == hipSuccess && per_cu > 0) ? (size_t)per_cu * cus : 1;   // 1: never enough, the merge kernel runs
     };
     static const size_t c128 = ask(true), c64 = ask(false);      // asked once (initialisation of a local static is thread-safe)
     return hd == 128 ? c128 : c64;
 }
 
-// Many query rows per head group in a pass that is too small for attn_prompt_kernel: one workgroup per group of row tiles and
-// only as many key splits as it takes to reach about a thousand workgroups; a single group keeps all the splits.
-int attn_used_splits(int dtype, int B, int q_len, int H, int KVH, int hd, int cache_len, int n_splits) {
-    if (dtype != BS_BF16) return n_splits;
-    if (attn_prompt_applies(B, q_len, H, KVH, hd)) return 1;
-    const int n_tiles = (H / KVH * q_len + 15) / 16, n_rt = n_tiles >= 2 ? (n_tiles + 1) / 2 : 1;
-    if (n_tiles <= 1) {
-        // One row tile: fewer splits than asked for where that is no slower.
-        const long long units = (long long)B * KVH;
-        int best = n_splits;
-        if (hd != 128) {
-            // head_dim 64, 4 workgroups per compute unit resident: the fewest splits with the least rounds of 1024 workgroups per split (16
-            // sequences of 4097 keys, 12 heads: 6 splits, 1152 workgroups, 36.5 us; 5 splits 35.2; two or fewer workgroups per compute
-            // unit have too little in flight: 9 sequences of 8000 keys, 2 splits, a whole pass 8 % longer than with 9).
-            for (int s = n_splits - 1; s >= 1; --s)
-                if ((units * s + 1023) / 1024 * best <= (units * best + 1023) / 1024 * s) best = s;
-            return best;
-        }
+// How a pass whose attention leaves the output itself (not the few-row schedule) cuts the keys when it may use up to n_splits parts.
+AttnPlan attn_plan(int dtype, int B, int q_len, int H, int KVH, int hd, int cache_len, int n_splits) {
+    AttnPlan p = {n_splits, false};
+    if (dtype != BS_BF16 || n_splits <= 1) return p;
+    if (attn_prompt_applies(B, q_len, H, KVH, hd)) { p.splits = 1; return p; }
+    const int n_tiles = (H / KVH * q_len + 15) / 16, n_rt = n_tiles >= 2 ? (n_tiles + 1) / 2 : 1, cus = device_cus();
+    if (n_tiles >= 2) {
+        // Two row tiles a wavefront: one workgroup per group of two and only as many key splits as it takes to reach about a
+        // thousand workgroups; a single group keeps all the splits.
+        const int want = (int)((4 * cus + (long long)B * KVH * n_rt - 1) / ((long long)B * KVH * n_rt));
+        if (n_rt > 1 && want < n_splits) p.splits = want;
+        return p;
+    }
+    // One row tile: fewer splits than asked for where that is no slower.
+    const long long units = (long long)B * KVH;
+    const int rows = B * q_len;
+    // Combined in the kernel: 3 to 16 rows whose workgroups all fit on the device, counted with the splits asked for, so that a pass of
+    // a batch, which may share the device with another stream's, does not come to wait for its own workgroups by being cut less.
+    p.in_kernel = rows > DEC_MAX_ROWS && rows <= ATTN_CELL_ROWS && units * n_splits <= (long long)attn_resident_workgroups(hd) &&
+                  attn_cells_bytes(rows, H, hd, n_splits) > 0;
+    if (hd != 128) {
+        // head_dim 64, 4 workgroups per compute unit resident: the fewest splits with the least rounds of 1024 workgroups per split (16
+        // sequences of 4097 keys, 12 heads: 6 splits, 1152 workgroups, 36.5 us; 5 splits 35.2; two or fewer workgroups per compute
+        // unit have too little in flight: 9 sequences of 8000 keys, 2 splits, a whole pass 8 % longer than with 9).
+        const int round = 4 * cus;
+        for (int s = n_splits - 1; s >= 1; --s)
+            if ((units * s + round - 1) / round * p.splits <= (units * p.splits + round - 1) / round * s) p.splits = s;
+    } else {
         // head_dim 128: the least estimated time.  A compute unit streams about 30 KB/us whether it holds one workgroup or two, so what counts
-        // is how evenly the workgroups fall on 256 compute units; all of them together get 6.4 TB/s, and the two bounds add like
-        // fourth powers; partials and their merge kernel cost 8 us.  16 sequences of 4105 keys, 32 heads: 2 splits 178.6 + 8.5 us, 1 split
+        // is how evenly the workgroups fall on the compute units; all of them together get 6.4 TB/s, and the two bounds add like
+        // fourth powers.  Partials and a merge kernel cost 5 us at 20 rows of 32 heads, 8 at 144, and 2 more where workgroups share compute
+        // units; combined in the kernel, a workgroup takes about 1.55 us for each of its share of the group's rows, one after the
+        // other.  16 sequences of 4105 keys, 32 heads: 2 splits 178.6 + 8.5 us, 1 split
         // 168.0.  Whole passes of the 7B shape: 6 sequences of 3007 keys, 1 / 2 / 3 / 4 / 5 splits 6240 / 6505 / 6627 / 6408 / 6596 us;
-        // 10 of 6004 keys, 1 / 2 / 3 / 4 splits 11281 / 10266 / 9831 / 9760; 4 of 2053 keys 4378 / 4128 / 4267 / 4158.
+        // 10 of 6004 keys, 1 / 2 / 3 / 4 splits 11281 / 10266 / 9831 / 9760; 4 of 2053 keys 4378 / 4128 / 4267 / 4158.  Eight layers of it, one
+        // sequence, splits combined in the kernel, cache of 900: 3 rows, 1 / 2 splits 781 / 761 us, 5 rows 788 / 782, 9 rows 821 / 836; of 1280:
+        // 9 rows, 1 / 2 / 3 splits 858 / 850 / 813, 16 rows 931 / 962 / 911; of 8192: 9 rows, 4 / 6 / 8 / 16 splits 995 / 928 / 894 / 924; 3 sequences
+        // of 5 rows, cache of 1280: 927 / 894 / 921.  With a merge kernel: 2 sequences of 9 rows, cache of 600, 1 / 2 splits 926 / 932, of 900 955 / 943;
+        // 3 of 6 rows, of 2304, 2 / 5 splits 1024 / 1011; 6 of 5 rows, of 2304, 1 / 4 splits 1227 / 1240.  More splits than that only for a tenth of the estimate.
         const double unit_mb = 4e-6 * hd * cache_len, f = units * unit_mb / 6.4;
+        const int group_rows = H / KVH * q_len;
         double best_us = 1e30;
         for (int s = 1; s <= n_splits; ++s) {
-            const double c = (double)((units * s + 255) / 256) / s * unit_mb / 0.030;
-            const double us = sqrt(sqrt(c * c * c * c + f * f * f * f)) + (s > 1 ? 8.0 : 0.0);
-            if (us < 0.999 * best_us) { best = s; best_us = us; }
+            const double c = (double)((units * s + cus - 1) / cus) / s * unit_mb / 0.030;
+            const double combine_us = s == 1 ? 0.0 : p.in_kernel ? 0.5 + 1.55 * ((group_rows + s - 1) / s) : 4.6 + 8e-4 * rows * H + (units * s > cus ? 2.0 : 0.0);
+            const double us = sqrt(sqrt(c * c * c * c + f * f * f * f)) + combine_us;
+            if (us < (p.in_kernel ? 0.9 : 0.999) * best_us) { p.splits = s; best_us = us; }
         }
-        return best;
     }
-    if (n_rt <= 1) return n_splits;
-    const int want = (int)((1024 + (long long)B * KVH * n_rt - 1) / ((long long)B * KVH * n_rt));
-    return want < n_splits ? want : n_splits;
+    p.in_kernel = p.in_kernel && p.splits > 1;
+    return p;
 }
 
 int launch_attention(int dtype, const float* q, const void* k_cache, const void* v_cache, const int32_t* pos, int B,
@@ -2078,15 +2096,15 @@ int launch_attention(int dtype, const float* q, const void* k_cache, const void*
         // queries: 287 -> 225 us per layer at batch 32 / 8192 keys; prompt chunks of a batch: 7-10 % off the prompt pass)
         const int nt = (n_tiles >= 2) ? 2 : 1;
         const int n_rt = (n_tiles + nt - 1) / nt;
-        const size_t asked = (size_t)n_splits * KVH * B;           // in-kernel merging stays with the launches that fitted before the rounds are counted
-        if (out) n_splits = attn_used_splits(dtype, B, q_len, H, KVH, hd, max_len, n_splits);
+        const AttnPlan plan = attn_plan(dtype, B, q_len, H, KVH, hd, max_len, n_splits);
+        if (out) n_splits = plan.splits;
         const dim3 mgrid(n_splits * (out ? n_rt : 1), KVH, B);
         uint16_t* direct = (out && n_splits == 1) ? reinterpret_cast<uint16_t*>(out) : nullptr;     // no merge needed
         // the splits combined inside the kernel: one row tile, exchange cells at hand, every workgroup resident at once
         AttnMerge mg = {};
         mg.tiled = out_tiled;
-        if (cells && cells->buf && out && !direct && nt == 1 && n_rt == 1 && attn_cells_bytes(B * q_len, H, hd, n_splits) <= cells->bytes &&
-            asked <= (hd == 128 ? 512 : 1024) && (size_t)n_splits * KVH * B <= attn_resident_workgroups(hd)) {
+        if (cells && cells->buf && out && plan.in_kernel) {
+            BS_REQUIRE(attn_cells_bytes(B * q_len, H, hd, n_splits) <= cells->bytes, BS_EWORKSPACE, "attention: %zu bytes of exchange cells", cells->bytes);
             mg.cells = cells->buf; mg.out = reinterpret_cast<uint16_t*>(out); mg.plane = plane;
             mg.flag = cells->flag; mg.spin_limit = cells->spin_limit; mg.status = cells->status;
         }

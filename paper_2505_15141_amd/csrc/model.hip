@@ -199,7 +199,9 @@ static FwdWs carve(const bs_model_cfg& c, int B, int q_len, int max_len, char* b
     // Up to 16 rows, a single sequence being verified as a rule: workgroups that wait for each other need the compute units to
     // themselves, and batches may be run on several streams side by side.  At 17..32 rows a merge kernel follows instead (20 rows at 2048
     // keys: two layers of the 7B shape 335 -> 334 us, four layers of its draft 218 -> 226).
-    w.acells_bytes = (c.dtype == BS_BF16 && M <= 16 && M > 2) ? attn_cells_bytes((int)M, c.n_heads, c.head_dim, attn_splits(B, c.n_heads, max_len)) : 0;
+    const int splits = attn_splits(B, c.n_heads, max_len);
+    const AttnPlan att = attn_plan(c.dtype, B, q_len, c.n_heads, c.n_kv_heads, c.head_dim, cache_rows(max_len), splits);
+    w.acells_bytes = att.in_kernel ? attn_cells_bytes((int)M, c.n_heads, c.head_dim, att.splits) : 0;
     w.acells = take(w.acells_bytes);
     // partial sums: those of launch_gemm, or of the items that a many-row projection with its consumer's work splits (big_plan)
     auto big = [&](int epi, size_t N, size_t K, int ks, bool* use, int* tiles) -> size_t {
@@ -216,9 +218,8 @@ static FwdWs carve(const bs_model_cfg& c, int B, int q_len, int max_len, char* b
     w.part_o = (float*)take(w.part_o_bytes);
     w.part_gu = (float*)take(w.part_gu_bytes);
     w.part_d = (float*)take(w.part_d_bytes);
-    const int splits = attn_splits(B, c.n_heads, max_len);         // one or two rows: all of them, the O projection merges
-    w.part_attn = (float*)take(M * c.n_heads * (M <= DEC_MAX_ROWS ? splits : attn_used_splits(c.dtype, B, q_len, c.n_heads, c.n_kv_heads, c.head_dim, cache_rows(max_len), splits)) *
-                               (size_t)(c.head_dim + 4) * 4);
+    // one or two rows: all the splits, the O projection merges
+    w.part_attn = (float*)take(M * c.n_heads * (M <= DEC_MAX_ROWS ? splits : att.splits) * (size_t)(c.head_dim + 4) * 4);
     w.total = off;
     return w;
 }
@@ -236,6 +237,16 @@ static size_t carve_max(const bs_model_cfg& c, int B, int max_q_len, int max_len
 extern "C" __attribute__((visibility("default"))) size_t bs_forward_workspace_bytes(const bs_model_cfg* c, int B, int max_q_len, int max_len) {
     if (!c || B < 1 || max_q_len < 1 || max_len < 1) return 0;
     return carve_max(*c, B, max_q_len, max_len);
+}
+
+extern "C" __attribute__((visibility("default"))) int bs_attention_splits(const bs_model_cfg* c, int B, int q_len, int max_len, int* splits, int* in_kernel) {
+    BS_REQUIRE(c && splits && in_kernel, BS_EINVAL, "bs_attention_splits: NULL argument");
+    const int rc = check_cfg(c, "bs_attention_splits");
+    if (rc != BS_OK) return rc;
+    BS_REQUIRE(B >= 1 && q_len >= 1 && max_len >= 1 && (long long)B * q_len <= (1 << 20), BS_ESHAPE, "bs_attention_splits: B=%d q_len=%d max_len=%d", B, q_len, max_len);
+    const AttnPlan p = attn_plan(c->dtype, B, q_len, c->n_heads, c->n_kv_heads, c->head_dim, cache_rows(max_len), attn_splits(B, c->n_heads, max_len));
+    *splits = p.splits; *in_kernel = p.in_kernel ? 1 : 0;
+    return BS_OK;
 }
 
 // One pass of the model over q_len tokens per sequence (see bs_verify_forward).  kv position of query j is
@@ -344,7 +355,7 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
     }
     int ssq_n = 0;                            // sums of squares per row that the latest writer of w.ssq left there
     // the attention's key splits combined inside its kernel (exchange cells, cleared by the prep kernel above)
-    const bool in_kernel_merge = w.acells_bytes > 0 && splits > 1 && c.n_layers < 65536;
+    const bool in_kernel_merge = w.acells_bytes > 0 && c.n_layers < 65536;
     AttnCells ac = {w.acells, w.acells_bytes, 0u, g_step_polls.load(), w.status};
     BS_TRY(launch_embed(dt, w.tok, m->embed, M, d, w.x, s));
     for (int l = 0; l < c.n_layers; ++l) {

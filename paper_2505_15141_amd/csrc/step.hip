@@ -834,6 +834,7 @@ int step_grid() {
     }
     return cus;
 }
+int device_cus() { return step_grid() >= 8 ? step_grid() : 256; }
 
 int launch_step(const StepArgs& a_in, hipStream_t s) {
     StepArgs a = a_in;

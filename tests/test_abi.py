@@ -10,7 +10,7 @@ import pytest
 from conftest import ROOT
 from oracle import philox
 from oracle.bandit import UCBSpec, EXP3Spec
-from paper_2505_15141_amd import binding as bs
+from paper_2505_15141_amd import binding as bs, synth
 
 
 def test_library_exports_every_declared_symbol():
@@ -99,6 +99,24 @@ def test_prompt_workspace_is_that_of_its_two_chunk_lengths(B, n):
     if chunk >= 1000:
         assert fastest(prompt, n) * 20 < fastest(upto, chunk)
     assert [prompt(C.byref(cfg), *a) for a in ((0, 1, 8), (1, 0, 8), (1, 1, 0))] == [0, 0, 0] and prompt(None, 1, 1, 8) == 0
+
+
+def test_key_splits_follow_what_combining_them_costs():
+    """The 7B shape and a grouped-query one.  In the kernel every workgroup combines its share of a group's rows one after the other: a
+    cache of 900 rows is worth two parts with 3 and 5 rows, not with 9 or 16; a merge kernel behind 20 rows costs less than one behind 144."""
+    c, g = synth.LLAMA7B_TARGET, synth.LLAMA3_8B_TARGET
+    for B, q_len, max_len, want in [(1, 3, 900, (2, True)), (1, 5, 900, (2, True)), (1, 9, 900, (1, False)), (1, 9, 1280, (3, True)), (1, 16, 1024, (1, False)),
+                                    (2, 5, 960, (2, True)), (3, 5, 900, (2, True)), (3, 5, 1280, (2, True)), (4, 4, 1248, (2, True)), (1, 9, 8192, (8, True)),
+                                    (1, 9, 8448, (8, False)), (4, 5, 900, (2, False)), (2, 9, 600, (1, False)), (6, 5, 2304, (1, False)), (4, 5, 2304, (2, False))]:
+        assert bs.attention_splits(c, B, q_len, max_len) == want, (B, q_len, max_len)
+    assert bs.attention_splits(g, 1, 4, 1024) == (1, False) and bs.attention_splits(g, 1, 4, 1929) == (4, True)
+    assert bs.attention_splits(synth.LLAMA7B_DRAFT, 16, 1, 4352) == (5, False)
+    for B in range(1, 17):                           # workgroups that wait for each other: 3 to 16 rows, all of them resident
+        for q_len in range(1, 17):
+            n, own = bs.attention_splits(c, B, q_len, 4352)
+            assert n >= 1 and (not own or 3 <= B * q_len <= 16 and 1 < n and 32 * B * n <= 512)
+    with pytest.raises(bs.BanditSpecError):
+        bs.attention_splits(c, 0, 1, 100)
 
 
 def test_host_side_argument_checks_launch_nothing():
