@@ -217,9 +217,10 @@ int bs_verify_forward(const bs_model* m, const bs_kv* kv, const int32_t* dev_q_t
  * not valid -- and sets bit 16 of the device status word; no launch ever waits without end.  Applies to passes enqueued
  * after the call.  Meant for tests of that path. */
 int bs_step_poll_limit(unsigned polls);
-/* Host only, for tests: into how many parts the attention of a bs_verify_forward pass of more than two rows cuts the keys, and
- * (in_kernel = 1) whether its workgroups combine them themselves instead of a merge kernel. */
-int bs_attention_splits(const bs_model_cfg* cfg, int B, int q_len, int max_len, int* splits, int* in_kernel);
+/* Host only, for tests: into how many parts the attention of a bs_verify_forward pass of more than two rows cuts the keys of a
+ * sequence, up to how many those of one much longer than the others, and (in_kernel = 1) whether its workgroups combine them
+ * themselves instead of a merge kernel. */
+int bs_attention_splits(const bs_model_cfg* cfg, int B, int q_len, int max_len, int* splits, int* most, int* in_kernel);
 
 /* Prompt processing: fills the cache for positions 0..n-1 of every sequence (same n for all), in
  * chunks through the same kernels.  dev_tokens [B, token_stride] int32, n <= token_stride.

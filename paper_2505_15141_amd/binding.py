@@ -90,7 +90,7 @@ _sig("bs_spec_round", C.c_int, vp, C.c_int, vp, vp, vp)
 _sig("bs_round_status", C.c_int, vp, C.POINTER(i32), vp)
 _sig("bs_draft_propose", C.c_int, vp, C.c_int, vp, vp, vp)
 _sig("bs_step_poll_limit", C.c_int, C.c_uint)
-_sig("bs_attention_splits", C.c_int, C.POINTER(ModelCfg), C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int))
+_sig("bs_attention_splits", C.c_int, C.POINTER(ModelCfg), C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int))
 _sig("bs_profile_enable", C.c_int, C.c_int)
 _sig("bs_profile_collect", C.c_int, C.c_int, C.POINTER(f64), C.POINTER(f64), C.POINTER(C.c_longlong))
 _sig("bs_round_debug_views", C.c_int, vp, C.POINTER(vp), C.POINTER(vp), C.POINTER(vp), C.POINTER(vp))
@@ -392,10 +392,11 @@ def step_poll_limit(polls=0):
 
 
 def attention_splits(c, B, q_len, max_len):
-    """(parts into which the attention of a pass cuts the keys, whether it combines them itself), see bs_attention_splits."""
-    n, own = C.c_int(), C.c_int()
-    check(lib.bs_attention_splits(C.byref(model_cfg(c)), B, q_len, max_len, C.byref(n), C.byref(own)))
-    return n.value, bool(own.value)
+    """(parts into which the attention of a pass cuts a sequence's keys, of a much longer one at most, whether it combines them
+    itself), see bs_attention_splits."""
+    n, most, own = C.c_int(), C.c_int(), C.c_int()
+    check(lib.bs_attention_splits(C.byref(model_cfg(c)), B, q_len, max_len, C.byref(n), C.byref(most), C.byref(own)))
+    return n.value, most.value, bool(own.value)
 
 
 def profile_enable(on=True):

@@ -97,11 +97,14 @@ int launch_gemm_big_fused(int epi, const GemmArgs& g, const DecArgs& e, float* p
 size_t packed_elems(int N, int K);                       // elements of the tiled copy of an [N][K] matrix
 int launch_pack_weights(const void* src, void* dst, int N, int K, hipStream_t s);
 
+// ap.parts != nullptr: also into how many parts the attention cuts the keys of every sequence, `few` or, of one much longer than the
+// others, up to `most`, and the work items of one kv head, (sequence | part << 16 | parts << 24) << 32 | first position (32 bits), -1 behind them
+struct AttnParts { int32_t* parts; long long* items; int few, most, n_items, kv_heads, cus; };
 // clear_bytes > 0: also zeroes that many bytes at `clear` (a multiple of 16, 16-byte aligned): the exchange cells of the
 // resident step kernel that follows
 int launch_prep(const int32_t* q_tokens, int q_stride, const int32_t* kv_len, int kv_base, int B, int q_len,
                 int max_len, int V, int hd, float rope_base, int32_t* pos, int32_t* tok, float2* rope,
-                int32_t* status, void* clear, size_t clear_bytes, hipStream_t s);
+                int32_t* status, void* clear, size_t clear_bytes, const AttnParts& ap, hipStream_t s);
 int launch_embed(int dtype, const int32_t* tok, const void* embed, int M, int d, float* x, hipStream_t s);
 int launch_rmsnorm(int dtype, float* x, const float* pend, int pend_ks, size_t pend_stride, const float* gain, int d,
                    float eps, int n_seq, int rows_in, int rows_out, size_t plane, void* out, hipStream_t s);
@@ -126,13 +129,14 @@ size_t attn_cells_bytes(int rows, int H, int hd, int n_splits);
 bool attn_prompt_applies(int B, int q_len, int H, int KVH, int hd);
 int launch_attn_prompt(const float* q, const uint16_t* k_cache, const uint16_t* v_cache, const int32_t* pos, int B, int q_len, int H, int KVH,
                        int hd, int cache_len, uint16_t* out, size_t plane, hipStream_t s);
-// key splits that a launch with `out` uses over a cache of cache_len rows when it may use up to n_splits, and whether its workgroups
-// combine them themselves (AttnCells) if the caller has cells
+// key splits that a launch with `out` uses over a cache of cache_len rows when it may use up to n_splits: `splits`, or where `most` is
+// more a count for every sequence between the two (AttnParts); and whether its workgroups combine them themselves (AttnCells)
+// if the caller has cells.  `part` holds `most` partials a row.
 constexpr int ATTN_CELL_ROWS = 16;
-struct AttnPlan { int splits; bool in_kernel; };
+struct AttnPlan { int splits, most, n_items; bool in_kernel; };
 AttnPlan attn_plan(int dtype, int B, int q_len, int H, int KVH, int hd, int cache_len, int n_splits);
 int launch_attention(int dtype, const float* q, const void* k_cache, const void* v_cache, const int32_t* pos, int B,
                      int q_len, int H, int KVH, int hd, int max_len, int n_splits, float* part, size_t plane, void* out, int out_tiled, const AttnCells* cells,
-                     bool stream, hipStream_t s);
+                     const AttnParts* ap, bool stream, hipStream_t s);
 
 }  // namespace bs

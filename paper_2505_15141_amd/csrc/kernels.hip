@@ -32,10 +32,50 @@ namespace bs {
 // for a prompt of 1023 rows took 140 us).  pos[m] = kv_len[b] + kv_base + j, or -1 for a sequence that would run
 // past max_len (then nothing of it is written anywhere).  tok[m] = token clamped into [0, V).
 constexpr int PREP_ROWS = 32;
+
+// The attention's work items where long sequences are cut into more parts (attn_plan): how many parts sequence b has, and its items.  Long
+// sequences come first, so that their parts fall on different compute units.  8 layers of the 7B shape, 8 sequences of 9 rows, one of
+// 8000 keys and seven of 500: 2388 us with one part for all, 2014 with the long one's other parts behind the first part of every
+// sequence, where two of them came to share a compute unit, 1865 like this; all of 8000 keys 2680 either way.  12 layers of 12 heads of 64, 32
+// sequences of one row, one of 8000 keys and the others of 300: 1103 -> 986, all of 8000 2269 -> 2268, all of 4096 1381 -> 1392.  One
+// wavefront per sequence, each with its own look at all lengths.
+__device__ __forceinline__ void attn_deal(const AttnParts& ap, const int32_t* __restrict__ kv_len, int kv_base, int q_len, int max_len, int B, int b, int pos0) {
+    const int lane = threadIdx.x;
+    auto keys = [&](int i) -> long long {
+        const int k = (kv_len ? kv_len[i] : 0) + kv_base;
+        return k >= 0 && k + q_len <= max_len ? k + q_len : 0;
+    };
+    auto total = [](long long v) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        return v;
+    };
+    long long sum = 0;
+    for (int i = lane; i < B; i += 64) sum += keys(i);
+    sum = total(sum);
+    auto cut = [&](long long own) -> int {                         // a long sequence: as many parts as compute units it would keep busy at an equal share
+        const long long share = sum > 0 ? own * ap.cus / (sum * ap.kv_heads) : 0;
+        return 4 * own * B > 5 * sum && share > ap.few ? (int)min(share, (long long)ap.most) : ap.few;
+    };
+    long long extra = 0, extra_before = 0, n_long = 0, long_before = 0;
+    for (int i = lane; i < B; i += 64) {
+        const int n = cut(keys(i)) - ap.few;
+        extra += n; n_long += n > 0;
+        if (i < b) { extra_before += n; long_before += n > 0; }
+    }
+    extra = total(extra); extra_before = total(extra_before); n_long = total(n_long); long_before = total(long_before);
+    const int own = pos0 >= 0 ? cut(pos0 + q_len) : ap.few;
+    const int first = own > ap.few ? (int)(long_before * ap.few + extra_before) : (int)(extra + (n_long + b - long_before) * ap.few);
+    if (lane < own) ap.items[first + lane] = (long long)(b | lane << 16 | own << 24) << 32 | (unsigned)pos0;
+    if (lane == 0) ap.parts[b] = own;
+    if (b == 0)
+        for (int i = (int)extra + B * ap.few + lane; i < ap.n_items; i += 64) ap.items[i] = -1;
+}
+
 __global__ void prep_kernel(const int32_t* __restrict__ q_tokens, int q_stride, const int32_t* __restrict__ kv_len,
                             int kv_base, int q_len, int max_len, int V, int half_hd, float rope_base,
                             int32_t* __restrict__ pos, int32_t* __restrict__ tok, float2* __restrict__ rope,
-                            int32_t* __restrict__ status, int B, uint4* __restrict__ clear, size_t clear16) {
+                            int32_t* __restrict__ status, int B, uint4* __restrict__ clear, size_t clear16, AttnParts ap) {
     const int jblocks = (q_len + PREP_ROWS - 1) / PREP_ROWS;
     if ((int)blockIdx.x >= B * jblocks) {             // the blocks behind the sequences zero the exchange cells
         const size_t nb = gridDim.x - B * jblocks;
@@ -47,6 +87,7 @@ __global__ void prep_kernel(const int32_t* __restrict__ q_tokens, int q_stride, 
     const int kvl = (kv_len ? kv_len[b] : 0) + kv_base;
     const bool ok = kvl >= 0 && kvl + q_len <= max_len;
     if (!ok && threadIdx.x == 0 && j0 == 0) atomicOr(status, 1);
+    if (ap.parts && j0 == 0 && threadIdx.x < 64) attn_deal(ap, kv_len, kv_base, q_len, max_len, B, b, ok ? kvl : -1);
     for (int j = j0 + threadIdx.x; j < j1; j += blockDim.x) {
         const int m = b * q_len + j;
         int t = q_tokens[(size_t)b * q_stride + j];
@@ -1482,32 +1523,48 @@ struct AttnMerge {
     int tiled;                   // rows of the tiled planes, 0: row-major (also of the planes of a single split)
     unsigned flag, spin_limit;
     int32_t* status;             // bit 16: a poll ran out of patience
+    unsigned* tickets;           // [B][KVH], with `parts`: the workgroups of a sequence cut into several parts that have handed over, of all layers
 };
 
 // AHEAD (one row tile): the next block is requested into the registers of the block at hand as they become free.  For launches whose
 // wavefronts walk many blocks (launch_attention); a few blocks are not worth the larger kernel (batch 1, 1682 keys in 4 splits: 17.0 us
 // without, 17.7 with).
-template <int HD, int NT, bool STREAM, bool AHEAD>
+// PARTS (one row tile): every sequence has its own number of splits of the n_splits that `part` and the cells have room for;
+// grid (KVH, items) with the sequence, its split and its first position from the items (attn_deal).  Where direct_out is given, a sequence of
+// one part writes the output itself, and of one of several the last workgroup to hand over combines the rows; nobody waits for a
+// workgroup that has not started.  A variant of its own: in the other kernels the larger code cost 0.8 us a launch (batch 16, head_dim 64).
+template <int HD, int NT, bool STREAM, bool AHEAD, bool PARTS>
 __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_kernel(const float* __restrict__ q, const uint16_t* __restrict__ k_cache,
                                                         const uint16_t* __restrict__ v_cache,
                                                         const int32_t* __restrict__ pos, int q_len, int H, int KVH,
                                                         int cache_len, float scale, float* __restrict__ part, int n_splits,
-                                                        uint16_t* __restrict__ direct_out, size_t plane, AttnMerge mg) {
+                                                        uint16_t* __restrict__ direct_out, size_t plane, AttnMerge mg,
+                                                        const long long* __restrict__ items) {
     constexpr int DS = HD / 32, DT = HD / 16;
     constexpr int PC = HD + 4;                   // cells of one partial
     __shared__ float wm[4][16], wl[4][16];
     __shared__ float wo[4][16][HD + 1];
     // blockIdx.x = (group of NT row tiles, split of the keys): with many query rows (a prompt chunk) the groups are
     // spread over workgroups and the keys over few splits; with one group all of gridDim.x are key splits
-    const int split = blockIdx.x % n_splits, rt = blockIdx.x / n_splits, n_rt = gridDim.x / n_splits;
-    const int kvh = blockIdx.y, b = blockIdx.z;
+    int split, rt, n_rt, kvh, b, used, pos0;
+    if constexpr (PARTS) {
+        const long long item = items[blockIdx.y];    // one load for all of it; behind the last item b and pos0 are negative
+        const int deal = (int)(item >> 32);
+        kvh = blockIdx.x; b = deal < 0 ? -1 : deal & 0xFFFF; split = (deal >> 16) & 0xFF; used = deal >> 24; rt = 0; n_rt = 1;
+        pos0 = (int)item;
+        if (used > 1) direct_out = nullptr;
+    } else {
+        split = blockIdx.x % n_splits; rt = blockIdx.x / n_splits; n_rt = gridDim.x / n_splits; kvh = blockIdx.y; b = blockIdx.z; used = n_splits;
+        pos0 = pos[b * q_len];
+    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int li = lane & 15, lq = lane >> 4;
     const int G = H / KVH, R = G * q_len;
     const int m_first = b * q_len;
-    const int pos0 = pos[m_first];
     const size_t pstride = (size_t)HD + 4;       // o[HD], max, sum, 2 pad: rows stay 16-byte aligned
+    const bool in_cells = PARTS ? mg.cells && !direct_out : mg.cells != nullptr;
     if (pos0 < 0) {                                  // sequence skipped: empty partials (zeros when writing the output itself)
+        if (PARTS && b < 0) return;
         if (direct_out) {
             for (int idx = threadIdx.x + rt * 256; idx < R * HD; idx += 256 * n_rt) {
                 const int r = idx / HD, d = idx % HD;
@@ -1516,7 +1573,7 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
             }
             return;
         }
-        if (NT == 1 && mg.cells) {                   // no workgroup of this sequence polls: the rows' owners write zeros
+        if (NT == 1 && in_cells) {                   // no workgroup of this sequence polls: the rows' owners write zeros
             for (int rr = n_splits - 1 - split; rr < R; rr += n_splits) {
                 const int m = m_first + rr % q_len, head = kvh * G + rr / q_len;
                 for (int d = threadIdx.x; d < HD; d += 256)
@@ -1540,7 +1597,7 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
         const int r_last = min(r0 + 16 * NT - 1, R - 1);
         const int qi_max = (r0 / q_len == r_last / q_len) ? r_last % q_len : q_len - 1;
         const int nblk = (pos0 + qi_max + 1 + 31) / 32;
-        const int per = (nblk + n_splits - 1) / n_splits;
+        const int per = (nblk + used - 1) / used;
         const int b_begin = split * per, b_end = min(nblk, b_begin + per);
         bool rvalid[NT];
         int row_pos[NT];
@@ -1724,7 +1781,7 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
                     Act<uint16_t>::store(direct_out, plane, mg.tiled ? xt_index(m, head * HD + d, mg.tiled) : ((size_t)m * H + head) * HD + d, lv > 0.f ? ov / lv : 0.f);
                     continue;
                 }
-                if (NT == 1 && mg.cells) {           // hand the partial over in cells
+                if (NT == 1 && in_cells) {           // hand the partial over in cells
                     const DevBuf bc = dev_buf(mg.cells);
                     const int c0 = (((m_first + qq) * H + kvh * G + gg) * n_splits + split) * PC;
                     st_cell1(bc, c0 + d, ov, mg.flag);
@@ -1738,7 +1795,75 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
         }
     }
     if constexpr (NT == 1) {
-        if (!mg.cells) return;
+        if (!in_cells) return;
+        if constexpr (PARTS) {                       // the sequence's last workgroup combines all rows
+            __shared__ int last;
+            __syncthreads();
+            if (threadIdx.x == 0) last = atomicAdd(mg.tickets + b * KVH + kvh, 1u) + 1u == mg.flag * used;
+            __syncthreads();
+            if (!last) return;
+            // four (row, head-dim element) pairs of four parts each in flight a lane: 9 rows in 4 parts are two trips to memory
+            // (two of two at head_dim 64, which has no registers for more)
+            constexpr int IT = HD == 128 ? 4 : 2, PU = IT;
+            const DevBuf bc = dev_buf(mg.cells);
+            for (int i0 = threadIdx.x; i0 < R * HD; i0 += 256 * IT) {
+                float mm[IT], o[IT], l[IT];
+                int cell[IT];
+                size_t dst[IT];
+#pragma unroll
+                for (int it = 0; it < IT; ++it) {
+                    const int idx = min(i0 + 256 * it, R * HD - 1), r = idx / HD, d = idx % HD, m = m_first + r % q_len, head = kvh * G + r / q_len;
+                    mm[it] = -INFINITY; o[it] = 0.f; l[it] = 0.f;
+                    cell[it] = (m * H + head) * n_splits * PC;
+                    dst[it] = mg.tiled ? xt_index(m, head * HD + d, mg.tiled) : ((size_t)m * H + head) * HD + d;
+                }
+                for (int s0 = 0; s0 < used; s0 += PU) {
+                    u32x2 co[IT][PU];
+                    u32x4 cml[IT][PU];
+                    unsigned spins = 0;
+                    while (true) {                          // handed over, so there at once
+                        asm volatile("" ::: "memory");
+                        bool ok = true;
+#pragma unroll
+                        for (int it = 0; it < IT; ++it)
+#pragma unroll
+                            for (int u = 0; u < PU; ++u) {
+                                const int c0 = cell[it] + min(s0 + u, used - 1) * PC;
+                                co[it][u] = ld_cell1(bc, c0 + (i0 + 256 * it) % HD);
+                                cml[it][u] = ld_cells2(bc, c0 + HD);
+                            }
+#pragma unroll
+                        for (int it = 0; it < IT; ++it)
+#pragma unroll
+                            for (int u = 0; u < PU; ++u) ok = ok && co[it][u].y == mg.flag && cml[it][u].y == mg.flag && cml[it][u].w == mg.flag;
+                        if (ok) break;
+                        if (++spins > mg.spin_limit) { atomicOr(mg.status, 16); break; }
+                    }
+#pragma unroll
+                    for (int it = 0; it < IT; ++it) {
+                        float gm = mm[it];
+#pragma unroll
+                        for (int u = 0; u < PU; ++u) gm = fmaxf(gm, __uint_as_float(cml[it][u].x));       // past the end: the last part again
+                        if (gm == -INFINITY) continue;
+                        const float keep = __expf(mm[it] - gm);       // 0 when nothing was accumulated yet
+                        o[it] *= keep; l[it] *= keep;
+#pragma unroll
+                        for (int u = 0; u < PU; ++u) {
+                            const float mv = __uint_as_float(cml[it][u].x);
+                            if (s0 + u >= used || mv == -INFINITY) continue;
+                            const float f = __expf(mv - gm);
+                            l[it] += __uint_as_float(cml[it][u].z) * f;
+                            o[it] += __uint_as_float(co[it][u].x) * f;
+                        }
+                        mm[it] = gm;
+                    }
+                }
+#pragma unroll
+                for (int it = 0; it < IT; ++it)
+                    if (i0 + 256 * it < R * HD) Act<uint16_t>::store(mg.out, mg.plane, dst[it], l[it] > 0.f ? o[it] / l[it] : 0.f);
+            }
+            return;
+        }
         // ---- combine the splits of this workgroup's rows: lane = (head-dim element d, share sp0 of the splits) ----
         constexpr int P = 256 / HD;                  // HD threads per share; sp0 is uniform in a wavefront
         constexpr int MU = 8;                        // splits a lane polls in one round (all loads in flight together)
@@ -1808,12 +1933,16 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
 // grid (M*H), threads hd: combine the splits, normalise, store in the storage dtype.  One pass: the (max, sum, o) of
 // 16 splits are requested together and folded into a running (max, sum, o) -- the partials were written by other dies
 // a moment ago, so every dependent round of loads is a trip to memory.
-template <typename T>
-__global__ void attn_merge_kernel(const float* __restrict__ part, int n_splits, int hd, size_t plane, void* __restrict__ out, int tiled_H, int tiled_R) {
+// PARTS: parts[b] of a sequence's n_splits partials are there, the others hold anything (seq_rows of the grid are one sequence); where
+// there is only one the output is there, too.
+template <typename T, bool PARTS>
+__global__ void attn_merge_kernel(const float* __restrict__ part, int n_splits, int hd, size_t plane, void* __restrict__ out, int tiled_H, int tiled_R,
+                                  const int32_t* __restrict__ parts, int seq_rows) {
     const size_t mh = blockIdx.x;
     const int d = threadIdx.x;
     const size_t pstride = (size_t)hd + 4;       // o[hd], max, sum, 2 pad: rows stay 16-byte aligned
     const float* base = part + mh * n_splits * pstride;
+    const int used = PARTS ? parts[blockIdx.x / seq_rows] : n_splits;      // asked for together with the first partials
     float mm = -INFINITY, o = 0.f, l = 0.f;
     for (int s0 = 0; s0 < n_splits; s0 += 16) {
         float mv[16], lv[16], ov[16];
@@ -1821,8 +1950,10 @@ __global__ void attn_merge_kernel(const float* __restrict__ part, int n_splits, 
         for (int u = 0; u < 16; ++u) {
             const float* ps = base + (size_t)min(s0 + u, n_splits - 1) * pstride;
             mv[u] = ps[hd]; lv[u] = ps[hd + 1]; ov[u] = ps[d];
-            if (s0 + u >= n_splits) mv[u] = -INFINITY;
         }
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            if (s0 + u >= used) mv[u] = -INFINITY;
         float gm = mm;
 #pragma unroll
         for (int u = 0; u < 16; ++u) gm = fmaxf(gm, mv[u]);
@@ -1838,6 +1969,7 @@ __global__ void attn_merge_kernel(const float* __restrict__ part, int n_splits, 
         }
         mm = gm;
     }
+    if (PARTS && used == 1) return;
     // tiled_H > 0: planes of tiled_R rows in the layout of the whole-K projections (xt_index), row = mh / H, column = (mh % H) * hd + d
     const size_t idx = tiled_H > 0 ? xt_index((int)(mh / tiled_H), (int)(mh % tiled_H) * hd + d, tiled_R) : mh * hd + d;
     Act<T>::store(out, plane, idx, l > 0.f ? o / l : 0.f);
@@ -1846,14 +1978,14 @@ __global__ void attn_merge_kernel(const float* __restrict__ part, int n_splits, 
 // ---- launchers -----------------------------------------------------------------------------------
 int launch_prep(const int32_t* q_tokens, int q_stride, const int32_t* kv_len, int kv_base, int B, int q_len,
                 int max_len, int V, int hd, float rope_base, int32_t* pos, int32_t* tok, float2* rope,
-                int32_t* status, void* clear, size_t clear_bytes, hipStream_t s) {
+                int32_t* status, void* clear, size_t clear_bytes, const AttnParts& ap, hipStream_t s) {
     const int threads = q_len > 16 ? 1024 : 128;
     const size_t clear16 = clear_bytes / 16;
     // one clearing block per 32 KiB, at most 512 (a few MB of attention cells: two or three sweeps per lane)
     int extra = (int)((clear_bytes + 32767) / 32768);
     if (extra > 512) extra = 512;
     hipLaunchKernelGGL(prep_kernel, dim3(B * ((q_len + PREP_ROWS - 1) / PREP_ROWS) + extra), dim3(threads), 0, s, q_tokens, q_stride, kv_len, kv_base, q_len, max_len, V,
-                       hd / 2, rope_base, pos, tok, rope, status, B, reinterpret_cast<uint4*>(clear), clear16);
+                       hd / 2, rope_base, pos, tok, rope, status, B, reinterpret_cast<uint4*>(clear), clear16, ap);
     BS_LAUNCH_CHECK();
     return BS_OK;
 }
@@ -2020,8 +2152,8 @@ static size_t attn_resident_workgroups(int hd) {
         int per_cu = 0;
         const int cus = step_grid();
         if (cus <= 0) return (size_t)device_cus() * (wide ? 2 : 4);
-        const hipError_t e = wide ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_mfma_kernel<128, 1, true, true>, 256, 0)
-                                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_mfma_kernel<64, 1, true, true>, 256, 0);
+        const hipError_t e = wide ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_mfma_kernel<128, 1, true, true, false>, 256, 0)
+                                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_mfma_kernel<64, 1, true, true, false>, 256, 0);
         return (e == hipSuccess && per_cu > 0) ? (size_t)per_cu * cus : 1;   // 1: never enough, the merge kernel runs
     };
     static const size_t c128 = ask(true), c64 = ask(false);      // asked once (initialisation of a local static is thread-safe)
@@ -2030,15 +2162,15 @@ static size_t attn_resident_workgroups(int hd) {
 
 // How a pass whose attention leaves the output itself (not the few-row schedule) cuts the keys when it may use up to n_splits parts.
 AttnPlan attn_plan(int dtype, int B, int q_len, int H, int KVH, int hd, int cache_len, int n_splits) {
-    AttnPlan p = {n_splits, false};
+    AttnPlan p = {n_splits, n_splits, 0, false};
     if (dtype != BS_BF16 || n_splits <= 1) return p;
-    if (attn_prompt_applies(B, q_len, H, KVH, hd)) { p.splits = 1; return p; }
+    if (attn_prompt_applies(B, q_len, H, KVH, hd)) { p.splits = p.most = 1; return p; }
     const int n_tiles = (H / KVH * q_len + 15) / 16, n_rt = n_tiles >= 2 ? (n_tiles + 1) / 2 : 1, cus = device_cus();
     if (n_tiles >= 2) {
         // Two row tiles a wavefront: one workgroup per group of two and only as many key splits as it takes to reach about a
         // thousand workgroups; a single group keeps all the splits.
         const int want = (int)((4 * cus + (long long)B * KVH * n_rt - 1) / ((long long)B * KVH * n_rt));
-        if (n_rt > 1 && want < n_splits) p.splits = want;
+        if (n_rt > 1 && want < n_splits) p.splits = p.most = want;
         return p;
     }
     // One row tile: fewer splits than asked for where that is no slower.
@@ -2048,6 +2180,7 @@ AttnPlan attn_plan(int dtype, int B, int q_len, int H, int KVH, int hd, int cach
     // a batch, which may share the device with another stream's, does not come to wait for its own workgroups by being cut less.
     p.in_kernel = rows > DEC_MAX_ROWS && rows <= ATTN_CELL_ROWS && units * n_splits <= (long long)attn_resident_workgroups(hd) &&
                   attn_cells_bytes(rows, H, hd, n_splits) > 0;
+    const double unit_mb = 4e-6 * hd * cache_len, merge_us = 4.6 + 8e-4 * rows * H;
     if (hd != 128) {
         // head_dim 64, 4 workgroups per compute unit resident: the fewest splits with the least rounds of 1024 workgroups per split (16
         // sequences of 4097 keys, 12 heads: 6 splits, 1152 workgroups, 36.5 us; 5 splits 35.2; two or fewer workgroups per compute
@@ -2067,23 +2200,31 @@ AttnPlan attn_plan(int dtype, int B, int q_len, int H, int KVH, int hd, int cach
         // 9 rows, 1 / 2 / 3 splits 858 / 850 / 813, 16 rows 931 / 962 / 911; of 8192: 9 rows, 4 / 6 / 8 / 16 splits 995 / 928 / 894 / 924; 3 sequences
         // of 5 rows, cache of 1280: 927 / 894 / 921.  With a merge kernel: 2 sequences of 9 rows, cache of 600, 1 / 2 splits 926 / 932, of 900 955 / 943;
         // 3 of 6 rows, of 2304, 2 / 5 splits 1024 / 1011; 6 of 5 rows, of 2304, 1 / 4 splits 1227 / 1240.  More splits than that only for a tenth of the estimate.
-        const double unit_mb = 4e-6 * hd * cache_len, f = units * unit_mb / 6.4;
+        const double f = units * unit_mb / 6.4;
         const int group_rows = H / KVH * q_len;
         double best_us = 1e30;
         for (int s = 1; s <= n_splits; ++s) {
             const double c = (double)((units * s + cus - 1) / cus) / s * unit_mb / 0.030;
-            const double combine_us = s == 1 ? 0.0 : p.in_kernel ? 0.5 + 1.55 * ((group_rows + s - 1) / s) : 4.6 + 8e-4 * rows * H + (units * s > cus ? 2.0 : 0.0);
+            const double combine_us = s == 1 ? 0.0 : p.in_kernel ? 0.5 + 1.55 * ((group_rows + s - 1) / s) : merge_us + (units * s > cus ? 2.0 : 0.0);
             const double us = sqrt(sqrt(c * c * c * c + f * f * f * f)) + combine_us;
             if (us < (p.in_kernel ? 0.9 : 0.999) * best_us) { p.splits = s; best_us = us; }
         }
     }
     p.in_kernel = p.in_kernel && p.splits > 1;
+    // That is for sequences of about one length.  One that is much longer than the others would end alone, so it is cut into more
+    // parts, up to what was asked for (prep_kernel, by the lengths on the device), where that is a quarter more parts and, if
+    // the others are not cut and its last workgroup has to combine them, saves it twice what that costs.
+    const double saved_us = unit_mb / 0.030 * (1.0 / p.splits - 1.0 / n_splits);
+    const bool worth = p.splits > 1 || (saved_us > 2.0 * (0.5 + 1.55 * (H / KVH) * q_len) && attn_cells_bytes(rows, H, hd, n_splits) > 0);
+    p.most = rows > DEC_MAX_ROWS && B < 65536 && !p.in_kernel && 5 * p.splits < 4 * n_splits && worth ? n_splits : p.splits;
+    const long long spare = units * (p.most - p.splits), room = cus;           // a long sequence's parts are at most its share of the compute units
+    p.n_items = B * p.splits + (int)((spare < room ? spare : room) / KVH);
     return p;
 }
 
 int launch_attention(int dtype, const float* q, const void* k_cache, const void* v_cache, const int32_t* pos, int B,
                      int q_len, int H, int KVH, int hd, int max_len, int n_splits, float* part, size_t plane, void* out,
-                     int out_tiled, const AttnCells* cells, bool stream, hipStream_t s) {
+                     int out_tiled, const AttnCells* cells, const AttnParts* ap, bool stream, hipStream_t s) {
     BS_REQUIRE(!out_tiled || (dtype == BS_BF16 && out && B * q_len <= out_tiled), BS_ESHAPE, "attention: tiled output planes hold at most %d rows", out_tiled);
     const float scale = 1.0f / sqrtf((float)hd);
     const dim3 block(256);
@@ -2097,14 +2238,19 @@ int launch_attention(int dtype, const float* q, const void* k_cache, const void*
         const int nt = (n_tiles >= 2) ? 2 : 1;
         const int n_rt = (n_tiles + nt - 1) / nt;
         const AttnPlan plan = attn_plan(dtype, B, q_len, H, KVH, hd, max_len, n_splits);
-        if (out) n_splits = plan.splits;
-        const dim3 mgrid(n_splits * (out ? n_rt : 1), KVH, B);
-        uint16_t* direct = (out && n_splits == 1) ? reinterpret_cast<uint16_t*>(out) : nullptr;     // no merge needed
+        const int few = out ? plan.splits : n_splits;              // of a sequence about as long as the others
+        if (out) n_splits = plan.most;
+        if (few == n_splits) ap = nullptr;
+        BS_REQUIRE(few == n_splits || (ap && ap->parts && ap->items && (hd == 64 || hd == 128) && nt == 1 && ap->few == few && ap->most == n_splits), BS_EINVAL, "attention: the work items are missing");
+        const dim3 mgrid = ap ? dim3(KVH, ap->n_items) : dim3(n_splits * (out ? n_rt : 1), KVH, B);
+        uint16_t* direct = (out && few == 1) ? reinterpret_cast<uint16_t*>(out) : nullptr;          // of one part: the output itself
         // the splits combined inside the kernel: one row tile, exchange cells at hand, every workgroup resident at once
         AttnMerge mg = {};
         mg.tiled = out_tiled;
-        if (cells && cells->buf && out && plan.in_kernel) {
-            BS_REQUIRE(attn_cells_bytes(B * q_len, H, hd, n_splits) <= cells->bytes, BS_EWORKSPACE, "attention: %zu bytes of exchange cells", cells->bytes);
+        if (cells && cells->buf && out && (plan.in_kernel || (ap && few == 1))) {
+            const size_t need = attn_cells_bytes(B * q_len, H, hd, n_splits);
+            BS_REQUIRE(need + (ap ? (size_t)B * KVH * 4 : 0) <= cells->bytes, BS_EWORKSPACE, "attention: %zu bytes of exchange cells", cells->bytes);
+            if (ap) mg.tickets = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(cells->buf) + need);
             mg.cells = cells->buf; mg.out = reinterpret_cast<uint16_t*>(out); mg.plane = plane;
             mg.flag = cells->flag; mg.spin_limit = cells->spin_limit; mg.status = cells->status;
         }
@@ -2112,13 +2258,14 @@ int launch_attention(int dtype, const float* q, const void* k_cache, const void*
         { const int prc = prof_events(s, &e0, &e1); if (prc != BS_OK) return prc; }
         // with several groups of row tiles every group reads the keys again: those loads stay cached
         stream = stream && n_rt == 1;
-#define BS_ATTN_ST(HD, NT, ST, AH) BS_LAUNCH_TIMED((attn_mfma_kernel<HD, NT, ST, AH>), mgrid, block, 0, s, e0, e1, q, (const uint16_t*)k_cache, \
-                                        (const uint16_t*)v_cache, pos, q_len, H, KVH, max_len, scale, part, n_splits, direct, plane, mg)
-#define BS_ATTN(HD, NT, AH) do { if (stream) BS_ATTN_ST(HD, NT, true, AH); else BS_ATTN_ST(HD, NT, false, AH); } while (0)
-#define BS_ATTN_1(HD) do { if (ahead) BS_ATTN(HD, 1, true); else BS_ATTN(HD, 1, false); } while (0)
-        const bool ahead = max_len / n_splits >= 768;              // six blocks and more per wavefront of a full cache
-        if (hd == 128) { if (nt == 2) BS_ATTN(128, 2, false); else BS_ATTN_1(128); }
-        else if (hd == 64) { if (nt == 2) BS_ATTN(64, 2, false); else BS_ATTN_1(64); }
+#define BS_ATTN_ST(HD, NT, ST, AH, PT) BS_LAUNCH_TIMED((attn_mfma_kernel<HD, NT, ST, AH, PT>), mgrid, block, 0, s, e0, e1, q, (const uint16_t*)k_cache, \
+                                        (const uint16_t*)v_cache, pos, q_len, H, KVH, max_len, scale, part, n_splits, direct, plane, mg, ap ? ap->items : nullptr)
+#define BS_ATTN(HD, NT, AH, PT) do { if (stream) BS_ATTN_ST(HD, NT, true, AH, PT); else BS_ATTN_ST(HD, NT, false, AH, PT); } while (0)
+#define BS_ATTN_1(HD, PT) do { if (ahead) BS_ATTN(HD, 1, true, PT); else BS_ATTN(HD, 1, false, PT); } while (0)
+        const bool ahead = max_len / few >= 768;              // six blocks and more per wavefront of a full cache
+        if (ap) { if (hd == 128) BS_ATTN_1(128, true); else BS_ATTN_1(64, true); }
+        else if (hd == 128) { if (nt == 2) BS_ATTN(128, 2, false, false); else BS_ATTN_1(128, false); }
+        else if (hd == 64) { if (nt == 2) BS_ATTN(64, 2, false, false); else BS_ATTN_1(64, false); }
         else
             BS_FAIL(BS_ESHAPE, "attention: bf16 caches need head_dim 64 or 128, got %d", hd);
 #undef BS_ATTN_1
@@ -2126,13 +2273,18 @@ int launch_attention(int dtype, const float* q, const void* k_cache, const void*
 #undef BS_ATTN
         BS_LAUNCH_CHECK();
         prof_record(e0, e1, 0.0, 100);                     // class 100: the split attention kernel (bytes known to the caller)
-        if (out && !direct && !mg.cells) hipLaunchKernelGGL((attn_merge_kernel<uint16_t>), dim3(B * q_len * H), dim3(hd), 0, s, part, n_splits, hd, plane, out, out_tiled ? H : 0, out_tiled);
+        if (out && n_splits > 1 && !mg.cells) {
+            if (ap)
+                hipLaunchKernelGGL((attn_merge_kernel<uint16_t, true>), dim3(B * q_len * H), dim3(hd), 0, s, part, n_splits, hd, plane, out, out_tiled ? H : 0, out_tiled, ap->parts, q_len * H);
+            else
+                hipLaunchKernelGGL((attn_merge_kernel<uint16_t, false>), dim3(B * q_len * H), dim3(hd), 0, s, part, n_splits, hd, plane, out, out_tiled ? H : 0, out_tiled, (const int32_t*)nullptr, 1);
+        }
     } else {
         float* direct = n_splits == 1 ? reinterpret_cast<float*>(out) : nullptr;
         hipLaunchKernelGGL((attn_kernel<float>), dim3(n_splits * ((q_len + ATT_RB - 1) / ATT_RB), H, B), block, 0, s, q, (const float*)k_cache,
                            (const float*)v_cache, pos, q_len, H, KVH, hd, max_len, scale, n_splits, part, direct);
         BS_LAUNCH_CHECK();
-        if (n_splits > 1) hipLaunchKernelGGL((attn_merge_kernel<float>), dim3(B * q_len * H), dim3(hd), 0, s, part, n_splits, hd, plane, out, out_tiled ? H : 0, out_tiled);
+        if (n_splits > 1) hipLaunchKernelGGL((attn_merge_kernel<float, false>), dim3(B * q_len * H), dim3(hd), 0, s, part, n_splits, hd, plane, out, out_tiled ? H : 0, out_tiled, (const int32_t*)nullptr, 1);
     }
     BS_LAUNCH_CHECK();
     return BS_OK;

@@ -153,7 +153,8 @@ static int attn_splits(int B, int H, int max_len) {
 struct FwdWs {
     int32_t* status; int32_t* pos; int32_t* tok; float2* rope; float* x; void* h; float* q; void* att; void* act; float* ssq;
     char* xch; size_t xch_bytes;    // resident step kernel: exchange cells (one or two rows only)
-    char* acells; size_t acells_bytes;   // attention: exchange cells of the key splits (up to 16 rows of a bf16 model)
+    char* acells; size_t acells_bytes;   // attention: exchange cells of key splits combined in the kernel, and tickets
+    AttnPlan att_plan; AttnParts att_parts;    // more than two rows; parts == nullptr: the same splits for every sequence
     float *part_qkv, *part_o, *part_gu, *part_d, *part_attn;
     int ks_qkv, ks_o, ks_gu, ks_d;
     bool big_qkv, big_gu, big_o, big_d;   // many-row projections whose epilogue does the consumer's work
@@ -198,11 +199,19 @@ static FwdWs carve(const bs_model_cfg& c, int B, int q_len, int max_len, char* b
     w.xch = take(w.xch_bytes);
     // Up to 16 rows, a single sequence being verified as a rule: workgroups that wait for each other need the compute units to
     // themselves, and batches may be run on several streams side by side.  At 17..32 rows a merge kernel follows instead (20 rows at 2048
-    // keys: two layers of the 7B shape 335 -> 334 us, four layers of its draft 218 -> 226).
+    // keys: two layers of the 7B shape 335 -> 334 us, four layers of its draft 218 -> 226).  Cells, with tickets, also where only sequences much
+    // longer than the others are cut: there the last workgroup to hand over combines, and nobody waits.
     const int splits = attn_splits(B, c.n_heads, max_len);
-    const AttnPlan att = attn_plan(c.dtype, B, q_len, c.n_heads, c.n_kv_heads, c.head_dim, cache_rows(max_len), splits);
-    w.acells_bytes = att.in_kernel ? attn_cells_bytes((int)M, c.n_heads, c.head_dim, att.splits) : 0;
+    w.att_plan = attn_plan(c.dtype, B, q_len, c.n_heads, c.n_kv_heads, c.head_dim, cache_rows(max_len), splits);
+    const bool by_length = w.att_plan.most > w.att_plan.splits;
+    w.acells_bytes = w.att_plan.in_kernel || (by_length && w.att_plan.splits == 1) ? attn_cells_bytes((int)M, c.n_heads, c.head_dim, w.att_plan.most) : 0;
+    if (w.acells_bytes && by_length) w.acells_bytes += align_up((size_t)B * c.n_kv_heads * 4, 16);     // and the tickets
     w.acells = take(w.acells_bytes);
+    w.att_parts = AttnParts{nullptr, nullptr, w.att_plan.splits, w.att_plan.most, w.att_plan.n_items, c.n_kv_heads, device_cus()};
+    if (by_length) {
+        w.att_parts.parts = (int32_t*)take((size_t)B * 4);
+        w.att_parts.items = (long long*)take((size_t)w.att_plan.n_items * 8);
+    }
     // partial sums: those of launch_gemm, or of the items that a many-row projection with its consumer's work splits (big_plan)
     auto big = [&](int epi, size_t N, size_t K, int ks, bool* use, int* tiles) -> size_t {
         const BigPlan p = c.dtype == BS_BF16 && big_fused_applies(epi, (int)N, (int)K, (int)M) ? big_plan(epi, (int)N, (int)K, (int)M) : BigPlan{};
@@ -219,7 +228,7 @@ static FwdWs carve(const bs_model_cfg& c, int B, int q_len, int max_len, char* b
     w.part_gu = (float*)take(w.part_gu_bytes);
     w.part_d = (float*)take(w.part_d_bytes);
     // one or two rows: all the splits, the O projection merges
-    w.part_attn = (float*)take(M * c.n_heads * (M <= DEC_MAX_ROWS ? splits : att.splits) * (size_t)(c.head_dim + 4) * 4);
+    w.part_attn = (float*)take(M * c.n_heads * (M <= DEC_MAX_ROWS ? splits : w.att_plan.most) * (size_t)(c.head_dim + 4) * 4);
     w.total = off;
     return w;
 }
@@ -239,13 +248,13 @@ extern "C" __attribute__((visibility("default"))) size_t bs_forward_workspace_by
     return carve_max(*c, B, max_q_len, max_len);
 }
 
-extern "C" __attribute__((visibility("default"))) int bs_attention_splits(const bs_model_cfg* c, int B, int q_len, int max_len, int* splits, int* in_kernel) {
-    BS_REQUIRE(c && splits && in_kernel, BS_EINVAL, "bs_attention_splits: NULL argument");
+extern "C" __attribute__((visibility("default"))) int bs_attention_splits(const bs_model_cfg* c, int B, int q_len, int max_len, int* splits, int* most, int* in_kernel) {
+    BS_REQUIRE(c && splits && most && in_kernel, BS_EINVAL, "bs_attention_splits: NULL argument");
     const int rc = check_cfg(c, "bs_attention_splits");
     if (rc != BS_OK) return rc;
     BS_REQUIRE(B >= 1 && q_len >= 1 && max_len >= 1 && (long long)B * q_len <= (1 << 20), BS_ESHAPE, "bs_attention_splits: B=%d q_len=%d max_len=%d", B, q_len, max_len);
     const AttnPlan p = attn_plan(c->dtype, B, q_len, c->n_heads, c->n_kv_heads, c->head_dim, cache_rows(max_len), attn_splits(B, c->n_heads, max_len));
-    *splits = p.splits; *in_kernel = p.in_kernel ? 1 : 0;
+    *splits = p.splits; *most = p.most; *in_kernel = p.in_kernel ? 1 : 0;
     return BS_OK;
 }
 
@@ -276,7 +285,7 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
     const int st_splits = M <= 2 ? step_splits(c, B, kv->max_len) : 0;
     const bool resident = few_rows && st_splits > 0 && step_fits(c, B, q_len, c.n_layers);
     BS_TRY(launch_prep(q_tokens, q_stride, kv_len, kv_base, B, q_len, kv->max_len, c.vocab, hd, c.rope_base, w.pos, w.tok,
-                       w.rope, w.status, resident ? w.xch : w.acells_bytes ? w.acells : nullptr, resident ? w.xch_bytes : w.acells_bytes, s));
+                       w.rope, w.status, resident ? w.xch : w.acells_bytes ? w.acells : nullptr, resident ? w.xch_bytes : w.acells_bytes, w.att_parts, s));
     if (resident) {
         StepArgs a = {};
         for (int l = 0; l < c.n_layers; ++l) {
@@ -316,7 +325,7 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
             a.q_out = w.q; a.k_cache = reinterpret_cast<uint16_t*>(kc); a.v_cache = reinterpret_cast<uint16_t*>(vc);
             BS_TRY(launch_gemm_dec(EPI_QKV, a, s));
             BS_TRY(launch_attention(dt, w.q, kc, vc, w.pos, B, q_len, H, KVH, hd, crow, splits, w.part_attn,
-                                    (size_t)M * nq, nullptr, 0, nullptr, stream, s));   // splits are merged by the O projection
+                                    (size_t)M * nq, nullptr, 0, nullptr, nullptr, stream, s));   // splits are merged by the O projection
             a = DecArgs{};
             a.att_part = w.part_attn; a.att_splits = splits; a.H = H; a.hd = hd;
             a.xh = reinterpret_cast<const uint16_t*>(w.att); a.x_plane = (size_t)M * nq; a.w[0] = L.wo; a.M = M; a.N = d; a.K = nq;
@@ -398,7 +407,7 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
                               w.q, kc, vc, ssq, ssq_n, d, c.norm_eps, s));
         }
         BS_TRY(launch_attention(dt, w.q, kc, vc, w.pos, B, q_len, H, KVH, hd, crow, splits, w.part_attn,
-                                fuse_o ? (size_t)RT * nq : (size_t)M * nq, w.att, fuse_o ? RT : 0, in_kernel_merge ? &ac : nullptr, stream, s));
+                                fuse_o ? (size_t)RT * nq : (size_t)M * nq, w.att, fuse_o ? RT : 0, in_kernel_merge ? &ac : nullptr, &w.att_parts, stream, s));
         g.x = w.att; g.x_plane = (size_t)M * nq; g.w[0] = L.wo; g.w[1] = g.w[2] = nullptr; g.seg_rows[0] = d; g.seg_rows[1] = 0;
         g.out = w.part_o; g.ks_stride = (size_t)M * d; g.M = M; g.N = d; g.K = nq; g.ldo = d; g.KS = w.ks_o;
         if (fuse_o) {

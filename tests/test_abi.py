@@ -105,18 +105,39 @@ def test_key_splits_follow_what_combining_them_costs():
     """The 7B shape and a grouped-query one.  In the kernel every workgroup combines its share of a group's rows one after the other: a
     cache of 900 rows is worth two parts with 3 and 5 rows, not with 9 or 16; a merge kernel behind 20 rows costs less than one behind 144."""
     c, g = synth.LLAMA7B_TARGET, synth.LLAMA3_8B_TARGET
-    for B, q_len, max_len, want in [(1, 3, 900, (2, True)), (1, 5, 900, (2, True)), (1, 9, 900, (1, False)), (1, 9, 1280, (3, True)), (1, 16, 1024, (1, False)),
-                                    (2, 5, 960, (2, True)), (3, 5, 900, (2, True)), (3, 5, 1280, (2, True)), (4, 4, 1248, (2, True)), (1, 9, 8192, (8, True)),
-                                    (1, 9, 8448, (8, False)), (4, 5, 900, (2, False)), (2, 9, 600, (1, False)), (6, 5, 2304, (1, False)), (4, 5, 2304, (2, False))]:
+    for B, q_len, max_len, want in [(1, 3, 900, (2, 2, True)), (1, 5, 900, (2, 2, True)), (1, 9, 900, (1, 1, False)), (1, 9, 1280, (3, 3, True)),
+                                    (1, 16, 1024, (1, 1, False)), (2, 5, 960, (2, 2, True)), (3, 5, 900, (2, 2, True)), (3, 5, 1280, (2, 2, True)),
+                                    (4, 4, 1248, (2, 2, True)), (1, 9, 8192, (8, 8, True)), (4, 5, 900, (2, 2, False)), (2, 9, 600, (1, 1, False))]:
         assert bs.attention_splits(c, B, q_len, max_len) == want, (B, q_len, max_len)
-    assert bs.attention_splits(g, 1, 4, 1024) == (1, False) and bs.attention_splits(g, 1, 4, 1929) == (4, True)
-    assert bs.attention_splits(synth.LLAMA7B_DRAFT, 16, 1, 4352) == (5, False)
+    for B, q_len, max_len, few in [(6, 5, 2304, 1), (4, 5, 2304, 2), (16, 9, 4352, 1), (1, 9, 8448, 8)]:
+        assert bs.attention_splits(c, B, q_len, max_len)[0] == few, (B, q_len, max_len)
+    assert bs.attention_splits(g, 1, 4, 1024) == (1, 1, False) and bs.attention_splits(g, 1, 4, 1929) == (4, 4, True)
+    assert bs.attention_splits(synth.LLAMA7B_DRAFT, 16, 1, 4352) == (5, 5, False)
     for B in range(1, 17):                           # workgroups that wait for each other: 3 to 16 rows, all of them resident
         for q_len in range(1, 17):
-            n, own = bs.attention_splits(c, B, q_len, 4352)
-            assert n >= 1 and (not own or 3 <= B * q_len <= 16 and 1 < n and 32 * B * n <= 512)
+            n, most, own = bs.attention_splits(c, B, q_len, 4352)
+            assert 1 <= n <= most and (not own or 3 <= B * q_len <= 16 and 1 < n == most and 32 * B * n <= 512)
     with pytest.raises(bs.BanditSpecError):
         bs.attention_splits(c, 0, 1, 100)
+
+
+@pytest.mark.parametrize("dtype,heads,kv_heads,hd", [("bf16", 32, 32, 128), ("bf16", 32, 8, 128), ("bf16", 12, 12, 64), ("f32", 32, 32, 128)])
+def test_a_sequence_much_longer_than_the_others_keeps_its_splits(dtype, heads, kv_heads, hd):
+    """A count below what the cache and the batch ask for (512 keys a part, about 1024 workgroups) is for sequences of one length: one that
+    is much longer is cut into as many parts as asked for, or the lower count is within a quarter of it, or there is little to save."""
+    c = synth.cfg(1, 256, heads, hd, 256, 512, n_kv_heads=kv_heads, dtype=dtype)
+    for B in (2, 3, 5, 8, 12, 16, 20, 31, 64, 100):
+        for q_len in (1, 2, 3, 5, 9, 16):
+            if B * q_len <= 2 or heads // kv_heads * q_len > 16:
+                continue
+            for max_len in (500, 1024, 2304, 4352, 8192, 20000):
+                asked = max(1, min(-(-max_len // 512), -(-1024 // (B * heads)), 64))
+                few, most, own = bs.attention_splits(c, B, q_len, max_len)
+                assert few <= most <= asked
+                one_part_us = 4 * hd * max_len / 30e3
+                assert own or most == asked or 5 * few >= 4 * asked or one_part_us * (1 - few / asked) < 2 * (1 + 1.6 * (heads // kv_heads * q_len)), (B, q_len, max_len, few, most)
+    assert bs.attention_splits(synth.LLAMA7B_TARGET, 8, 9, 8192) == (1, 4, False)
+    assert bs.attention_splits(synth.LLAMA7B_TARGET, 16, 9, 4352) == (1, 2, False)
 
 
 def test_host_side_argument_checks_launch_nothing():

@@ -368,6 +368,41 @@ def test_key_splits_of_batches(heads, hd, B, n_prefix, q_len, max_len):
         assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
 
 
+# A batch with sequences much longer than the others: these are cut into more parts, up to `most`, the others into `few`.
+@pytest.mark.parametrize("c,B,q_len,max_len,few,most,long_len", [
+    (synth.cfg(2, 256, 16, 128, 256, 512), 16, 5, 2304, 1, 4, 1500),                       # parts combined by the last workgroup
+    (synth.cfg(1, 256, 32, 128, 256, 512, n_kv_heads=8), 24, 2, 4200, 1, 2, 1100),         # the same with grouped queries
+    (synth.cfg(2, 256, 16, 128, 256, 512, n_kv_heads=8), 16, 3, 2304, 2, 4, 1500),         # merge kernel
+    (synth.cfg(1, 3328, 26, 128, 6912, 512), 8, 3, 2304, 1, 5, 600),                       # tiled planes for the O projection
+    (synth.cfg(1, 3328, 26, 128, 6912, 512), 4, 7, 2304, 2, 5, 600),
+    (synth.cfg(2, 256, 16, 64, 256, 512), 40, 1, 2304, 1, 2, 900), (synth.cfg(1, 256, 12, 64, 256, 512), 32, 2, 2304, 2, 3, 900)])
+def test_sequences_much_longer_than_the_others(c, B, q_len, max_len, few, most, long_len):
+    """One long sequence; another one, with a sequence left out beside it; two long ones; all of one length: four passes in one workspace."""
+    assert bs().attention_splits(c, B, q_len, max_len) == (few, most, False)
+    W, m, kv = setup(c, B, max_len, seed=75, packed=True)
+    toks = synth.make_prompts(B, long_len + q_len, c["vocab"], seed=76)
+    dt = torch.from_numpy(toks.astype(np.int32)).cuda()
+    bs().prefill(m, kv, dt, long_len, want_logits=False)
+    short = [20 + 7 * b % 50 for b in range(B)]
+    n = m.forward_workspace_bytes(B, q_len, max_len)
+    ws = torch.zeros(n + 256, dtype=torch.uint8, device="cuda")
+    ws[n:] = 77
+    for longs, out in (([0], None), ([B - 1], 1), ([0, B // 2], None), (list(range(B)), None)):
+        lens = [long_len if b in longs else short[b] for b in range(B)]
+        bs().prefill(m, kv, dt, long_len, want_logits=False)
+        kvl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+        if out is not None:
+            kvl[out] = max_len - q_len + 1
+        ws[:4] = 0
+        q = torch.stack([dt[b, k:k + q_len] for b, k in enumerate(lens)]).contiguous()
+        logits = bs().verify_forward(m, kv, q, kvl, workspace=ws[:n])
+        assert int(ws[:4].view(torch.int32).cpu()[0]) == (0 if out is None else 1)
+        assert bool((ws[n:] == 77).all())
+        for b in {longs[0], longs[-1], 2, B - 2}:
+            ref = forward(c, W, toks[b][:lens[b] + q_len], storage="bf16", last_rows=q_len)
+            assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], (longs, b)
+
+
 # one of the many-row projections in whole rounds of 256 items, finished in the GEMM, and the rest of the last round split along
 # K: gate/up is 272 items of 128 columns per block of 256 rows
 FFN_WIDE = synth.cfg(1, 1024, 2, 64, 34784, 512, dtype="bf16")
