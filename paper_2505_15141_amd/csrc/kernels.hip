@@ -2102,12 +2102,11 @@ int launch_resid_sum(float* x, const float* pend, int pend_ks, size_t pend_strid
                      size_t plane, void* out, float* ssq, int tiled, hipStream_t s) {
     if (rows <= 0) return BS_OK;
     BS_REQUIRE(!tiled || (rows <= tiled && d % 32 == 0), BS_ESHAPE, "resid_sum: tiled planes hold at most %d rows (%d) of a multiple of 32 columns (%d)", tiled, rows, d);
-    // as many splits in flight as there are, up to 16
+    // up to 8 splits in flight
 #define BS_RESID(AHEAD) hipLaunchKernelGGL(resid_sum_kernel<AHEAD>, dim3(rows, norm_chunks(d)), dim3(256), 0, s, x, pend, pend_ks, pend_stride, gain, d, plane, \
                                            (uint16_t*)out, ssq, tiled)
     if (!pend || pend_ks <= 4) BS_RESID(4);
-    else if (pend_ks <= 8) BS_RESID(8);
-    else BS_RESID(16);
+    else BS_RESID(8);
 #undef BS_RESID
     BS_LAUNCH_CHECK();
     return BS_OK;
