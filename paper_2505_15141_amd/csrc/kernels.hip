@@ -1798,6 +1798,7 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
         if (!in_cells) return;
         if constexpr (PARTS) {                       // the sequence's last workgroup combines all rows
             __shared__ int last;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // this wavefront's cells are stored
             __syncthreads();
             if (threadIdx.x == 0) last = atomicAdd(mg.tickets + b * KVH + kvh, 1u) + 1u == mg.flag * used;
             __syncthreads();
@@ -1821,7 +1822,7 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
                     u32x2 co[IT][PU];
                     u32x4 cml[IT][PU];
                     unsigned spins = 0;
-                    while (true) {                          // handed over, so there at once
+                    while (true) {                          // handed over before the ticket, so there at once whatever the limit of the waits is
                         asm volatile("" ::: "memory");
                         bool ok = true;
 #pragma unroll
@@ -1837,7 +1838,7 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
 #pragma unroll
                             for (int u = 0; u < PU; ++u) ok = ok && co[it][u].y == mg.flag && cml[it][u].y == mg.flag && cml[it][u].w == mg.flag;
                         if (ok) break;
-                        if (++spins > mg.spin_limit) { atomicOr(mg.status, 16); break; }
+                        if (++spins > (1u << 18)) { atomicOr(mg.status, 16); break; }
                     }
 #pragma unroll
                     for (int it = 0; it < IT; ++it) {

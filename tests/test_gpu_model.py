@@ -377,7 +377,8 @@ def test_key_splits_of_batches(heads, hd, B, n_prefix, q_len, max_len):
     (synth.cfg(1, 3328, 26, 128, 6912, 512), 4, 7, 2304, 2, 5, 600),
     (synth.cfg(2, 256, 16, 64, 256, 512), 40, 1, 2304, 1, 2, 900), (synth.cfg(1, 256, 12, 64, 256, 512), 32, 2, 2304, 2, 3, 900)])
 def test_sequences_much_longer_than_the_others(c, B, q_len, max_len, few, most, long_len):
-    """One long sequence; another one, with a sequence left out beside it; two long ones; all of one length: four passes in one workspace."""
+    """One long sequence; another one, with a sequence left out beside it; two long ones; all of one length: four passes in one workspace.
+    With the poll limit at 1: these passes wait for nobody."""
     assert bs().attention_splits(c, B, q_len, max_len) == (few, most, False)
     W, m, kv = setup(c, B, max_len, seed=75, packed=True)
     toks = synth.make_prompts(B, long_len + q_len, c["vocab"], seed=76)
@@ -395,7 +396,11 @@ def test_sequences_much_longer_than_the_others(c, B, q_len, max_len, few, most, 
             kvl[out] = max_len - q_len + 1
         ws[:4] = 0
         q = torch.stack([dt[b, k:k + q_len] for b, k in enumerate(lens)]).contiguous()
-        logits = bs().verify_forward(m, kv, q, kvl, workspace=ws[:n])
+        bs().step_poll_limit(1)
+        try:
+            logits = bs().verify_forward(m, kv, q, kvl, workspace=ws[:n])
+        finally:
+            bs().step_poll_limit(0)
         assert int(ws[:4].view(torch.int32).cpu()[0]) == (0 if out is None else 1)
         assert bool((ws[n:] == 77).all())
         for b in {longs[0], longs[-1], 2, B - 2}:
