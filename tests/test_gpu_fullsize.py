@@ -214,7 +214,7 @@ def test_lockstep_rounds_at_batch_16_with_4096_cached_tokens_exp3spec_and_noise(
     """The batched non-stationary workload at its real batch x cache length: 16 sequences with 4096 cached tokens each,
     EXP3Spec over gamma in {2,3,4,5,6,8}, draft-logit noise 0.2 <-> 1.5 switching every 64 generated tokens (the
     sequences are told they have already generated 58..73 tokens, so the switch falls inside these rounds), 144-row
-    projections at the 7B layer widths, key splits over a 4.1k-token cache, replayed from a graph as bench.py does.  One
+    projections at the 7B layer widths, one key split of the target and five of the draft over a 4.1k-token cache, replayed from a graph as bench.py does.  One
     layer of the target and of the draft, so that the fp64 oracle needs seconds per round; three sequences per round
     are recomputed by the oracle, the others follow the device."""
     from oracle.bandit import EXP3Spec

@@ -349,12 +349,14 @@ def test_one_and_two_rows_on_a_narrow_model_with_a_long_cache(B, n_prefix, q_len
 
 
 # 512, 576 and 128 (sequence, head) pairs of 128: one split of the keys and several with a merge kernel; 192 pairs of 64: five splits
-@pytest.mark.parametrize("heads,hd,B,n_prefix,q_len,max_len", [
-    (32, 128, 16, 1000, 9, 1024), (32, 128, 16, 863, 1, 900), (36, 128, 16, 831, 2, 1700), (16, 128, 8, 1203, 5, 2400), (12, 64, 16, 2047, 1, 4200), (12, 64, 16, 1300, 3, 4200)])
-def test_key_splits_of_batches(heads, hd, B, n_prefix, q_len, max_len):
+@pytest.mark.parametrize("heads,hd,B,n_prefix,q_len,max_len,splits", [
+    (32, 128, 16, 1000, 9, 1024, 1), (32, 128, 16, 863, 1, 900, 1), (36, 128, 16, 831, 2, 1700, 2), (16, 128, 8, 1203, 5, 2400, 2),
+    (12, 64, 16, 2047, 1, 4200, 5), (12, 64, 16, 1300, 3, 4200, 5)])
+def test_key_splits_of_batches(heads, hd, B, n_prefix, q_len, max_len, splits):
     """Sequences of different lengths, their new keys at different places of the last block; the wavefronts of a split walk
-    from one to nine blocks, requested ahead."""
+    from one to eight blocks, requested ahead."""
     c = synth.cfg(1, 256, heads, hd, 256, 512, dtype="bf16")
+    assert bs().attention_splits(c, B, q_len, max_len)[0] == splits and max_len // splits >= 768
     W, m, kv = setup(c, B, max_len, seed=71, packed=True)
     toks = synth.make_prompts(B, n_prefix + q_len, c["vocab"], seed=72)
     dtoks = torch.from_numpy(toks.astype(np.int32)).cuda()
@@ -366,6 +368,29 @@ def test_key_splits_of_batches(heads, hd, B, n_prefix, q_len, max_len):
     for b in (0, 1, 6, B - 1):
         ref = forward(c, W, toks[b][:lens[b] + q_len], storage="bf16", last_rows=q_len)
         assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
+
+
+# Splits combined in the kernel by wavefronts that request their next block ahead: one query head per kv head and four, both head_dims
+@pytest.mark.parametrize("heads,kv_heads,hd,q_len,max_len,splits,lens", [
+    (32, 32, 128, 9, 8192, 8, [5003]), (32, 8, 128, 4, 8192, 8, [4100, 3001, None, 35]), (16, 16, 64, 2, 8192, 8, [4600, 31, 2000, None, 4599, 1, 700, 1025]),
+    (32, 32, 128, 5, 4096, 4, [None, 3333])])
+def test_splits_combined_in_the_kernel_with_blocks_requested_ahead(heads, kv_heads, hd, q_len, max_len, splits, lens):
+    """Up to seven blocks a wavefront; None: a sequence left out."""
+    c, B, n = synth.cfg(1, 256, heads, hd, 256, 512, n_kv_heads=kv_heads), len(lens), max(k or 0 for k in lens)
+    assert bs().attention_splits(c, B, q_len, max_len) == (splits, splits, True) and max_len // splits >= 768
+    W, m, kv = setup(c, B, max_len, seed=77, packed=True)
+    toks = synth.make_prompts(B, n + q_len, c["vocab"], seed=78)
+    dt = torch.from_numpy(toks.astype(np.int32)).cuda()
+    bs().prefill(m, kv, dt, n, want_logits=False)
+    kvl = torch.tensor([max_len if k is None else k for k in lens], dtype=torch.int32, device="cuda")
+    q = torch.stack([dt[b, (k or 0):(k or 0) + q_len] for b, k in enumerate(lens)]).contiguous()
+    ws = torch.zeros(m.forward_workspace_bytes(B, q_len, max_len), dtype=torch.uint8, device="cuda")
+    logits = bs().verify_forward(m, kv, q, kvl, workspace=ws)
+    assert int(ws[:4].view(torch.int32).cpu()[0]) == (1 if None in lens else 0)
+    for b, k in enumerate(lens):
+        if k is not None:
+            ref = forward(c, W, toks[b][:k + q_len], storage="bf16", last_rows=q_len)
+            assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
 
 
 # A batch with sequences much longer than the others: these are cut into more parts, up to `most`, the others into `few`.
@@ -413,14 +438,16 @@ def test_sequences_much_longer_than_the_others(c, B, q_len, max_len, few, most, 
 FFN_WIDE = synth.cfg(1, 1024, 2, 64, 34784, 512, dtype="bf16")
 
 
-@pytest.mark.parametrize("c,B,n_prefix,q_len", [
+@pytest.mark.parametrize("c,B,n_prefix,q_len,max_len,splits", [
     # 17..32 rows on models with several 16-column units per compute unit: the whole-K projections with two row tiles
-    (ROWS, 2, 30, 9), (ROWS, 1, 40, 17), (ROWS, 4, 8, 8), (ROWS_GQA, 3, 21, 6), (ROWS_MANY, 2, 25, 16), (ROWS_MANY, 7, 5, 3),
-    # the same against one key split and against several (max_len), the O projection on tiled planes in both
-    (WIDE_ROWS, 2, 30, 9), (WIDE_ROWS, 4, 540, 5),
-    (FFN_WIDE, 1, 220, 3), (FFN_WIDE, 1, 390, 40)])
-def test_projections_with_epilogues_on_more_rows(c, B, n_prefix, q_len):
-    W, m, kv = setup(c, B, n_prefix + q_len + 8, seed=61, packed=True)
+    (ROWS, 2, 30, 9, 47, 1), (ROWS, 1, 40, 17, 65, 1), (ROWS, 4, 8, 8, 24, 1), (ROWS_GQA, 3, 21, 6, 35, 1), (ROWS_MANY, 2, 25, 16, 49, 1), (ROWS_MANY, 7, 5, 3, 16, 1),
+    # the same against one key split and against several, the O projection on tiled planes in all; with two splits a merge kernel
+    # writes them and a wavefront walks up to three blocks
+    (WIDE_ROWS, 2, 30, 9, 47, 1), (WIDE_ROWS, 4, 540, 5, 553, 1), (WIDE_ROWS, 4, 540, 5, 1100, 2), (WIDE_ROWS, 2, 540, 9, 2100, 4),
+    (FFN_WIDE, 1, 220, 3, 231, 1), (FFN_WIDE, 1, 390, 40, 438, 1)])
+def test_projections_with_epilogues_on_more_rows(c, B, n_prefix, q_len, max_len, splits):
+    assert bs().attention_splits(c, B, q_len, max_len)[0] == splits
+    W, m, kv = setup(c, B, max_len, seed=61, packed=True)
     toks = synth.make_prompts(B, n_prefix + q_len, c["vocab"], seed=62)
     dtoks = torch.from_numpy(toks.astype(np.int32)).cuda()
     last = bs().prefill(m, kv, dtoks, n_prefix, want_logits=True)
@@ -640,6 +667,7 @@ def test_key_splits_combined_in_the_attention_kernel_with_a_sequence_left_out_an
     b = bs()
     c = MID
     max_len, n_prefix, q_len = 8300, 600, 5
+    assert b.attention_splits(c, 3, q_len, max_len) == (17, 17, True)
     W, m, kv = setup(c, 3, max_len, seed=27, packed=True)
     toks = synth.make_prompts(3, n_prefix + q_len, c["vocab"], 28)
     dt = torch.from_numpy(toks.astype(np.int32)).cuda()
@@ -673,6 +701,7 @@ def test_passes_of_17_to_32_rows_wait_for_nobody(c, B, q_len):
     """Such passes may run beside others on other streams: with the poll limit at 1, where every wait between workgroups runs
     out at once, they give the right logits against several key splits, and report nothing."""
     b, n_prefix, max_len = bs(), 100, 2100
+    assert b.attention_splits(c, B, q_len, max_len) == (5, 5, False)
     W, m, kv = setup(c, B, max_len, seed=27, packed=True)
     toks = synth.make_prompts(B, n_prefix + q_len, c["vocab"], 28)
     dt = torch.from_numpy(toks.astype(np.int32)).cuda()
