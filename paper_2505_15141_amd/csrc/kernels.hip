@@ -41,35 +41,39 @@ constexpr int PREP_ROWS = 32;
 // wavefront per sequence, each with its own look at all lengths.
 __device__ __forceinline__ void attn_deal(const AttnParts& ap, const int32_t* __restrict__ kv_len, int kv_base, int q_len, int max_len, int B, int b, int pos0) {
     const int lane = threadIdx.x;
-    auto keys = [&](int i) -> long long {
-        const int k = (kv_len ? kv_len[i] : 0) + kv_base;
+    auto keys = [&](int i) -> int {                                // all of them together fit a cache in memory: 31 bits
+        const int k = i < B ? (kv_len ? kv_len[i] : 0) + kv_base : -1;
         return k >= 0 && k + q_len <= max_len ? k + q_len : 0;
     };
-    auto total = [](long long v) {
+    auto total = [](int v) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
         return v;
     };
-    long long sum = 0;
-    for (int i = lane; i < B; i += 64) sum += keys(i);
+    const int k0 = keys(lane);                                     // the first 64 sequences are asked for once
+    int sum = k0;
+    for (int i = lane + 64; i < B; i += 64) sum += keys(i);
     sum = total(sum);
-    auto cut = [&](long long own) -> int {                         // a long sequence: as many parts as compute units it would keep busy at an equal share
-        const long long share = sum > 0 ? own * ap.cus / (sum * ap.kv_heads) : 0;
-        return 4 * own * B > 5 * sum && share > ap.few ? (int)min(share, (long long)ap.most) : ap.few;
+    auto cut = [&](int own) -> int {                               // a long sequence: as many parts as compute units it would keep busy at an equal share
+        if (4ll * own * B <= 5ll * sum) return ap.few;
+        const int share = (int)((long long)own * ap.cus / ((long long)sum * ap.kv_heads));
+        return share > ap.few ? min(share, ap.most) : ap.few;
     };
-    long long extra = 0, extra_before = 0, n_long = 0, long_before = 0;
-    for (int i = lane; i < B; i += 64) {
-        const int n = cut(keys(i)) - ap.few;
-        extra += n; n_long += n > 0;
-        if (i < b) { extra_before += n; long_before += n > 0; }
+    int extra = 0, n_long = 0, extra_before = 0, long_before = 0;
+    for (int i0 = 0; i0 < B; i0 += 64) {
+        const int n = cut(i0 == 0 ? k0 : keys(i0 + lane)) - ap.few;
+        const unsigned long long is_long = __ballot(n > 0), before = b >= i0 + 64 ? ~0ull : b > i0 ? (1ull << (b - i0)) - 1 : 0ull;
+        if (!is_long) continue;
+        const int both = total(n | ((before >> lane) & 1 ? n << 16 : 0));       // n and those in front of b: at most as many as compute units
+        extra += both & 0xFFFF; extra_before += both >> 16;
+        n_long += __popcll(is_long); long_before += __popcll(is_long & before);
     }
-    extra = total(extra); extra_before = total(extra_before); n_long = total(n_long); long_before = total(long_before);
     const int own = pos0 >= 0 ? cut(pos0 + q_len) : ap.few;
-    const int first = own > ap.few ? (int)(long_before * ap.few + extra_before) : (int)(extra + (n_long + b - long_before) * ap.few);
+    const int first = own > ap.few ? long_before * ap.few + extra_before : extra + (n_long + b - long_before) * ap.few;
     if (lane < own) ap.items[first + lane] = (long long)(b | lane << 16 | own << 24) << 32 | (unsigned)pos0;
     if (lane == 0) ap.parts[b] = own;
     if (b == 0)
-        for (int i = (int)extra + B * ap.few + lane; i < ap.n_items; i += 64) ap.items[i] = -1;
+        for (int i = extra + B * ap.few + lane; i < ap.n_items; i += 64) ap.items[i] = -1;
 }
 
 __global__ void prep_kernel(const int32_t* __restrict__ q_tokens, int q_stride, const int32_t* __restrict__ kv_len,
@@ -2212,11 +2216,12 @@ AttnPlan attn_plan(int dtype, int B, int q_len, int H, int KVH, int hd, int cach
     }
     p.in_kernel = p.in_kernel && p.splits > 1;
     // That is for sequences of about one length.  One that is much longer than the others would end alone, so it is cut into more
-    // parts, up to what was asked for (prep_kernel, by the lengths on the device), where that is a quarter more parts and, if
-    // the others are not cut and its last workgroup has to combine them, saves it twice what that costs.
+    // parts, up to what was asked for (prep_kernel, by the lengths on the device), where that saves it 6 us or, if the others are not cut
+    // and its last workgroup has to combine them, twice what that costs.  (The way over the items costs batches of one length up to
+    // 1 us a launch: four layers of the 8B's draft, 12 x 2 rows at 3000 keys, 5 splits or up to 7: 304 -> 308 us a pass.)
     const double saved_us = unit_mb / 0.030 * (1.0 / p.splits - 1.0 / n_splits);
-    const bool worth = p.splits > 1 || (saved_us > 2.0 * (0.5 + 1.55 * (H / KVH) * q_len) && attn_cells_bytes(rows, H, hd, n_splits) > 0);
-    p.most = rows > DEC_MAX_ROWS && B < 65536 && !p.in_kernel && 5 * p.splits < 4 * n_splits && worth ? n_splits : p.splits;
+    const bool worth = p.splits > 1 ? saved_us > 6.0 : saved_us > 2.0 * (0.5 + 1.55 * (H / KVH) * q_len) && attn_cells_bytes(rows, H, hd, n_splits) > 0;
+    p.most = rows > DEC_MAX_ROWS && B < 65536 && !p.in_kernel && worth ? n_splits : p.splits;
     const long long spare = units * (p.most - p.splits), room = cus;           // a long sequence's parts are at most its share of the compute units
     p.n_items = B * p.splits + (int)((spare < room ? spare : room) / KVH);
     return p;

@@ -400,7 +400,7 @@ def test_splits_combined_in_the_kernel_with_blocks_requested_ahead(heads, kv_hea
     (synth.cfg(2, 256, 16, 128, 256, 512, n_kv_heads=8), 16, 3, 2304, 2, 4, 1500),         # merge kernel
     (synth.cfg(1, 3328, 26, 128, 6912, 512), 8, 3, 2304, 1, 5, 600),                       # tiled planes for the O projection
     (synth.cfg(1, 3328, 26, 128, 6912, 512), 4, 7, 2304, 2, 5, 600),
-    (synth.cfg(2, 256, 16, 64, 256, 512), 40, 1, 2304, 1, 2, 900), (synth.cfg(1, 256, 12, 64, 256, 512), 32, 2, 2304, 2, 3, 900)])
+    (synth.cfg(2, 256, 16, 64, 256, 512), 40, 1, 2304, 1, 2, 900), (synth.cfg(1, 256, 12, 64, 256, 512), 32, 2, 8300, 2, 3, 900)])
 def test_sequences_much_longer_than_the_others(c, B, q_len, max_len, few, most, long_len):
     """One long sequence; another one, with a sequence left out beside it; two long ones; all of one length: four passes in one workspace.
     With the poll limit at 1: these passes wait for nobody."""
