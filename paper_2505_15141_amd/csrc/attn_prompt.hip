@@ -52,7 +52,7 @@ template <int HD, int NT>
 __global__ __launch_bounds__(256, 2) void attn_prompt_kernel(const float* __restrict__ q, const uint16_t* __restrict__ k_cache,
                                                              const uint16_t* __restrict__ v_cache, const int32_t* __restrict__ pos,
                                                              int B, int q_len, int H, int KVH, int cache_len, float scale,
-                                                             int n_rt, uint16_t* __restrict__ out, size_t plane) {
+                                                             int n_rt, uint16_t* __restrict__ out, size_t plane, int tiled) {
     constexpr int DS = HD / 32, DT = HD / 16, ROWS = 64 * NT, FK = HD / 64;      // FK: kilobytes of K (and of V) a wavefront fetches
     __shared__ __attribute__((aligned(16))) KvBlock<HD> kvs[3];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lq = lane >> 4;
@@ -64,7 +64,8 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_kernel(const float* __rest
         const int nr = min(ROWS, R - r0);
         for (int idx = threadIdx.x; idx < nr * (HD / 4); idx += 256) {
             const int r = r0 + idx / (HD / 4), c = idx % (HD / 4) * 4;
-            store_planes4(out, plane, ((size_t)(m_first + r / G) * H + kvh * G + r % G) * HD + c, 0.f, 0.f, 0.f, 0.f);
+            const int m = m_first + r / G, col = (kvh * G + r % G) * HD + c;
+            store_planes4(out, plane, tiled ? xt_index(m, col, tiled) : (size_t)m * H * HD + col, 0.f, 0.f, 0.f, 0.f);
         }
         return;
     }
@@ -217,9 +218,9 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_kernel(const float* __rest
         if (row >= R) continue;
         const int qi = row / G, g = row - qi * G;
         const float inv = l > 0.f ? 1.0f / l : 0.f;
-        const size_t base = ((size_t)(m_first + qi) * H + kvh * G + g) * HD + 4 * lq;
+        const int m = m_first + qi, col = (kvh * G + g) * HD + 4 * lq;
 #pragma unroll
-        for (int t = 0; t < DT; ++t) store_planes4(out, plane, base + 16 * t, o[x][t][0] * inv, o[x][t][1] * inv, o[x][t][2] * inv, o[x][t][3] * inv);
+        for (int t = 0; t < DT; ++t) store_planes4(out, plane, tiled ? xt_index(m, col + 16 * t, tiled) : (size_t)m * H * HD + col + 16 * t, o[x][t][0] * inv, o[x][t][1] * inv, o[x][t][2] * inv, o[x][t][3] * inv);
     }
 }
 
@@ -231,7 +232,7 @@ bool attn_prompt_applies(int B, int q_len, int H, int KVH, int hd) {
 }
 
 int launch_attn_prompt(const float* q, const uint16_t* k_cache, const uint16_t* v_cache, const int32_t* pos, int B, int q_len, int H, int KVH,
-                       int hd, int cache_len, uint16_t* out, size_t plane, hipStream_t s) {
+                       int hd, int cache_len, uint16_t* out, size_t plane, int tiled, hipStream_t s) {
     BS_REQUIRE(attn_prompt_applies(B, q_len, H, KVH, hd) && cache_len % 32 == 0, BS_ESHAPE, "attn_prompt: B=%d q_len=%d head_dim=%d", B, q_len, hd);
     const int R = H / KVH * q_len;
     const float scale = 1.44269504088896341f / sqrtf((float)hd);   // scores as base-2 exponents
@@ -243,7 +244,7 @@ int launch_attn_prompt(const float* q, const uint16_t* k_cache, const uint16_t* 
     hipEvent_t e0 = nullptr, e1 = nullptr;
     const int rc = prof_events(s, &e0, &e1);
     if (rc != BS_OK) return rc;
-#define BS_PROMPT(HD, NT) BS_LAUNCH_TIMED((attn_prompt_kernel<HD, NT>), grid, block, 0, s, e0, e1, q, k_cache, v_cache, pos, B, q_len, H, KVH, cache_len, scale, n_rt, out, plane)
+#define BS_PROMPT(HD, NT) BS_LAUNCH_TIMED((attn_prompt_kernel<HD, NT>), grid, block, 0, s, e0, e1, q, k_cache, v_cache, pos, B, q_len, H, KVH, cache_len, scale, n_rt, out, plane, tiled)
     if (hd == 128) { if (wide) BS_PROMPT(128, 2); else BS_PROMPT(128, 1); }
     else { if (wide) BS_PROMPT(64, 2); else BS_PROMPT(64, 1); }
 #undef BS_PROMPT

@@ -72,6 +72,20 @@ __device__ __forceinline__ void store_planes4(uint16_t* base, size_t plane, size
     *reinterpret_cast<uint2*>(base + plane + idx) = make_uint2((uint32_t)l0 | ((uint32_t)l1 << 16), (uint32_t)l2 | ((uint32_t)l3 << 16));
 }
 
+// Tiled activation planes: [K/32][R rows][32 columns].  For the whole-K projections of up to 32 rows (gemm_rows_kernel) R = 16
+// or 32 (rows_tiled), so that the B operand of one k step (16 rows x 64 bytes) is one contiguous kilobyte like a weight tile,
+// instead of 16 pieces of 16 different cache lines.  A plane is R*K elements whatever the row count; rows >= M are neither
+// written nor read.  For the many-row projections (gemm_big.hip) R is the row count rounded up to 16: the 16 rows of a stage that a
+// wavefront's transfer moves into LDS are then eight whole cache lines, not halves of sixteen whose other halves are the next stage's.
+// R = 32: inside a k step [row / 4][chunk of 8 columns][row % 4][8].  The address unit takes four consecutive lanes at a time, and in
+// a B operand these hold one chunk of four rows: here they meet in one 64-byte run instead of four.  With two row tiles the activations are
+// most of what O and down request (7B layer, 20 rows: O 14.0 -> 13.2, down 33.5 -> 31.8 us; a pass 4646 -> 4553).  With one tile
+// the planes stay row by row: 9 rows touch 5 lines of a k step that way and 6 this way (O and down together 31.5 -> 32.3 us).
+__device__ __forceinline__ size_t xt_index(int m, int k, int R) {
+    const int in = R == 32 ? (m >> 2) * 128 + ((k >> 3) & 3) * 32 + (m & 3) * 8 + (k & 7) : m * 32 + (k & 31);
+    return (size_t)(k >> 5) * (R * 32) + in;
+}
+
 // r = rsqrt(mean square + eps) of row m from its per-chunk sums of squares (null: no scaling)
 __device__ __forceinline__ float row_rscale(const float* __restrict__ ssq, int nchunks, int m, float inv_d, float eps) {
     if (!ssq) return 1.f;

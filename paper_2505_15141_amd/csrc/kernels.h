@@ -16,6 +16,7 @@ struct GemmArgs {
     size_t ks_stride;
     int M, N, K, ldo, KS;
     int tiled;            // weights are in the 64x32-block layout written by launch_pack_weights
+    int x_tiled;          // many-row GEMM: R = many_tiled(M) if the planes of x are tiled (xt_index, x_plane = R K), else 0 (row-major)
 };
 
 // Fused projection for a handful of rows (see gemm_dec_kernel): tiled bf16 weights, activations as planes.
@@ -27,13 +28,14 @@ struct DecArgs {
     int M, N, K;                              // N: output columns (per matrix for SWIGLU)
     const float* ssq_in; int ssq_tiles; float eps;     // input rows' partial sums of squares [M][ssq_tiles] (QKV, SWIGLU)
     float* x; const float* gain_next; uint16_t* out_planes; size_t out_plane; float* ssq_out;   // RESID; out_planes also SWIGLU
-    int out_tiled;                            // gemm_rows: R = rows_tiled(M) if the output planes are tiled (xt_index; out_plane = R N), else 0
+    int out_tiled;                            // R = rows_tiled(M) (gemm_rows) or many_tiled(M) (gemm_big) if the output planes are tiled (xt_index; out_plane = R N), else 0
     const int32_t* pos; const float2* rope; int q_len, H, KVH, hd, cache_len;                    // QKV
     float* q_out; uint16_t* k_cache; uint16_t* v_cache;
     const float* att_part; int att_splits;    // RESID with the attention's per-split partials as input instead of planes (uses H, hd)
 };
 bool gemm_dec_fits(int M, int K);
 int launch_gemm_dec(int epi, const DecArgs& a, hipStream_t s);
+inline int many_tiled(int M) { return (M + 15) / 16 * 16; }    // rows of the tiled activation planes of the many-row projections
 constexpr int ROWS_MAX = 32;                                 // rows the whole-K projections take
 inline int rows_tiled(int M) { return M <= 16 ? 16 : 32; }   // rows of their tiled activation planes
 // The same epilogues for up to ROWS_MAX rows of a wide model: one workgroup per compute unit owns several
@@ -107,15 +109,15 @@ int launch_prep(const int32_t* q_tokens, int q_stride, const int32_t* kv_len, in
                 int32_t* status, void* clear, size_t clear_bytes, const AttnParts& ap, hipStream_t s);
 int launch_embed(int dtype, const int32_t* tok, const void* embed, int M, int d, float* x, hipStream_t s);
 int launch_rmsnorm(int dtype, float* x, const float* pend, int pend_ks, size_t pend_stride, const float* gain, int d,
-                   float eps, int n_seq, int rows_in, int rows_out, size_t plane, void* out, hipStream_t s);
+                   float eps, int n_seq, int rows_in, int rows_out, size_t plane, void* out, int tiled, hipStream_t s);
 // bf16 models: residual completion + planes of gain .* x + per-chunk sums of squares [rows][norm_chunks(d)]; the
 // consumers below apply the rows' RMS scale when given such sums (ssq != nullptr), ssq_n of them per row: other writers of x
 // leave another number
 int norm_chunks(int d);
-// tiled = R > 0: planes in the layout of the whole-K projections, [d/32][R][32], plane = R*d elements
+// tiled = R > 0 (here, above and below): planes in the layout of xt_index, [d/32][R][32], plane = R*d elements
 int launch_resid_sum(float* x, const float* pend, int pend_ks, size_t pend_stride, const float* gain, int d, int rows,
                      size_t plane, void* out, float* ssq, int tiled, hipStream_t s);
-int launch_swiglu(int dtype, const float* part, int ks, size_t ks_stride, int M, int ff, size_t plane, void* out,
+int launch_swiglu(int dtype, const float* part, int ks, size_t ks_stride, int M, int ff, size_t plane, void* out, int tiled,
                   const float* ssq, int ssq_n, int d, float eps, hipStream_t s);
 int launch_rope_kv(int dtype, const float* part, int ks, size_t ks_stride, const int32_t* pos, const float2* rope, int M,
                    int q_len, int H, int KVH, int hd, int max_len, float* q_out, void* k_cache, void* v_cache,
@@ -125,10 +127,10 @@ int launch_rope_kv(int dtype, const float* part, int ks, size_t ks_stride, const
 // workgroups resident together; otherwise a merge kernel runs): zero when the pass starts, one flag per layer.
 struct AttnCells { void* buf; size_t bytes; unsigned flag, spin_limit; int32_t* status; };
 size_t attn_cells_bytes(int rows, int H, int hd, int n_splits);
-// prompt chunks (attn_prompt.hip): whole output, row-major planes
+// prompt chunks (attn_prompt.hip): whole output, planes row-major or tiled (rows of the planes, xt_index)
 bool attn_prompt_applies(int B, int q_len, int H, int KVH, int hd);
 int launch_attn_prompt(const float* q, const uint16_t* k_cache, const uint16_t* v_cache, const int32_t* pos, int B, int q_len, int H, int KVH,
-                       int hd, int cache_len, uint16_t* out, size_t plane, hipStream_t s);
+                       int hd, int cache_len, uint16_t* out, size_t plane, int tiled, hipStream_t s);
 // key splits that a launch with `out` uses over a cache of cache_len rows when it may use up to n_splits: `splits`, or where `most` is
 // more a count for every sequence between the two (AttnParts); and whether its workgroups combine them themselves (AttnCells)
 // if the caller has cells.  `part` holds `most` partials a row.

@@ -158,19 +158,6 @@ __global__ __launch_bounds__(256) void embed_dec_kernel(const int32_t* __restric
     if (threadIdx.x == 0) ssq[m] = red[0] + red[1] + red[2] + red[3];
 }
 
-// Activation planes for the whole-K projections of up to 32 rows (gemm_rows_kernel): [K/32][R rows][32 columns], R = 16
-// or 32 (rows_tiled), so that the B operand of one k step (16 rows x 64 bytes) is one contiguous kilobyte like a weight tile,
-// instead of 16 pieces of 16 different cache lines.  A plane is R*K elements whatever the row count; rows >= M are neither
-// written nor read.
-// R = 32: inside a k step [row / 4][chunk of 8 columns][row % 4][8].  The address unit takes four consecutive lanes at a time, and in
-// a B operand these hold one chunk of four rows: here they meet in one 64-byte run instead of four.  With two row tiles the activations are
-// most of what O and down request (7B layer, 20 rows: O 14.0 -> 13.2, down 33.5 -> 31.8 us; a pass 4646 -> 4553).  With one tile
-// the planes stay row by row: 9 rows touch 5 lines of a k step that way and 6 this way (O and down together 31.5 -> 32.3 us).
-__device__ __forceinline__ size_t xt_index(int m, int k, int R) {
-    const int in = R == 32 ? (m >> 2) * 128 + ((k >> 3) & 3) * 32 + (m & 3) * 8 + (k & 7) : m * 32 + (k & 31);
-    return (size_t)(k >> 5) * (R * 32) + in;
-}
-
 // ---- RMSNorm (+ pending split-K partials of the previous projection) -----------------------------
 // out row r takes input row src = (r / rows_out) * rows_in + (rows_in - rows_out) + r % rows_out
 // (rows_out = rows_in: identity; rows_out < rows_in: the trailing rows of every sequence).
@@ -179,7 +166,7 @@ template <typename T>
 __global__ __launch_bounds__(1024) void rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ pend, int pend_ks,
                                                        size_t pend_stride, const float* __restrict__ gain, int d,
                                                        float eps, int rows_in, int rows_out, size_t plane,
-                                                       void* __restrict__ out) {
+                                                       void* __restrict__ out, int tiled) {
     __shared__ float red[16];
     const int r = blockIdx.x;
     const int src = (r / rows_out) * rows_in + (rows_in - rows_out) + r % rows_out;
@@ -213,10 +200,11 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(float* __restrict__ x, co
     for (int i = threadIdx.x * 4; i < d; i += 4096) {
         const float4 v = *reinterpret_cast<const float4*>(row + i);        // own earlier write, or the input
         const float4 g = *reinterpret_cast<const float4*>(gain + i);
-        Act<T>::store(out, plane, (size_t)r * d + i, v.x * scale * g.x);
-        Act<T>::store(out, plane, (size_t)r * d + i + 1, v.y * scale * g.y);
-        Act<T>::store(out, plane, (size_t)r * d + i + 2, v.z * scale * g.z);
-        Act<T>::store(out, plane, (size_t)r * d + i + 3, v.w * scale * g.w);
+        const size_t idx = tiled ? xt_index(r, i, tiled) : (size_t)r * d + i;        // four columns side by side in either layout
+        Act<T>::store(out, plane, idx, v.x * scale * g.x);
+        Act<T>::store(out, plane, idx + 1, v.y * scale * g.y);
+        Act<T>::store(out, plane, idx + 2, v.z * scale * g.z);
+        Act<T>::store(out, plane, idx + 3, v.w * scale * g.w);
     }
 }
 
@@ -265,7 +253,7 @@ __global__ __launch_bounds__(256) void resid_sum_kernel(float* __restrict__ x, c
 // ---- SwiGLU over split-K partials: act = silu(sum_s g) * sum_s u, columns [0,ff) gate, [ff,2ff) up ------
 template <typename T>
 __global__ void swiglu_kernel(const float* __restrict__ part, int ks, size_t ks_stride, int M, int ff, size_t plane,
-                              void* __restrict__ out, const float* __restrict__ ssq, int nchunks, float inv_d, float eps) {
+                              void* __restrict__ out, int tiled, const float* __restrict__ ssq, int nchunks, float inv_d, float eps) {
     const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (size_t)M * ff) return;
     const size_t m = idx / ff, j = idx % ff;
@@ -276,7 +264,7 @@ __global__ void swiglu_kernel(const float* __restrict__ part, int ks, size_t ks_
     }
     const float rs = row_rscale(ssq, nchunks, (int)m, inv_d, eps);     // the input rows' RMS scale, if it was deferred
     g *= rs; u *= rs;
-    Act<T>::store(out, plane, idx, g / (1.0f + __expf(-g)) * u);
+    Act<T>::store(out, plane, tiled ? xt_index((int)m, (int)j, tiled) : idx, g / (1.0f + __expf(-g)) * u);
 }
 
 // ---- GEMM, bf16 weights streamed through MFMA -------------------------------------------------------
@@ -2092,13 +2080,13 @@ int launch_embed(int dtype, const int32_t* tok, const void* embed, int M, int d,
 }
 
 int launch_rmsnorm(int dtype, float* x, const float* pend, int pend_ks, size_t pend_stride, const float* gain, int d,
-                   float eps, int n_seq, int rows_in, int rows_out, size_t plane, void* out, hipStream_t s) {
+                   float eps, int n_seq, int rows_in, int rows_out, size_t plane, void* out, int tiled, hipStream_t s) {
     const int rows = n_seq * rows_out;
     if (rows <= 0) return BS_OK;
     if (dtype == BS_BF16)
-        hipLaunchKernelGGL((rmsnorm_kernel<uint16_t>), dim3(rows), dim3(1024), 0, s, x, pend, pend_ks, pend_stride, gain, d, eps, rows_in, rows_out, plane, out);
+        hipLaunchKernelGGL((rmsnorm_kernel<uint16_t>), dim3(rows), dim3(1024), 0, s, x, pend, pend_ks, pend_stride, gain, d, eps, rows_in, rows_out, plane, out, tiled);
     else
-        hipLaunchKernelGGL((rmsnorm_kernel<float>), dim3(rows), dim3(1024), 0, s, x, pend, pend_ks, pend_stride, gain, d, eps, rows_in, rows_out, plane, out);
+        hipLaunchKernelGGL((rmsnorm_kernel<float>), dim3(rows), dim3(1024), 0, s, x, pend, pend_ks, pend_stride, gain, d, eps, rows_in, rows_out, plane, out, tiled);
     BS_LAUNCH_CHECK();
     return BS_OK;
 }
@@ -2117,13 +2105,13 @@ int launch_resid_sum(float* x, const float* pend, int pend_ks, size_t pend_strid
     return BS_OK;
 }
 
-int launch_swiglu(int dtype, const float* part, int ks, size_t ks_stride, int M, int ff, size_t plane, void* out,
+int launch_swiglu(int dtype, const float* part, int ks, size_t ks_stride, int M, int ff, size_t plane, void* out, int tiled,
                   const float* ssq, int ssq_n, int d, float eps, hipStream_t s) {
     const size_t n = (size_t)M * ff;
     const dim3 grid((unsigned)((n + 255) / 256)), block(256);
     const float inv_d = 1.0f / (float)d;
-    if (dtype == BS_BF16) hipLaunchKernelGGL((swiglu_kernel<uint16_t>), grid, block, 0, s, part, ks, ks_stride, M, ff, plane, out, ssq, ssq_n, inv_d, eps);
-    else hipLaunchKernelGGL((swiglu_kernel<float>), grid, block, 0, s, part, ks, ks_stride, M, ff, plane, out, ssq, ssq_n, inv_d, eps);
+    if (dtype == BS_BF16) hipLaunchKernelGGL((swiglu_kernel<uint16_t>), grid, block, 0, s, part, ks, ks_stride, M, ff, plane, out, tiled, ssq, ssq_n, inv_d, eps);
+    else hipLaunchKernelGGL((swiglu_kernel<float>), grid, block, 0, s, part, ks, ks_stride, M, ff, plane, out, tiled, ssq, ssq_n, inv_d, eps);
     BS_LAUNCH_CHECK();
     return BS_OK;
 }
@@ -2233,9 +2221,9 @@ int launch_attention(int dtype, const float* q, const void* k_cache, const void*
     BS_REQUIRE(!out_tiled || (dtype == BS_BF16 && out && B * q_len <= out_tiled), BS_ESHAPE, "attention: tiled output planes hold at most %d rows", out_tiled);
     const float scale = 1.0f / sqrtf((float)hd);
     const dim3 block(256);
-    if (dtype == BS_BF16 && out && !out_tiled && attn_prompt_applies(B, q_len, H, KVH, hd))
+    if (dtype == BS_BF16 && out && (!out_tiled || out_tiled > ROWS_MAX) && attn_prompt_applies(B, q_len, H, KVH, hd))
         return launch_attn_prompt(q, reinterpret_cast<const uint16_t*>(k_cache), reinterpret_cast<const uint16_t*>(v_cache), pos, B, q_len, H, KVH, hd,
-                                  max_len, reinterpret_cast<uint16_t*>(out), plane, s);
+                                  max_len, reinterpret_cast<uint16_t*>(out), plane, out_tiled, s);
     if (dtype == BS_BF16) {
         const int n_tiles = (H / KVH * q_len + 15) / 16;
         // two tiles per wavefront as soon as there are two: a K or V block then serves 32 rows (verification with grouped

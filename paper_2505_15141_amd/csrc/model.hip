@@ -177,7 +177,7 @@ static bool streams_past_cache(const bs_model_cfg& c, size_t kv_bytes) {
 static FwdWs carve(const bs_model_cfg& c, int B, int q_len, int max_len, char* base) {
     FwdWs w;
     const size_t M = (size_t)B * q_len;
-    const size_t Mp = M <= ROWS_MAX ? rows_tiled((int)M) : M;     // planes in the tiled layout of the whole-K projections
+    const size_t Mp = M <= ROWS_MAX ? rows_tiled((int)M) : many_tiled((int)M);     // planes in a tiled layout (xt_index)
     const size_t nq = (size_t)c.n_heads * c.head_dim, nkv = (size_t)c.n_kv_heads * c.head_dim;
     w.ks_qkv = gemm_splits(c.dtype, (int)(nq + 2 * nkv), c.d_model, (int)M);
     w.ks_o = gemm_splits(c.dtype, c.d_model, (int)nq, (int)M);
@@ -350,7 +350,11 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
     // turns: QKV and gate/up from two units per compute unit on; O and down (one unit each on the 7B shape) only between
     // those two, which produce and consume the layouts they use.  A layer is then 6 kernels instead of 10.
     bool fuse_qkv = false, fuse_gu = false, fuse_o = false, fuse_d = false;
-    const int RT = rows_tiled(M);             // rows of the tiled planes there
+    // Rows of the tiled planes: there; and with 33 rows and more, where every projection reads whole stages of 32 columns (one of 144 rows
+    // 66.5 -> 64.0 us, a prompt of 1023 tokens 24.0 -> 23.2 ms on the 7B shape).
+    const int RT = dt != BS_BF16 ? 0 : M <= ROWS_MAX ? rows_tiled(M) : d % 32 == 0 && nq % 32 == 0 && ff % 32 == 0 ? many_tiled(M) : 0;
+    const bool many = M > ROWS_MAX && RT > 0;
+    const int MP = many ? RT : M;             // rows that a plane of a projection with split sums holds
     if (dt == BS_BF16 && m->packed && M <= ROWS_MAX) {
         int g = 0;
         int tu = (hd == 64 || hd == 128) && nq % 16 == 0 && nkv % 16 == 0 ? gemm_rows_units(EPI_QKV, M, nqkv, d, &g) : 0;
@@ -377,15 +381,15 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
         const bool ready = defer && (fuse_d || w.big_d) && l > 0;       // the down projection of the layer before left x, the planes and the sums of squares
         if (ready) {}
         else if (defer) {
-            BS_TRY(launch_resid_sum(w.x, pend, w.ks_d, (size_t)M * d, L.attn_norm, d, M, fuse_qkv ? (size_t)RT * d : (size_t)M * d, w.h, w.ssq,
-                                    fuse_qkv ? RT : 0, s));
+            BS_TRY(launch_resid_sum(w.x, pend, w.ks_d, (size_t)M * d, L.attn_norm, d, M, fuse_qkv ? (size_t)RT * d : (size_t)MP * d, w.h, w.ssq,
+                                    fuse_qkv || many ? RT : 0, s));
             ssq_n = norm_chunks(d);
         } else
             BS_TRY(launch_rmsnorm(dt, w.x, pend, w.ks_d, (size_t)M * d, L.attn_norm, d, c.norm_eps, B, q_len, q_len,
-                                  (size_t)M * d, w.h, s));
+                                  (size_t)M * d, w.h, 0, s));
         GemmArgs g;
-        g.tiled = m->packed ? 1 : 0;
-        g.x = w.h; g.x_plane = (size_t)M * d; g.w[0] = L.wq; g.w[1] = L.wk; g.w[2] = L.wv; g.seg_rows[0] = nq; g.seg_rows[1] = nkv;
+        g.tiled = m->packed ? 1 : 0; g.x_tiled = many ? RT : 0;
+        g.x = w.h; g.x_plane = (size_t)MP * d; g.w[0] = L.wq; g.w[1] = L.wk; g.w[2] = L.wv; g.seg_rows[0] = nq; g.seg_rows[1] = nkv;
         g.out = w.part_qkv; g.ks_stride = (size_t)M * nqkv; g.M = M; g.N = nqkv; g.K = d; g.ldo = nqkv; g.KS = w.ks_qkv;
         if (fuse_qkv) {
             DecArgs a = {};
@@ -407,8 +411,8 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
                               w.q, kc, vc, ssq, ssq_n, d, c.norm_eps, s));
         }
         BS_TRY(launch_attention(dt, w.q, kc, vc, w.pos, B, q_len, H, KVH, hd, crow, splits, w.part_attn,
-                                fuse_o ? (size_t)RT * nq : (size_t)M * nq, w.att, fuse_o ? RT : 0, in_kernel_merge ? &ac : nullptr, &w.att_parts, stream, s));
-        g.x = w.att; g.x_plane = (size_t)M * nq; g.w[0] = L.wo; g.w[1] = g.w[2] = nullptr; g.seg_rows[0] = d; g.seg_rows[1] = 0;
+                                fuse_o ? (size_t)RT * nq : (size_t)MP * nq, w.att, fuse_o || many ? RT : 0, in_kernel_merge ? &ac : nullptr, &w.att_parts, stream, s));
+        g.x = w.att; g.x_plane = (size_t)MP * nq; g.w[0] = L.wo; g.w[1] = g.w[2] = nullptr; g.seg_rows[0] = d; g.seg_rows[1] = 0;
         g.out = w.part_o; g.ks_stride = (size_t)M * d; g.M = M; g.N = d; g.K = nq; g.ldo = d; g.KS = w.ks_o;
         if (fuse_o) {
             DecArgs a = {};
@@ -419,20 +423,20 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
             ssq_n = d / 16;
         } else if (w.big_o) {
             DecArgs a = {};
-            a.N = d; a.x = w.x; a.gain_next = L.ffn_norm; a.out_planes = reinterpret_cast<uint16_t*>(w.h); a.out_plane = (size_t)M * d; a.ssq_out = w.ssq;
+            a.N = d; a.x = w.x; a.gain_next = L.ffn_norm; a.out_planes = reinterpret_cast<uint16_t*>(w.h); a.out_plane = (size_t)MP * d; a.out_tiled = g.x_tiled; a.ssq_out = w.ssq;
             BS_TRY(launch_gemm_big_fused(EPI_RESID, g, a, w.part_o, w.part_o_bytes, s));
             ssq_n = w.tiles_o;
         } else {
         BS_TRY(launch_gemm(dt, g, s));
         if (defer) {
-            BS_TRY(launch_resid_sum(w.x, w.part_o, w.ks_o, (size_t)M * d, L.ffn_norm, d, M, fuse_gu ? (size_t)RT * d : (size_t)M * d, w.h, w.ssq,
-                                    fuse_gu ? RT : 0, s));
+            BS_TRY(launch_resid_sum(w.x, w.part_o, w.ks_o, (size_t)M * d, L.ffn_norm, d, M, fuse_gu ? (size_t)RT * d : (size_t)MP * d, w.h, w.ssq,
+                                    fuse_gu || many ? RT : 0, s));
             ssq_n = norm_chunks(d);
         } else
             BS_TRY(launch_rmsnorm(dt, w.x, w.part_o, w.ks_o, (size_t)M * d, L.ffn_norm, d, c.norm_eps, B, q_len, q_len,
-                                  (size_t)M * d, w.h, s));
+                                  (size_t)M * d, w.h, 0, s));
         }
-        g.x = w.h; g.x_plane = (size_t)M * d; g.w[0] = L.w_gate; g.w[1] = L.w_up; g.w[2] = nullptr; g.seg_rows[0] = ff; g.seg_rows[1] = ff;
+        g.x = w.h; g.x_plane = (size_t)MP * d; g.w[0] = L.w_gate; g.w[1] = L.w_up; g.w[2] = nullptr; g.seg_rows[0] = ff; g.seg_rows[1] = ff;
         g.out = w.part_gu; g.ks_stride = (size_t)M * 2 * ff; g.M = M; g.N = 2 * ff; g.K = d; g.ldo = 2 * ff; g.KS = w.ks_gu;
         if (fuse_gu) {
             DecArgs a = {};
@@ -443,13 +447,13 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
         } else if (w.big_gu) {
             DecArgs a = {};
             g.N = ff; a.N = ff; a.ssq_in = w.ssq; a.ssq_tiles = ssq_n; a.eps = c.norm_eps;
-            a.out_planes = reinterpret_cast<uint16_t*>(w.act); a.out_plane = (size_t)M * ff;
+            a.out_planes = reinterpret_cast<uint16_t*>(w.act); a.out_plane = (size_t)MP * ff; a.out_tiled = g.x_tiled;
             BS_TRY(launch_gemm_big_fused(EPI_SWIGLU, g, a, w.part_gu, w.part_gu_bytes, s));
         } else {
         BS_TRY(launch_gemm(dt, g, s));
-        BS_TRY(launch_swiglu(dt, w.part_gu, w.ks_gu, (size_t)M * 2 * ff, M, ff, (size_t)M * ff, w.act, ssq, ssq_n, d, c.norm_eps, s));
+        BS_TRY(launch_swiglu(dt, w.part_gu, w.ks_gu, (size_t)M * 2 * ff, M, ff, (size_t)MP * ff, w.act, g.x_tiled, ssq, ssq_n, d, c.norm_eps, s));
         }
-        g.x = w.act; g.x_plane = (size_t)M * ff; g.w[0] = L.w_down; g.w[1] = g.w[2] = nullptr; g.seg_rows[0] = d; g.seg_rows[1] = 0;
+        g.x = w.act; g.x_plane = (size_t)MP * ff; g.w[0] = L.w_down; g.w[1] = g.w[2] = nullptr; g.seg_rows[0] = d; g.seg_rows[1] = 0;
         g.out = w.part_d; g.ks_stride = (size_t)M * d; g.M = M; g.N = d; g.K = ff; g.ldo = d; g.KS = w.ks_d;
         if (fuse_d) {
             const bool more = l + 1 < c.n_layers;
@@ -463,7 +467,7 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
         } else if (w.big_d) {
             DecArgs a = {};
             a.N = d; a.x = w.x; a.gain_next = l + 1 < c.n_layers ? m->layers[l + 1].attn_norm : nullptr;
-            a.out_planes = reinterpret_cast<uint16_t*>(w.h); a.out_plane = (size_t)M * d; a.ssq_out = a.gain_next ? w.ssq : nullptr;
+            a.out_planes = reinterpret_cast<uint16_t*>(w.h); a.out_plane = (size_t)MP * d; a.out_tiled = g.x_tiled; a.ssq_out = a.gain_next ? w.ssq : nullptr;
             BS_TRY(launch_gemm_big_fused(EPI_RESID, g, a, w.part_d, w.part_d_bytes, s));
             ssq_n = w.tiles_d;
         } else {
@@ -474,11 +478,13 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
     }
     if (logit_rows > 0) {
         const int R = B * logit_rows;
+        const bool together = logits_bstride == (size_t)logit_rows * c.vocab || logit_rows == 1;      // one product for all sequences
+        const int LT = dt == BS_BF16 && together && R > ROWS_MAX && d % 32 == 0 ? many_tiled(R) : 0, LP = LT ? LT : R;
         BS_TRY(launch_rmsnorm(dt, w.x, pend, w.ks_d, (size_t)M * d, m->final_norm, d, c.norm_eps, B, q_len, logit_rows,
-                              (size_t)R * d, w.h, s));
+                              (size_t)LP * d, w.h, LT, s));
         GemmArgs g;
-        g.tiled = m->packed ? 1 : 0;
-        g.x_plane = (size_t)R * d;
+        g.tiled = m->packed ? 1 : 0; g.x_tiled = LT;
+        g.x_plane = (size_t)LP * d;
         g.w[0] = m->lm_head; g.w[1] = g.w[2] = nullptr; g.seg_rows[0] = c.vocab; g.seg_rows[1] = 0;
         g.N = c.vocab; g.K = d; g.KS = 1; g.ks_stride = 0;
         if (logits_bstride == (size_t)logit_rows * c.vocab) {            // rows of all sequences contiguous

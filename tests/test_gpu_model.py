@@ -741,3 +741,18 @@ def test_resident_step_with_a_sequence_left_out():
         ref = forward(c, W, toks[0, :31 + step], storage="bf16")
         assert np.max(np.abs(lg[0, 0].cpu().numpy() - ref[30 + step])) < TOL["bf16"], step
         kvl[0] += 1
+
+
+# Passes of 33 rows and more: tiled activation planes (rows rounded up to 16) in the layers, and in front of the LM head where it has that many rows
+@pytest.mark.parametrize("c", [MID_GQA, synth.cfg(2, 96, 2, 64, 168, 1000, dtype="bf16")], ids=["tiled", "d_ff of 168: row by row"])
+@pytest.mark.parametrize("B,q_len,rows", [(11, 3, 3), (9, 5, 4), (9, 5, 1), (35, 1, 1), (3, 16, 16), (29, 9, 9)])
+def test_planes_of_33_rows_and_more(c, B, q_len, rows):
+    n, max_len = 20, 40
+    W, m, kv = setup(c, B, max_len, seed=91, packed=c["d_ff"] % 32 == 0)
+    toks = synth.make_prompts(B, n + q_len, c["vocab"], 92)
+    dt = torch.from_numpy(toks.astype(np.int32)).cuda()
+    bs().prefill(m, kv, dt, n)
+    logits = bs().verify_forward(m, kv, dt[:, n:].contiguous(), torch.full((B,), n, dtype=torch.int32, device="cuda"), rows)
+    for b in {0, 1, B // 2, B - 1}:
+        ref = forward(c, W, toks[b], storage="bf16", last_rows=rows)
+        assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
