@@ -1507,7 +1507,7 @@ __global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, 
 // check): a workgroup hands its partial over in exchange cells instead of `part`, then the workgroup of split s combines,
 // for the rows r = S-1-s, 2S-1-s, ... of its head group (S splits; the last splits hold the fewest keys, often none), the
 // partials of all splits as they arrive (bounded polls) and writes the attention output planes -- the hand-over costs
-// about 0.5 us and 1.55 for each of these rows (attn_plan), where a merge kernel costs five.
+// about 2 us, 1.6 more for every 256 / HD rows beyond the first, where a merge kernel costs five.
 // The cells are all zero when the pass starts (prep kernel) and every layer hands over under its own flag.
 struct AttnMerge {
     void* cells;                 // [M][H][n_splits][HD + 4] cells: o[HD], max, sum, 2 pad
@@ -1526,7 +1526,7 @@ struct AttnMerge {
 // one part writes the output itself, and of one of several the last workgroup to hand over combines the rows; nobody waits for a
 // workgroup that has not started.  A variant of its own: in the other kernels the larger code cost 0.8 us a launch (batch 16, head_dim 64).
 template <int HD, int NT, bool STREAM, bool AHEAD, bool PARTS>
-__global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_kernel(const float* __restrict__ q, const uint16_t* __restrict__ k_cache,
+__global__ __launch_bounds__(256, NT == 2 ? 1 : HD == 64 ? 4 : 2) void attn_mfma_kernel(const float* __restrict__ q, const uint16_t* __restrict__ k_cache,
                                                         const uint16_t* __restrict__ v_cache,
                                                         const int32_t* __restrict__ pos, int q_len, int H, int KVH,
                                                         int cache_len, float scale, float* __restrict__ part, int n_splits,
@@ -1535,7 +1535,7 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
     constexpr int DS = HD / 32, DT = HD / 16;
     constexpr int PC = HD + 4;                   // cells of one partial
     __shared__ float wm[4][16], wl[4][16];
-    __shared__ float wo[4][16][HD + 1];
+    __shared__ __attribute__((aligned(16))) float wo[4][16][HD + 4];
     // blockIdx.x = (group of NT row tiles, split of the keys): with many query rows (a prompt chunk) the groups are
     // spread over workgroups and the keys over few splits; with one group all of gridDim.x are key splits
     int split, rt, n_rt, kvh, b, used, pos0;
@@ -1591,32 +1591,6 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
         const int nblk = (pos0 + qi_max + 1 + 31) / 32;
         const int per = (nblk + used - 1) / used;
         const int b_begin = split * per, b_end = min(nblk, b_begin + per);
-        bool rvalid[NT];
-        int row_pos[NT];
-        uint4 qh[NT][DS], ql[NT][DS];
-        float m_run[NT], l_run[NT];
-        f32x4 o[NT][DT];
-#pragma unroll
-        for (int x = 0; x < NT; ++x) {
-            const int row = r0 + 16 * x + li;
-            rvalid[x] = row < R;
-            const int g = rvalid[x] ? row / q_len : 0, qi = rvalid[x] ? row % q_len : 0;
-            row_pos[x] = pos0 + qi;
-            const float* qrow = q + ((size_t)(m_first + qi) * H + kvh * G + g) * HD;
-#pragma unroll
-            for (int ds = 0; ds < DS; ++ds) {
-                float v[8];
-                const float4 a = *reinterpret_cast<const float4*>(qrow + ds * 32 + lq * 8);
-                const float4 c = *reinterpret_cast<const float4*>(qrow + ds * 32 + lq * 8 + 4);
-                v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = c.x; v[5] = c.y; v[6] = c.z; v[7] = c.w;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = rvalid[x] ? v[e] * scale : 0.f;
-                split8(v, qh[x][ds], ql[x][ds]);
-            }
-            m_run[x] = -INFINITY; l_run[x] = 0.f;
-#pragma unroll
-            for (int t = 0; t < DT; ++t) o[x][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
         // STREAM: K rows of 256 bytes and V are asked for as data nobody reads again (batch 16, 4096 keys, head_dim 128: 212
         // -> 179 us; V alone 192); rows of 128 bytes stay cached, both halves of a line are then served by one request
         // (head_dim 64: a step of the batch 919 -> 890 us)
@@ -1633,6 +1607,48 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
 #pragma unroll
             for (int t = 0; t < DT; ++t) vf[t] = ldg16_stream<STREAM>(vb + ((size_t)blk * HD + t * 16 + li) * 32 + lq * 8);
         };
+        auto fetch = [&](int blk, uint4 (&kf)[2][DS], uint4 (&vf)[DT]) { fetch_k(blk, kf); fetch_v(blk, vf); };
+        bool rvalid[NT];
+        int row_pos[NT];
+        float4 qa[NT][DS][2];
+#pragma unroll
+        for (int x = 0; x < NT; ++x) {
+            const int row = r0 + 16 * x + li;
+            rvalid[x] = row < R;
+            const int g = rvalid[x] ? row / q_len : 0, qi = rvalid[x] ? row % q_len : 0;
+            row_pos[x] = pos0 + qi;
+            const float* qrow = q + ((size_t)(m_first + qi) * H + kvh * G + g) * HD;
+#pragma unroll
+            for (int ds = 0; ds < DS; ++ds) {
+                qa[x][ds][0] = *reinterpret_cast<const float4*>(qrow + ds * 32 + lq * 8);
+                qa[x][ds][1] = *reinterpret_cast<const float4*>(qrow + ds * 32 + lq * 8 + 4);
+            }
+        }
+        // The wavefront's first block is asked for together with the queries (without a block: the last one, not used).  That, two
+        // register sets, four elements a lane where the wavefronts' sums meet and rows combined side by side, us a launch, 7B shape: 1 x 9 rows,
+        // 1682 keys in 4 splits 16.9 -> 14.9; 1 x 5 at 705 in 2 15.1 -> 12.6; 1 x 9 at 7909 in 8 28.4 -> 26.7; 2 x 5 at 1805 in 3 19.0 -> 17.1; 8B
+        // shape, 2 x 4 at 2504 in 6 18.5 -> 14.9; 32 x 6 at 8198, two row tiles, 168 -> 160.
+        uint4 kf0[2][DS], vf0[DT];
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(min(b_begin + wave, nblk - 1), kf0, vf0);
+        __builtin_amdgcn_sched_barrier(0);
+        uint4 qh[NT][DS], ql[NT][DS];
+        float m_run[NT], l_run[NT];
+        f32x4 o[NT][DT];
+#pragma unroll
+        for (int x = 0; x < NT; ++x) {
+#pragma unroll
+            for (int ds = 0; ds < DS; ++ds) {
+                const float4 a = qa[x][ds][0], c = qa[x][ds][1];
+                float v[8] = {a.x, a.y, a.z, a.w, c.x, c.y, c.z, c.w};
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = rvalid[x] ? v[e] * scale : 0.f;
+                split8(v, qh[x][ds], ql[x][ds]);
+            }
+            m_run[x] = -INFINITY; l_run[x] = 0.f;
+#pragma unroll
+            for (int t = 0; t < DT; ++t) o[x][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
         // more (one tile): the next block's keys and values are asked for as soon as their registers are free, under this block's
         // softmax and products.  Four blocks before the end every key is visible to all of the at most 16 query positions (rows
         // that do not exist have zero queries, and nobody reads their sums).  No branch around those loads: the compiler would have to wait for all of them at the next use.
@@ -1713,26 +1729,33 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        auto fetch = [&](int blk, uint4 (&kf)[2][DS], uint4 (&vf)[DT]) { fetch_k(blk, kf); fetch_v(blk, vf); };
-        if constexpr (NT == 1 && !AHEAD) {
+        if constexpr (NT == 1 && !AHEAD && HD == 64) {
             for (int blk = b_begin + wave; blk < b_end; blk += 4) {
-                uint4 kf[2][DS], vf[DT];
-                fetch(blk, kf, vf);
-                block(blk, kf, vf, false);
+                if (blk != b_begin + wave) fetch(blk, kf0, vf0);
+                block(blk, kf0, vf0, false);
             }
+        } else if constexpr (NT == 1 && !AHEAD) {
+            // two register sets (head_dim 64, which keeps four workgroups on a compute unit, has none to spare): the next block is
+            // requested before the one at hand is multiplied
+            uint4 kf1[2][DS], vf1[DT];
+            int blk = b_begin + wave;
+            for (; blk + 4 < b_end; blk += 8) {
+                fetch(blk + 4, kf1, vf1);
+                block(blk, kf0, vf0, false);
+                fetch(min(blk + 8, b_end - 1), kf0, vf0);
+                block(blk + 4, kf1, vf1, false);
+            }
+            if (blk < b_end) block(blk, kf0, vf0, false);
         } else if constexpr (NT == 1) {
-            uint4 kf[2][DS], vf[DT];
             int blk = b_begin + wave;
             if (blk < b_end) {
-                fetch(blk, kf, vf);
-                for (; blk + 4 < b_end; blk += 4) block(blk, kf, vf, true);
-                block(blk, kf, vf, false);
+                for (; blk + 4 < b_end; blk += 4) block(blk, kf0, vf0, true);
+                block(blk, kf0, vf0, false);
             }
         } else if (b_begin + wave < b_end) {
             // a request past the wavefront's last block repeats that block: in bounds, never used
             const int blk_last = b_begin + wave + ((b_end - 1 - b_begin - wave) >> 2) * 4;
-            uint4 kf0[2][DS], vf0[DT], kf1[2][DS], vf1[DT];
-            fetch(b_begin + wave, kf0, vf0);
+            uint4 kf1[2][DS], vf1[DT];
             for (int blk = b_begin + wave; blk < b_end; blk += 8) {
                 fetch(min(blk + 4, blk_last), kf1, vf1);
                 block(blk, kf0, vf0, false);
@@ -1752,36 +1775,38 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
             __syncthreads();
             if (lq == 0) { wm[wave][li] = m_run[x]; wl[wave][li] = lr; }
 #pragma unroll
-            for (int t = 0; t < DT; ++t)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) wo[wave][li][t * 16 + 4 * lq + e] = o[x][t][e];
+            for (int t = 0; t < DT; ++t) *reinterpret_cast<f32x4*>(&wo[wave][li][t * 16 + 4 * lq]) = o[x][t];
             __syncthreads();
-            for (int idx = threadIdx.x; idx < 16 * HD; idx += 256) {
-                const int r = idx / HD, d = idx % HD;
-                if (rbase + r >= R) continue;
+            // four elements a lane: 9 rows of 128 are two turns instead of eight 
+            for (int idx = threadIdx.x; idx < min(16, R - rbase) * (HD / 4); idx += 256) {
+                const int r = idx / (HD / 4), d = idx % (HD / 4) * 4;
                 const float mm = fmaxf(fmaxf(wm[0][r], wm[1][r]), fmaxf(wm[2][r], wm[3][r]));
-                float ov = 0.f, lv = 0.f;
+                f32x4 ov = {0.f, 0.f, 0.f, 0.f};
+                float lv = 0.f;
 #pragma unroll
                 for (int w = 0; w < 4; ++w) {
                     const float f = (wm[w][r] == -INFINITY) ? 0.f : __expf(wm[w][r] - mm);
-                    ov += wo[w][r][d] * f;
+                    const f32x4 wv = *reinterpret_cast<const f32x4*>(&wo[w][r][d]);
+                    ov[0] += wv[0] * f; ov[1] += wv[1] * f; ov[2] += wv[2] * f; ov[3] += wv[3] * f;
                     lv += wl[w][r] * f;
                 }
                 const int gg = (rbase + r) / q_len, qq = (rbase + r) % q_len;
                 if (direct_out) {                    // a single split of the keys: this is the attention output
                     const int m = m_first + qq, head = kvh * G + gg;
-                    Act<uint16_t>::store(direct_out, plane, mg.tiled ? xt_index(m, head * HD + d, mg.tiled) : ((size_t)m * H + head) * HD + d, lv > 0.f ? ov / lv : 0.f);
+                    const bool some = lv > 0.f;
+                    store_planes4(direct_out, plane, mg.tiled ? xt_index(m, head * HD + d, mg.tiled) : ((size_t)m * H + head) * HD + d,
+                                  some ? ov[0] / lv : 0.f, some ? ov[1] / lv : 0.f, some ? ov[2] / lv : 0.f, some ? ov[3] / lv : 0.f);
                     continue;
                 }
                 if (NT == 1 && in_cells) {           // hand the partial over in cells
                     const DevBuf bc = dev_buf(mg.cells);
                     const int c0 = (((m_first + qq) * H + kvh * G + gg) * n_splits + split) * PC;
-                    st_cell1(bc, c0 + d, ov, mg.flag);
+                    st_cells4(bc, c0 + d, ov[0], ov[1], ov[2], ov[3], mg.flag);
                     if (d == 0) st_cells2(bc, c0 + HD, mm, lv, mg.flag);
                     continue;
                 }
                 float* dst = part + ((((size_t)(m_first + qq)) * H + kvh * G + gg) * n_splits + split) * pstride;
-                dst[d] = ov;
+                *reinterpret_cast<f32x4*>(dst + d) = ov;
                 if (d == 0) { dst[HD] = mm; dst[HD + 1] = lv; }
             }
         }
@@ -1857,16 +1882,23 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
             }
             return;
         }
-        // ---- combine the splits of this workgroup's rows: lane = (head-dim element d, share sp0 of the splits) ----
-        constexpr int P = 256 / HD;                  // HD threads per share; sp0 is uniform in a wavefront
+        // ---- combine the splits of this workgroup's rows, 256 / HD of them at a time: lane = (head-dim element d, row, share of the
+        // splits).  With fewer rows than that the spare lanes take shares; row and share are uniform in a wavefront. ----
+        constexpr int SUBS = 256 / HD;
         constexpr int MU = 8;                        // splits a lane polls in one round (all loads in flight together)
         const DevBuf bc = dev_buf(mg.cells);
-        const int d = threadIdx.x % HD, sp0 = threadIdx.x / HD;
-        for (int rr = n_splits - 1 - split; rr < R; rr += n_splits) {
+        const int d = threadIdx.x % HD, sub = threadIdx.x / HD;
+        const int first = n_splits - 1 - split;
+        if (first >= R) return;
+        const int sh = SUBS == 4 && first + 2 * n_splits < R ? 2 : first + n_splits < R ? 1 : 0;         // 2^sh rows at a time
+        const int P = SUBS >> sh, rl = sub & ((1 << sh) - 1), sp0 = sub >> sh;
+        for (int rr0 = first; rr0 < R; rr0 += n_splits << sh) {
+            const bool live = rr0 + rl * n_splits < R;
+            const int rr = live ? rr0 + rl * n_splits : rr0;
             const int m = m_first + rr % q_len, head = kvh * G + rr / q_len;
             const int base = ((m * H + head) * n_splits) * PC;
             float mm = -INFINITY, o = 0.f, l = 0.f;
-            for (int s0 = sp0; s0 < n_splits; s0 += MU * P) {
+            for (int s0 = live ? sp0 : n_splits; s0 < n_splits; s0 += MU * P) {
                 u32x2 co[MU];
                 u32x4 cml[MU];
                 unsigned spins = 0;
@@ -1901,24 +1933,23 @@ __global__ __launch_bounds__(256, HD == 64 && NT == 1 ? 4 : 1) void attn_mfma_ke
                 }
                 mm = gm;
             }
-            __syncthreads();                         // wo / wm / wl are free again
-            wo[sp0][0][d] = o;
-            if (d == 0) { wm[sp0][0] = mm; wl[sp0][0] = l; }
-            __syncthreads();
-            if (sp0 == 0) {
-                float gm = wm[0][0];
-#pragma unroll
-                for (int p = 1; p < P; ++p) gm = fmaxf(gm, wm[p][0]);
-                float ov = 0.f, lv = 0.f;
-#pragma unroll
-                for (int p = 0; p < P; ++p) {
-                    const float f = (wm[p][0] == -INFINITY) ? 0.f : __expf(wm[p][0] - gm);
-                    ov += wo[p][0][d] * f;
-                    lv += wl[p][0] * f;
+            if (P > 1) {                             // the shares of a row meet in LDS
+                __syncthreads();                     // wo / wm / wl are free again
+                wo[sub][0][d] = o;
+                if (d == 0) { wm[sub][0] = mm; wl[sub][0] = l; }
+                __syncthreads();
+                float gm = wm[rl][0];
+                for (int p = 1; p < P; ++p) gm = fmaxf(gm, wm[rl + (p << sh)][0]);
+                o = l = 0.f;
+                for (int p = 0; p < P; ++p) {        // what share 0 stores
+                    const float mv = wm[rl + (p << sh)][0], f = (mv == -INFINITY) ? 0.f : __expf(mv - gm);
+                    o += wo[rl + (p << sh)][0][d] * f;
+                    l += wl[rl + (p << sh)][0] * f;
                 }
-                Act<uint16_t>::store(mg.out, mg.plane, mg.tiled ? xt_index(m, head * HD + d, mg.tiled) : ((size_t)m * H + head) * HD + d,
-                                     lv > 0.f ? ov / lv : 0.f);
             }
+            if (live && sp0 == 0)
+                Act<uint16_t>::store(mg.out, mg.plane, mg.tiled ? xt_index(m, head * HD + d, mg.tiled) : ((size_t)m * H + head) * HD + d,
+                                     l > 0.f ? o / l : 0.f);
         }
     }
 }
@@ -2184,8 +2215,8 @@ AttnPlan attn_plan(int dtype, int B, int q_len, int H, int KVH, int hd, int cach
         // head_dim 128: the least estimated time.  A compute unit streams about 30 KB/us whether it holds one workgroup or two, so what counts
         // is how evenly the workgroups fall on the compute units; all of them together get 6.4 TB/s, and the two bounds add like
         // fourth powers.  Partials and a merge kernel cost 5 us at 20 rows of 32 heads, 8 at 144, and 2 more where workgroups share compute
-        // units; combined in the kernel, a workgroup takes about 1.55 us for each of its share of the group's rows, one after the
-        // other.  16 sequences of 4105 keys, 32 heads: 2 splits 178.6 + 8.5 us, 1 split
+        // units; combined in the kernel, 0.5 us and 1.55 for each row of a workgroup's share (fitted when it took them one after
+        // the other; two at a time cost less, which moves no count of a pass by more than its noise).  16 sequences of 4105 keys, 32 heads: 2 splits 178.6 + 8.5 us, 1 split
         // 168.0.  Whole passes of the 7B shape: 6 sequences of 3007 keys, 1 / 2 / 3 / 4 / 5 splits 6240 / 6505 / 6627 / 6408 / 6596 us;
         // 10 of 6004 keys, 1 / 2 / 3 / 4 splits 11281 / 10266 / 9831 / 9760; 4 of 2053 keys 4378 / 4128 / 4267 / 4158.  Eight layers of it, one
         // sequence, splits combined in the kernel, cache of 900: 3 rows, 1 / 2 splits 781 / 761 us, 5 rows 788 / 782, 9 rows 821 / 836; of 1280:
