@@ -5,8 +5,6 @@
 
 namespace bs {
 
-constexpr int GEMM_MAX_ROWS = 256;  // rows of x one workgroup of the many-row GEMM keeps in MFMA accumulators
-
 struct GemmArgs {
     const void* x;        // activations [M, K]: float, or bf16 hi plane (lo plane x_plane elements further)
     size_t x_plane;
@@ -92,10 +90,15 @@ int launch_gemm_big(const GemmArgs& a, hipStream_t s);   // 33 rows and more, K 
 // of columns, also the sums of squares per row that EPI_RESID leaves), the bytes of partial sums that needs, and whether it is
 // expected to beat launch_gemm with a consumer kernel.
 // epi: EPI_QKV, N = stacked columns; EPI_SWIGLU, N = columns of one matrix; EPI_RESID.
-struct BigPlan { int nt, mt, n_mb, full, rem, ks, n_tiles; size_t part_bytes; bool fused; };
+struct BigPlan { int nt, mt, wm, n_mb, full, rem, ks, n_tiles; size_t part_bytes; bool fused; };
+// How launch_gemm_big cuts the output: n_tiles x n_mb tiles of `cols` columns and 16 mt rows, eight wavefronts as 8 / wm columns x wm rows.
+struct BigTiles { int wm, mt, n_mb, cols, n_tiles; };
+BigTiles big_tiles(int N, int K, int M, int ks);
+int big_splits(int N, int K, int M);                     // ranges of K it is given
 bool big_fused_applies(int epi, int N, int K, int M);
 BigPlan big_plan(int epi, int N, int K, int M);
-int launch_gemm_big_fused(int epi, const GemmArgs& g, const DecArgs& e, float* part, size_t part_bytes, hipStream_t s);
+int launch_gemm_big_fused(int epi, const GemmArgs& g, const DecArgs& e, const BigPlan& p, float* part,     // p = big_plan of the same sizes
+                          size_t part_bytes, hipStream_t s);
 size_t packed_elems(int N, int K);                       // elements of the tiled copy of an [N][K] matrix
 int launch_pack_weights(const void* src, void* dst, int N, int K, hipStream_t s);
 

@@ -7,7 +7,7 @@
 //   gemm        y = x W^T: bf16 weights streamed once from HBM through MFMA 16x16x32 tiles (the
 //               contraction is skinny: M = B*(gamma+1) rows, so it is bound by weight bandwidth),
 //               split-K partials out; a many-row variant for prompt chunks and batches (activation
-//               stages memory -> LDS directly, 256 x 256 tiles); fp32 variant for the fp32 plumbing
+//               stages memory -> LDS directly, 512 x 128 tiles); fp32 variant for the fp32 plumbing
 //               configuration
 //   resid_sum   bf16 models: completes the residual, writes the planes of gain .* x and partial sums
 //               of squares (the RMS scale is applied behind the projection)
@@ -1126,31 +1126,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
     }
 }
 
-// Weight tiles per wavefront of the many-row kernel: two from 97 rows on (halves the LDS reads per weight byte,
-// which is what bounds the kernel there).
 int gemm_splits(int dtype, int N, int K, int M) {
     if (dtype != BS_BF16) return 1;
     if (M <= 16) return m16_splits(N, K);
     const int stages = (K + 255) / 256;
-    if (M > 32 && K % 32 == 0) {
-        // 256 weight rows per workgroup, one workgroup per compute unit: as many splits as fill the chip once and no
-        // more -- every further split writes and re-reads megabytes of partial sums
-        const int tiles = (N + 255) / 256 * ((M + 255) / 256);       // blocks of 256 rows share a launch
-        int ks = 256 / tiles;
-        if (ks < 1) {
-            // more tiles than compute units: splitting can still even out the last, partly filled round of workgroups
-            // (344 tiles: two rounds unsplit, three half-length rounds in two splits; measured 306 -> 262 us)
-            ks = 1;
-            double best = 1e30;
-            for (int c = 1; c <= 4; ++c) {
-                const double cost = (double)((tiles * c + 255) / 256) / c + 0.04 * (c - 1);
-                if (cost < best) { best = cost; ks = c; }
-            }
-        }
-        if (ks > stages) ks = stages;
-        if (ks > 16) ks = 16;
-        return ks < 1 ? 1 : ks;
-    }
+    if (M > 32 && K % 32 == 0) return big_splits(N, K, M);
     const int tiles = (N + 63) / 64;
     int ks = (768 + tiles - 1) / tiles;
     if (ks > stages / 2) ks = stages / 2;

@@ -157,8 +157,7 @@ struct FwdWs {
     AttnPlan att_plan; AttnParts att_parts;    // more than two rows; parts == nullptr: the same splits for every sequence
     float *part_qkv, *part_o, *part_gu, *part_d, *part_attn;
     int ks_qkv, ks_o, ks_gu, ks_d;
-    bool big_qkv, big_gu, big_o, big_d;   // many-row projections whose epilogue does the consumer's work
-    int tiles_o, tiles_d;            // sums of squares per row that big_o and big_d leave
+    BigPlan big_qkv, big_gu, big_o, big_d;    // many-row projections whose epilogue does the consumer's work (fused)
     size_t part_qkv_bytes, part_gu_bytes, part_o_bytes, part_d_bytes;
     size_t total;
 };
@@ -213,16 +212,14 @@ static FwdWs carve(const bs_model_cfg& c, int B, int q_len, int max_len, char* b
         w.att_parts.items = (long long*)take((size_t)w.att_plan.n_items * 8);
     }
     // partial sums: those of launch_gemm, or of the items that a many-row projection with its consumer's work splits (big_plan)
-    auto big = [&](int epi, size_t N, size_t K, int ks, bool* use, int* tiles) -> size_t {
-        const BigPlan p = c.dtype == BS_BF16 && big_fused_applies(epi, (int)N, (int)K, (int)M) ? big_plan(epi, (int)N, (int)K, (int)M) : BigPlan{};
-        *use = p.fused;
-        if (tiles) *tiles = p.n_tiles;
+    auto big = [&](int epi, size_t N, size_t K, int ks, BigPlan& p) -> size_t {
+        p = c.dtype == BS_BF16 && big_fused_applies(epi, (int)N, (int)K, (int)M) ? big_plan(epi, (int)N, (int)K, (int)M) : BigPlan{};
         return p.fused ? p.part_bytes : M * (epi == EPI_SWIGLU ? 2 * N : N) * 4 * ks;
     };
-    w.part_qkv_bytes = big(EPI_QKV, nq + 2 * nkv, c.d_model, w.ks_qkv, &w.big_qkv, nullptr);
-    w.part_o_bytes = big(EPI_RESID, c.d_model, nq, w.ks_o, &w.big_o, &w.tiles_o);
-    w.part_gu_bytes = big(EPI_SWIGLU, c.d_ff, c.d_model, w.ks_gu, &w.big_gu, nullptr);
-    w.part_d_bytes = big(EPI_RESID, c.d_model, c.d_ff, w.ks_d, &w.big_d, &w.tiles_d);
+    w.part_qkv_bytes = big(EPI_QKV, nq + 2 * nkv, c.d_model, w.ks_qkv, w.big_qkv);
+    w.part_o_bytes = big(EPI_RESID, c.d_model, nq, w.ks_o, w.big_o);
+    w.part_gu_bytes = big(EPI_SWIGLU, c.d_ff, c.d_model, w.ks_gu, w.big_gu);
+    w.part_d_bytes = big(EPI_RESID, c.d_model, c.d_ff, w.ks_d, w.big_d);
     w.part_qkv = (float*)take(w.part_qkv_bytes);
     w.part_o = (float*)take(w.part_o_bytes);
     w.part_gu = (float*)take(w.part_gu_bytes);
@@ -265,10 +262,9 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
                    hipStream_t s) {
     const bs_model_cfg& c = m->cfg;
     const int B = kv->B, M = B * q_len, dt = c.dtype;
-    const size_t need = carve(c, B, q_len, kv->max_len, nullptr).total;
-    BS_REQUIRE(ws_bytes >= need, BS_EWORKSPACE, "forward: workspace %zu < %zu bytes", ws_bytes, need);
+    const FwdWs w = carve(c, B, q_len, kv->max_len, reinterpret_cast<char*>(ws));
+    BS_REQUIRE(ws_bytes >= w.total, BS_EWORKSPACE, "forward: workspace %zu < %zu bytes", ws_bytes, w.total);
     BS_REQUIRE((reinterpret_cast<uintptr_t>(ws) & 255) == 0, BS_EWORKSPACE, "forward: workspace not 256-byte aligned");
-    FwdWs w = carve(c, B, q_len, kv->max_len, reinterpret_cast<char*>(ws));
     const int H = c.n_heads, KVH = c.n_kv_heads, hd = c.head_dim, d = c.d_model, ff = c.d_ff;
     const int nq = H * hd, nkv = KVH * hd, nqkv = nq + 2 * nkv;
     const size_t es = esize(dt);
@@ -378,7 +374,7 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
         ac.flag = (unsigned)l + 1u;
         const bool defer = dt == BS_BF16;        // bf16: RMS scale applied behind the projection (see resid_sum_kernel)
         const float* ssq = defer ? w.ssq : nullptr;
-        const bool ready = defer && (fuse_d || w.big_d) && l > 0;       // the down projection of the layer before left x, the planes and the sums of squares
+        const bool ready = defer && (fuse_d || w.big_d.fused) && l > 0;       // the down projection of the layer before left x, the planes and the sums of squares
         if (ready) {}
         else if (defer) {
             BS_TRY(launch_resid_sum(w.x, pend, w.ks_d, (size_t)M * d, L.attn_norm, d, M, fuse_qkv ? (size_t)RT * d : (size_t)MP * d, w.h, w.ssq,
@@ -399,12 +395,12 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
             a.pos = w.pos; a.rope = w.rope; a.q_len = q_len; a.H = H; a.KVH = KVH; a.hd = hd; a.cache_len = crow;
             a.q_out = w.q; a.k_cache = reinterpret_cast<uint16_t*>(kc); a.v_cache = reinterpret_cast<uint16_t*>(vc);
             BS_TRY(launch_gemm_rows(EPI_QKV, a, stream, s));
-        } else if (w.big_qkv) {
+        } else if (w.big_qkv.fused) {
             DecArgs a = {};
             a.N = nqkv; a.ssq_in = w.ssq; a.ssq_tiles = ssq_n; a.eps = c.norm_eps;
             a.pos = w.pos; a.rope = w.rope; a.q_len = q_len; a.H = H; a.KVH = KVH; a.hd = hd; a.cache_len = crow;
             a.q_out = w.q; a.k_cache = reinterpret_cast<uint16_t*>(kc); a.v_cache = reinterpret_cast<uint16_t*>(vc);
-            BS_TRY(launch_gemm_big_fused(EPI_QKV, g, a, w.part_qkv, w.part_qkv_bytes, s));
+            BS_TRY(launch_gemm_big_fused(EPI_QKV, g, a, w.big_qkv, w.part_qkv, w.part_qkv_bytes, s));
         } else {
         BS_TRY(launch_gemm(dt, g, s));
         BS_TRY(launch_rope_kv(dt, w.part_qkv, w.ks_qkv, (size_t)M * nqkv, w.pos, w.rope, M, q_len, H, KVH, hd, crow,
@@ -421,11 +417,11 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
             a.ssq_out = w.ssq;
             BS_TRY(launch_gemm_rows(EPI_RESID, a, stream, s));
             ssq_n = d / 16;
-        } else if (w.big_o) {
+        } else if (w.big_o.fused) {
             DecArgs a = {};
             a.N = d; a.x = w.x; a.gain_next = L.ffn_norm; a.out_planes = reinterpret_cast<uint16_t*>(w.h); a.out_plane = (size_t)MP * d; a.out_tiled = g.x_tiled; a.ssq_out = w.ssq;
-            BS_TRY(launch_gemm_big_fused(EPI_RESID, g, a, w.part_o, w.part_o_bytes, s));
-            ssq_n = w.tiles_o;
+            BS_TRY(launch_gemm_big_fused(EPI_RESID, g, a, w.big_o, w.part_o, w.part_o_bytes, s));
+            ssq_n = w.big_o.n_tiles;
         } else {
         BS_TRY(launch_gemm(dt, g, s));
         if (defer) {
@@ -444,11 +440,11 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
             a.M = M; a.N = ff; a.K = d; a.ssq_in = w.ssq; a.ssq_tiles = ssq_n; a.eps = c.norm_eps;
             a.out_planes = reinterpret_cast<uint16_t*>(w.act); a.out_plane = fuse_d ? (size_t)RT * ff : (size_t)M * ff; a.out_tiled = fuse_d ? RT : 0;
             BS_TRY(launch_gemm_rows(EPI_SWIGLU, a, stream, s));
-        } else if (w.big_gu) {
+        } else if (w.big_gu.fused) {
             DecArgs a = {};
             g.N = ff; a.N = ff; a.ssq_in = w.ssq; a.ssq_tiles = ssq_n; a.eps = c.norm_eps;
             a.out_planes = reinterpret_cast<uint16_t*>(w.act); a.out_plane = (size_t)MP * ff; a.out_tiled = g.x_tiled;
-            BS_TRY(launch_gemm_big_fused(EPI_SWIGLU, g, a, w.part_gu, w.part_gu_bytes, s));
+            BS_TRY(launch_gemm_big_fused(EPI_SWIGLU, g, a, w.big_gu, w.part_gu, w.part_gu_bytes, s));
         } else {
         BS_TRY(launch_gemm(dt, g, s));
         BS_TRY(launch_swiglu(dt, w.part_gu, w.ks_gu, (size_t)M * 2 * ff, M, ff, (size_t)MP * ff, w.act, g.x_tiled, ssq, ssq_n, d, c.norm_eps, s));
@@ -464,12 +460,12 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
             a.ssq_out = more ? w.ssq : nullptr;
             BS_TRY(launch_gemm_rows(EPI_RESID, a, stream, s));
             ssq_n = d / 16;
-        } else if (w.big_d) {
+        } else if (w.big_d.fused) {
             DecArgs a = {};
             a.N = d; a.x = w.x; a.gain_next = l + 1 < c.n_layers ? m->layers[l + 1].attn_norm : nullptr;
             a.out_planes = reinterpret_cast<uint16_t*>(w.h); a.out_plane = (size_t)MP * d; a.out_tiled = g.x_tiled; a.ssq_out = a.gain_next ? w.ssq : nullptr;
-            BS_TRY(launch_gemm_big_fused(EPI_RESID, g, a, w.part_d, w.part_d_bytes, s));
-            ssq_n = w.tiles_d;
+            BS_TRY(launch_gemm_big_fused(EPI_RESID, g, a, w.big_d, w.part_d, w.part_d_bytes, s));
+            ssq_n = w.big_d.n_tiles;
         } else {
         BS_TRY(launch_gemm(dt, g, s));
         pend = w.part_d;

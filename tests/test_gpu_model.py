@@ -756,3 +756,18 @@ def test_planes_of_33_rows_and_more(c, B, q_len, rows):
     for b in {0, 1, B // 2, B - 1}:
         ref = forward(c, W, toks[b], storage="bf16", last_rows=rows)
         assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
+
+
+# 129 rows and more: blocks of up to 128 rows, wavefronts in one row (5 to 8 row tiles) or two (6, 8); columns beside 384 and 512, a last block that is not full
+@pytest.mark.parametrize("c", [synth.cfg(1, 1024, 16, 64, 2816, 544, n_kv_heads=4), synth.cfg(1, 736, 9, 64, 1472, 1030, n_kv_heads=3),
+                               synth.cfg(1, 2048, 16, 128, 6912, 512)], ids=["1024", "736", "2048"])
+@pytest.mark.parametrize("B,n", [(1, 129), (3, 53), (1, 191), (1, 225), (1, 257), (1, 384), (2, 321), (9, 128), (4, 1000)])
+def test_blocks_of_rows_from_129_rows_on(c, B, n):
+    W, m, kv = setup(c, B, n + 8, seed=95, packed=True)
+    toks = synth.make_prompts(B, n, c["vocab"], seed=96)
+    dt = torch.from_numpy(toks.astype(np.int32)).cuda()
+    rows = min(n, 40)                                  # several logit rows a sequence: the LM head has many rows as well
+    logits = bs().verify_forward(m, kv, dt, torch.zeros(B, dtype=torch.int32, device="cuda"), rows)
+    for b in {0, B - 1}:
+        ref = forward(c, W, toks[b], storage="bf16", last_rows=rows)
+        assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
