@@ -122,6 +122,20 @@ int launch_resid_sum(float* x, const float* pend, int pend_ks, size_t pend_strid
                      size_t plane, void* out, float* ssq, int tiled, hipStream_t s);
 int launch_swiglu(int dtype, const float* part, int ks, size_t ks_stride, int M, int ff, size_t plane, void* out, int tiled,
                   const float* ssq, int ssq_n, int d, float eps, hipStream_t s);
+// fp32 projections with the work around them (f32_fused_kernel), for passes where f32_fused_applies
+enum { F32_QKV, F32_SWIGLU, F32_RESID, F32_HEAD };
+struct F32Args {
+    const float* x; const int32_t* tok;       // input rows [.][K]: row m, or where tok is given (QKV) row tok[m] of the embedding
+    const float* gain; float eps;             // RMSNorm of the input rows (not RESID)
+    const float* w[3];                        // [N][K]; QKV: q, k, v; SWIGLU: gate, up
+    float* out;                               // QKV: q [M][nq]; SWIGLU: [M][N]; RESID: x [M][N], added to (tok: to rows tok[m] of x_old); HEAD: row stride ldo
+    const float* x_old;
+    int M, N, K, ldo, rows_in, rows_out;      // HEAD: the last rows_out of every rows_in input rows
+    const int32_t* pos; const float2* rope; int q_len, nq, nkv, hd, cache_len;      // QKV
+    float* k_cache; float* v_cache;
+};
+bool f32_fused_applies(int M, int d, int ff);
+int launch_f32_fused(int epi, const F32Args& a, hipStream_t s);
 int launch_rope_kv(int dtype, const float* part, int ks, size_t ks_stride, const int32_t* pos, const float2* rope, int M,
                    int q_len, int H, int KVH, int hd, int max_len, float* q_out, void* k_cache, void* v_cache,
                    const float* ssq, int ssq_n, int d, float eps, hipStream_t s);

@@ -1301,16 +1301,120 @@ __global__ void rope_kv_kernel(const float* __restrict__ part, int ks, size_t ks
     }
 }
 
+// ---- fp32 projections with the work around them -----------------------------------------------------------
+// A pass of a small fp32 model is launches: of a layer's nine, four moved a few KB (norm, RoPE + cache write, norm, SwiGLU) and took 2 to 3 us
+// each.  Here a wavefront has two columns (a rotation pair; gate and up of a column) under four rows, sums the rows' squares beside the
+// products (RMSNorm is linear: r (g .* x) W^T, r per row) and finishes them: RMS scale + RoPE + q + cache write (QKV), silu(r g) r u
+// (SWIGLU), x += y (RESID), the logits (HEAD: N rows of the LM head, RMS scale).  The first layer reads the embedding's rows itself, and the first
+// RESID leaves x.  A layer is five launches instead of nine, a pass two more instead of four: a round of four steps of a draft of 64 columns and one layer and
+// a target of 128 and two, batch 4, 321 -> 246 us (23 of them by attn_kernel).
+// The twelve sums of a wavefront (two products and the squares of four rows) are halved in number at each of the first four steps of their
+// reduction: 17 exchanges instead of 72.  Sum i ends in lanes 4 i .. 4 i + 3.
+template <int N>
+__device__ __forceinline__ void halve_sums(float (&v)[16], int lane) {
+    const bool up = lane & (4 * N);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const float keep = up ? v[i + N] : v[i], give = up ? v[i] : v[i + N];
+        v[i] = keep + __shfl_xor(give, 4 * N, 64);
+    }
+}
+__device__ __forceinline__ float reduce16(float (&v)[16]) {
+    const int lane = threadIdx.x & 63;
+    halve_sums<8>(v, lane); halve_sums<4>(v, lane); halve_sums<2>(v, lane); halve_sums<1>(v, lane);
+    float t = v[0];
+    t += __shfl_xor(t, 2, 64);
+    return t + __shfl_xor(t, 1, 64);
+}
+template <int EPI, bool VEC>
+__global__ __launch_bounds__(256) void f32_fused_kernel(F32Args a) {
+    const int lane = threadIdx.x & 63, p = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int c = EPI == F32_SWIGLU ? p : 2 * p;                   // this wavefront's output column, or the first of two
+    if (c >= a.N) return;
+    const float *w0, *w1;
+    if (EPI == F32_SWIGLU) {
+        w0 = a.w[0] + (size_t)c * a.K; w1 = a.w[1] + (size_t)c * a.K;
+    } else {
+        int seg = 0, local = c;                                    // segments are of even length
+        if (EPI == F32_QKV && local >= a.nq) { local -= a.nq; seg = 1; if (local >= a.nkv) { local -= a.nkv; seg = 2; } }
+        w0 = a.w[seg] + (size_t)local * a.K; w1 = c + 1 < a.N ? w0 + a.K : w0;
+    }
+    for (int m0 = blockIdx.y * 4; m0 < a.M; m0 += gridDim.y * 4) { // one turn unless the rows exceed the grid's limit
+        const float* xr[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = min(m0 + r, a.M - 1);
+            const int src = EPI == F32_HEAD ? (m / a.rows_out) * a.rows_in + (a.rows_in - a.rows_out) + m % a.rows_out : m;
+            xr[r] = a.x + (size_t)(EPI != F32_RESID && a.tok ? a.tok[src] : src) * a.K;
+        }
+        // what the epilogue needs: lane 4 r finishes row r
+        const int m = min(m0 + ((lane >> 2) & 3), a.M - 1);
+        int pos = -1;
+        float2 cs = make_float2(1.f, 0.f), old = make_float2(0.f, 0.f);
+        if (EPI == F32_QKV) {
+            pos = a.pos[m];
+            if (c < a.nq + a.nkv) cs = a.rope[(size_t)m * (a.hd / 2) + c % a.hd / 2];
+        }
+        if (EPI == F32_RESID) old = *reinterpret_cast<const float2*>(a.tok ? a.x_old + (size_t)a.tok[m] * a.N + c : a.out + (size_t)m * a.N + c);     // N is even
+        float v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = 0.f;
+        for (int k = lane * 4; k < a.K; k += 256) {                // K % 8 == 0 (host check)
+            float4 u0 = VEC ? *reinterpret_cast<const float4*>(w0 + k) : make_float4(w0[k], w0[k + 1], w0[k + 2], w0[k + 3]);
+            float4 u1 = VEC ? *reinterpret_cast<const float4*>(w1 + k) : make_float4(w1[k], w1[k + 1], w1[k + 2], w1[k + 3]);
+            float4 xv[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) xv[r] = *reinterpret_cast<const float4*>(xr[r] + k);
+            if (EPI != F32_RESID) {
+                const float4 g = *reinterpret_cast<const float4*>(a.gain + k);
+                u0 = make_float4(u0.x * g.x, u0.y * g.y, u0.z * g.z, u0.w * g.w);
+                u1 = make_float4(u1.x * g.x, u1.y * g.y, u1.z * g.z, u1.w * g.w);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                v[r] = fmaf(xv[r].w, u0.w, fmaf(xv[r].z, u0.z, fmaf(xv[r].y, u0.y, fmaf(xv[r].x, u0.x, v[r]))));
+                v[4 + r] = fmaf(xv[r].w, u1.w, fmaf(xv[r].z, u1.z, fmaf(xv[r].y, u1.y, fmaf(xv[r].x, u1.x, v[4 + r]))));
+                if (EPI != F32_RESID) v[8 + r] = fmaf(xv[r].w, xv[r].w, fmaf(xv[r].z, xv[r].z, fmaf(xv[r].y, xv[r].y, fmaf(xv[r].x, xv[r].x, v[8 + r]))));
+            }
+        }
+        const float t = reduce16(v);
+        float y0 = t, y1 = __shfl(t, (lane & 15) + 16, 64);
+        if (EPI != F32_RESID) {
+            const float rs = 1.0f / sqrtf(__shfl(t, (lane & 15) + 32, 64) / (float)a.K + a.eps);
+            y0 *= rs; y1 *= rs;
+        }
+        if (lane >= 16 || (lane & 3) || m0 + (lane >> 2) >= a.M) continue;
+        if (EPI == F32_SWIGLU) a.out[(size_t)m * a.N + c] = y0 / (1.0f + __expf(-y0)) * y1;
+        if (EPI == F32_RESID) *reinterpret_cast<float2*>(a.out + (size_t)m * a.N + c) = make_float2(old.x + y0, old.y + y1);
+        if (EPI == F32_HEAD) {
+            float* o = a.out + (size_t)m * a.ldo + c;
+            o[0] = y0;
+            if (c + 1 < a.N) o[1] = y1;
+        }
+        if (EPI == F32_QKV) {
+            const float2 rot = make_float2(y0 * cs.x - y1 * cs.y, y0 * cs.y + y1 * cs.x);
+            const int b = m / a.q_len, d = c % a.hd;
+            if (c < a.nq) *reinterpret_cast<float2*>(a.out + (size_t)m * a.nq + c) = rot;
+            else if (pos >= 0) {
+                const bool key = c < a.nq + a.nkv;
+                const int head = (c - a.nq - (key ? 0 : a.nkv)) / a.hd;
+                float* dst = (key ? a.k_cache : a.v_cache) + (((size_t)b * (a.nkv / a.hd) + head) * a.cache_len + pos) * a.hd + d;
+                *reinterpret_cast<float2*>(dst) = key ? rot : make_float2(y0, y1);
+            }
+        }
+    }
+}
+
 // ---- attention -------------------------------------------------------------------------------------
 // grid (n_splits x row groups, H, B), 256 lanes.  The keys 0..n_keys-1 (n_keys = pos of the last query row + 1) are cut
-// into n_splits chunks of whole 64-key tiles; the 4 wavefronts of a workgroup take the tiles of their
+// into n_splits chunks of whole 64-key tiles; the 4 wavefronts of a workgroup take 16, 32 or 64 keys of their
 // chunk in turn.  Score phase: lane = key.  Value phase: lane = head-dim element (d and d+64).
 // A workgroup takes ATT_RB query rows (the shuffles of nine rows at a time were most of what a launch over a short cache does,
-// and a prompt chunk's rows ran one group after the other in one workgroup), keys of the value phase ATT_VB at a time, all their
-// loads in flight.  Writes un-normalised partials (m, l, o[hd]) per split, or the output itself where there is one split.  One
-// row / 5 rows against 50 keys: 16.5 us each before, now 8.6 / 8.9.
+// and a prompt chunk's rows ran one group after the other in one workgroup); the keys and values of a turn are in flight before the queries
+// are there.  Writes un-normalised partials (m, l, o[hd]) per split, or the output itself where there is one split.  One
+// row / 5 rows against 50 keys: 8.9 / 9.1 us each with a wavefront's 64 keys at a time and loads where they are used, 5.0 / 5.5 like this.
 constexpr int ATT_RB = 2;
-constexpr int ATT_VB = 32;
+constexpr int ATT_VF = 16;
 
 template <typename T>
 __device__ __forceinline__ void load8(const T* p, float out[8]);
@@ -1328,7 +1432,9 @@ __device__ __forceinline__ void load8<uint16_t>(const uint16_t* p, float out[8])
     out[6] = __uint_as_float(a.w << 16); out[7] = __uint_as_float(a.w & 0xFFFF0000u);
 }
 
-template <typename T>
+// SHORT, for caches of up to 512 keys: the longer ones' workgroups are many and each has many turns, what counts there is how many fit a
+// compute unit (20 rows of 8 heads of 32 at 5000 keys: a pass of two layers 121 us without, 163 with).
+template <typename T, bool SHORT>
 __global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, const T* __restrict__ k_cache,
                                                    const T* __restrict__ v_cache, const int32_t* __restrict__ pos,
                                                    int q_len, int H, int KVH, int hd, int max_len, float scale, int n_splits,
@@ -1360,6 +1466,24 @@ __global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, 
     const T* kb = k_cache + ((size_t)b * KVH + kvh) * (size_t)max_len * hd;
     const T* vb = v_cache + ((size_t)b * KVH + kvh) * (size_t)max_len * hd;
     const int d0 = lane, d1 = lane + 64;
+    // up to 64 keys are dealt to the four wavefronts 16 at a time, up to 128 in turns of 32
+    const int k_end = min(t_end * 64, n_keys), len = k_end - t_begin * 64, turn = SHORT && len <= 64 ? 16 : SHORT && len <= 128 ? 32 : 64;
+    // 32 dimensions of a turn's keys and, of up to 32 keys, the values of the first ATT_VF are asked for ahead of it
+    float kf[4][8], vf0[ATT_VF], vf1[ATT_VF];
+    auto ask = [&](int key0) {
+        const T* krow = kb + (size_t)min(key0 + lane, n_keys - 1) * hd;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) load8<T>(krow + min(8 * j, hd - 8), kf[j]);
+        if (turn == 64) return;                      // two trips of 32 values a turn
+#pragma unroll
+        for (int u = 0; u < ATT_VF; ++u) {
+            const int vk = min(key0 + u, n_keys - 1);
+            vf0[u] = to_f(vb[v_index<T>(vk, min(d0, hd - 1), hd)]);
+            vf1[u] = hd > 64 ? to_f(vb[v_index<T>(vk, min(d1, hd - 1), hd)]) : 0.f;
+        }
+    };
+    int key0 = t_begin * 64 + wave * turn;
+    if (SHORT) ask(key0);
 
     {
         const int r0 = rg * ATT_RB, nr = min(ATT_RB, q_len - r0);
@@ -1372,9 +1496,9 @@ __global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, 
 #pragma unroll
         for (int r = 0; r < ATT_RB; ++r) { mrow[r] = -INFINITY; lrow[r] = 0.f; o0[r] = 0.f; o1[r] = 0.f; }
 
-        for (int t = t_begin + wave; t < t_end; t += 4) {
-            const int key = t * 64 + lane;
-            const bool kvalid = key < n_keys;
+        for (; key0 < k_end; key0 += 4 * turn) {
+            const int key = key0 + lane;
+            const bool kvalid = lane < turn && key < k_end;
             // ---- scores: lane = key ----
             float s[ATT_RB];
 #pragma unroll
@@ -1384,7 +1508,12 @@ __global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, 
                 for (int dd = 0; dd < hd; dd += 32) {                           // 32 dimensions asked for together
                     float kv[4][8];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) load8<T>(krow + min(dd + 8 * j, hd - 8), kv[j]);
+                    for (int j = 0; j < 4; ++j) {
+                        if (!SHORT || dd > 0) load8<T>(krow + min(dd + 8 * j, hd - 8), kv[j]);
+                        else
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) kv[j][e] = kf[j][e];
+                    }
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const int d = dd + 8 * j;
@@ -1414,17 +1543,10 @@ __global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, 
             // ---- values: lane = head-dim element ----
 #pragma unroll
             for (int r = 0; r < ATT_RB; ++r) { o0[r] *= alpha[r]; o1[r] *= alpha[r]; }
-            const int kmax = min(64, n_keys - t * 64);
-            for (int k0 = 0; k0 < kmax; k0 += ATT_VB) {                             // ATT_VB keys asked for together
-                float v0[ATT_VB], v1[ATT_VB];
+            const int kmax = min(turn, k_end - key0);
+            auto add = [&](int k0, float (&v0)[ATT_VF], float (&v1)[ATT_VF]) {
 #pragma unroll
-                for (int u = 0; u < ATT_VB; ++u) {
-                    const int vk = t * 64 + min(k0 + u, kmax - 1);
-                    v0[u] = to_f(vb[v_index<T>(vk, min(d0, hd - 1), hd)]);
-                    v1[u] = hd > 64 ? to_f(vb[v_index<T>(vk, min(d1, hd - 1), hd)]) : 0.f;
-                }
-#pragma unroll
-                for (int u = 0; u < ATT_VB; u += 4) {
+                for (int u = 0; u < ATT_VF; u += 4) {
 #pragma unroll
                     for (int e = u; e < u + 4; ++e)
                         if (k0 + e >= kmax) { v0[e] = 0.f; v1[e] = 0.f; }       // keys past the end: their probability is zero too
@@ -1435,7 +1557,22 @@ __global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, 
                         o1[r] += pp.x * v1[u] + pp.y * v1[u + 1] + pp.z * v1[u + 2] + pp.w * v1[u + 3];
                     }
                 }
+            };
+            if (SHORT && turn < 64) add(0, vf0, vf1);
+            for (int k0 = SHORT && turn < 64 ? ATT_VF : 0; k0 < kmax; k0 += 2 * ATT_VF) {    // the others 2 ATT_VF at a time
+                float v0[2][ATT_VF], v1[2][ATT_VF];
+#pragma unroll
+                for (int x = 0; x < 2; ++x)
+#pragma unroll
+                    for (int u = 0; u < ATT_VF; ++u) {
+                        const int vk = key0 + min(k0 + x * ATT_VF + u, kmax - 1);
+                        v0[x][u] = to_f(vb[v_index<T>(vk, min(d0, hd - 1), hd)]);
+                        v1[x][u] = hd > 64 ? to_f(vb[v_index<T>(vk, min(d1, hd - 1), hd)]) : 0.f;
+                    }
+                add(k0, v0[0], v1[0]);
+                if (k0 + ATT_VF < 64) add(k0 + ATT_VF, v0[1], v1[1]);
             }
+            if (SHORT && key0 + 4 * turn < k_end) ask(key0 + 4 * turn);
         }
         // ---- combine the 4 wavefronts ----
 #pragma unroll
@@ -2142,6 +2279,30 @@ int launch_rope_kv(int dtype, const float* part, int ks, size_t ks_stride, const
     return BS_OK;
 }
 
+// The fused fp32 projections read the weights once per four rows.  Against a kernel per step: 128 to 1536 columns, 1 to 1024 rows a pass 1.1 to 1.5
+// times as fast, 2048 columns 1.2 (4 rows) to 1.04 (1024 rows), 4096 columns 1.27 up to 40 rows; from 48 rows on gemm_f32_kernel's groups of
+// eight beat them there (48 rows 1551 us against 1752, 1024 rows 28.5 against 36.2 ms), whose feed-forward matrices are 180 MB each.
+bool f32_fused_applies(int M, int d, int ff) { return M < 48 || (size_t)d * ff <= 12000000; }
+
+int launch_f32_fused(int epi, const F32Args& a, hipStream_t s) {
+    if (a.M <= 0 || a.N <= 0) return BS_OK;
+    BS_REQUIRE(a.x && a.w[0] && a.out && a.K % 8 == 0 && (epi == F32_HEAD || a.N % 2 == 0) && (epi == F32_RESID || a.gain), BS_EINVAL, "f32_fused: M=%d N=%d K=%d", a.M, a.N, a.K);
+    BS_REQUIRE(epi != F32_QKV || (a.w[1] && a.w[2] && a.pos && a.rope && a.k_cache && a.v_cache && a.nq + 2 * a.nkv == a.N && a.hd >= 2 && a.q_len >= 1), BS_EINVAL, "f32_fused: QKV arguments");
+    BS_REQUIRE(epi != F32_SWIGLU || a.w[1], BS_EINVAL, "f32_fused: up matrix missing");
+    BS_REQUIRE(epi != F32_RESID || !a.tok || a.x_old, BS_EINVAL, "f32_fused: residual rows missing");
+    const int pairs = epi == F32_SWIGLU ? a.N : (a.N + 1) / 2, groups = (a.M + 3) / 4;
+    const dim3 grid((pairs + 3) / 4, groups < 65535 ? groups : 65535), block(256);
+    // a caller's LM head need not be 16-byte aligned (the layers' matrices and the activations are)
+    const bool vec = (reinterpret_cast<uintptr_t>(a.w[0]) & 15) == 0;
+    if (epi == F32_QKV) hipLaunchKernelGGL((f32_fused_kernel<F32_QKV, true>), grid, block, 0, s, a);
+    else if (epi == F32_SWIGLU) hipLaunchKernelGGL((f32_fused_kernel<F32_SWIGLU, true>), grid, block, 0, s, a);
+    else if (epi == F32_RESID) hipLaunchKernelGGL((f32_fused_kernel<F32_RESID, true>), grid, block, 0, s, a);
+    else if (vec) hipLaunchKernelGGL((f32_fused_kernel<F32_HEAD, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((f32_fused_kernel<F32_HEAD, false>), grid, block, 0, s, a);
+    BS_LAUNCH_CHECK();
+    return BS_OK;
+}
+
 // bytes of the exchange cells through which the key splits of `rows` query rows are combined inside the attention kernel
 size_t attn_cells_bytes(int rows, int H, int hd, int n_splits) {
     const double b = (double)rows * H * n_splits * (hd + 4) * 8.0;
@@ -2285,7 +2446,9 @@ int launch_attention(int dtype, const float* q, const void* k_cache, const void*
         }
     } else {
         float* direct = n_splits == 1 ? reinterpret_cast<float*>(out) : nullptr;
-        hipLaunchKernelGGL((attn_kernel<float>), dim3(n_splits * ((q_len + ATT_RB - 1) / ATT_RB), H, B), block, 0, s, q, (const float*)k_cache,
+        if (max_len <= 512) hipLaunchKernelGGL((attn_kernel<float, true>), dim3(n_splits * ((q_len + ATT_RB - 1) / ATT_RB), H, B), block, 0, s, q, (const float*)k_cache,
+                           (const float*)v_cache, pos, q_len, H, KVH, hd, max_len, scale, n_splits, part, direct);
+        else hipLaunchKernelGGL((attn_kernel<float, false>), dim3(n_splits * ((q_len + ATT_RB - 1) / ATT_RB), H, B), block, 0, s, q, (const float*)k_cache,
                            (const float*)v_cache, pos, q_len, H, KVH, hd, max_len, scale, n_splits, part, direct);
         BS_LAUNCH_CHECK();
         if (n_splits > 1) hipLaunchKernelGGL((attn_merge_kernel<float, false>), dim3(B * q_len * H), dim3(hd), 0, s, part, n_splits, hd, plane, out, out_tiled ? H : 0, out_tiled, (const int32_t*)nullptr, 1);

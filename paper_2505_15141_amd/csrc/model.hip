@@ -305,6 +305,7 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
         BS_TRY(launch_step(a, s));
         return BS_OK;
     }
+    const bool f32_fused = dt == BS_F32 && f32_fused_applies(M, d, ff);
     if (few_rows) {
         const size_t pd = (size_t)M * d;
         uint16_t* hp = reinterpret_cast<uint16_t*>(w.h);
@@ -340,6 +341,47 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
             a.ssq_out = more ? w.ssq : nullptr;
             BS_TRY(launch_gemm_dec(EPI_RESID, a, s));
         }
+    } else if (f32_fused) {
+        // the embedding's rows are read where they are if they are aligned like everything else
+        const bool gather = (reinterpret_cast<uintptr_t>(m->embed) & 15) == 0;
+        const float* embed = reinterpret_cast<const float*>(m->embed);
+        if (!gather) BS_TRY(launch_embed(dt, w.tok, m->embed, M, d, w.x, s));
+        auto mat = [](const void* p) { return reinterpret_cast<const float*>(p); };
+        for (int l = 0; l < c.n_layers; ++l) {
+            const bs_layer_weights& L = m->layers[l];
+            char* kc = kv->buf + (size_t)l * kv_layer;
+            char* vc = kc + kv_layer / 2;
+            const bool first = gather && l == 0;
+            F32Args a = {};
+            a.M = M; a.eps = c.norm_eps;
+            a.x = first ? embed : w.x; a.tok = first ? w.tok : nullptr; a.gain = L.attn_norm; a.w[0] = mat(L.wq); a.w[1] = mat(L.wk); a.w[2] = mat(L.wv); a.N = nqkv; a.K = d;
+            a.out = w.q; a.pos = w.pos; a.rope = w.rope; a.q_len = q_len; a.nq = nq; a.nkv = nkv; a.hd = hd; a.cache_len = crow;
+            a.k_cache = reinterpret_cast<float*>(kc); a.v_cache = reinterpret_cast<float*>(vc);
+            BS_TRY(launch_f32_fused(F32_QKV, a, s));
+            BS_TRY(launch_attention(dt, w.q, kc, vc, w.pos, B, q_len, H, KVH, hd, crow, splits, w.part_attn, (size_t)M * nq, w.att, 0, nullptr, nullptr, false, s));
+            a.x = reinterpret_cast<const float*>(w.att); a.w[0] = mat(L.wo); a.N = d; a.K = nq; a.out = w.x; a.x_old = embed;
+            BS_TRY(launch_f32_fused(F32_RESID, a, s));
+            a.tok = nullptr;
+            a.x = w.x; a.gain = L.ffn_norm; a.w[0] = mat(L.w_gate); a.w[1] = mat(L.w_up); a.N = ff; a.K = d; a.out = reinterpret_cast<float*>(w.act);
+            BS_TRY(launch_f32_fused(F32_SWIGLU, a, s));
+            a.x = reinterpret_cast<const float*>(w.act); a.w[0] = mat(L.w_down); a.N = d; a.K = ff; a.out = w.x;
+            BS_TRY(launch_f32_fused(F32_RESID, a, s));
+        }
+        if (logit_rows > 0) {
+            F32Args a = {};
+            a.x = w.x; a.gain = m->final_norm; a.eps = c.norm_eps; a.w[0] = mat(m->lm_head); a.K = d; a.N = c.vocab; a.rows_in = q_len; a.rows_out = logit_rows; a.ldo = c.vocab;
+            if (logits_bstride == (size_t)logit_rows * c.vocab || logit_rows == 1) {
+                a.M = B * logit_rows; a.out = logits; a.ldo = logit_rows == 1 ? (int)logits_bstride : c.vocab;
+                BS_TRY(launch_f32_fused(F32_HEAD, a, s));
+            } else {
+                a.M = logit_rows;
+                for (int b = 0; b < B; ++b) {
+                    a.x = w.x + (size_t)b * q_len * d; a.out = logits + (size_t)b * logits_bstride;
+                    BS_TRY(launch_f32_fused(F32_HEAD, a, s));
+                }
+            }
+        }
+        return BS_OK;
     } else {
     // Up to 32 rows of a wide model (verification of one to a few sequences): whole-K projections with the consumer's work in the
     // epilogue (gemm_rows_kernel), where the 16-column units of a projection fill at least four fifths of the compute units'

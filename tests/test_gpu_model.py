@@ -771,3 +771,46 @@ def test_blocks_of_rows_from_129_rows_on(c, B, n):
     for b in {0, B - 1}:
         ref = forward(c, W, toks[b], storage="bf16", last_rows=rows)
         assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
+
+
+# fp32 projections with the work around them: rows and columns that four and eight do not divide, a vocabulary of an odd size, an embedding and an
+# LM head at addresses that 16 does not divide, trailing logit rows, a sequence left out; short caches and one in several splits
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("c,B,n,q_len,rows,max_len", [
+    (synth.cfg(2, 72, 3, 24, 104, 131, dtype="f32"), 1, 9, 1, 1, 11), (synth.cfg(2, 72, 3, 24, 104, 131, dtype="f32"), 3, 61, 3, 2, 64),
+    (synth.cfg(1, 264, 6, 40, 520, 999, n_kv_heads=2, dtype="f32"), 5, 130, 1, 1, 140), (synth.cfg(1, 264, 6, 40, 520, 999, n_kv_heads=2, dtype="f32"), 2, 500, 9, 9, 512),
+    (synth.cfg(1, 64, 2, 128, 96, 300, dtype="f32"), 3, 520, 6, 6, 530)])
+def test_f32_projections_with_the_work_around_them(c, B, n, q_len, rows, max_len, shift):
+    W = synth.make_weights(c, 33)
+    dev = {k: torch.from_numpy(v).cuda() for k, v in W.items()}
+    for k in ("embed", "lm_head"):
+        dev[k] = torch.empty(dev[k].numel() + shift, device="cuda")[shift:].view(dev[k].shape).copy_(dev[k])
+    m = bs().Model(c, dev)
+    kv = bs().KV(m, B, max_len)
+    toks = synth.make_prompts(B, n + q_len, c["vocab"], seed=34)
+    dt = torch.from_numpy(toks.astype(np.int32)).cuda()
+    bs().prefill(m, kv, dt, n)
+    kvl = torch.full((B,), n, dtype=torch.int32, device="cuda")
+    if B > 2:
+        kvl[1] = max_len                               # no room: left out
+    logits = bs().verify_forward(m, kv, dt[:, n:].contiguous(), kvl, rows)
+    for b in range(B):
+        if B <= 2 or b != 1:
+            ref = forward(c, W, toks[b], storage="f32", last_rows=rows)
+            assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["f32"], b
+
+
+@pytest.mark.parametrize("B,q_len", [(1, 47), (3, 16), (1, 130)])
+def test_f32_kernel_per_step_under_wide_feed_forward_matrices(B, q_len):
+    """48 rows and more of a model whose feed-forward matrices have more than 12 million elements each."""
+    c = synth.cfg(1, 1024, 2, 32, 11800, 8201, n_kv_heads=1, dtype="f32")
+    W = synth.make_weights(c, 35)
+    dev = {k: torch.from_numpy(v).cuda() for k, v in W.items()}
+    dev["lm_head"] = torch.empty(8201 * 1024 + 1, device="cuda")[1:].view(8201, 1024).copy_(dev["lm_head"])
+    m = bs().Model(c, dev)
+    kv = bs().KV(m, B, q_len)
+    toks = synth.make_prompts(B, q_len, c["vocab"], seed=36)
+    logits = bs().verify_forward(m, kv, torch.from_numpy(toks.astype(np.int32)).cuda(), torch.zeros(B, dtype=torch.int32, device="cuda"))
+    for b in range(B):
+        ref = forward(c, W, toks[b], storage="f32")
+        assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["f32"], b
