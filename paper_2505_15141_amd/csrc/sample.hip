@@ -120,29 +120,36 @@ __device__ __forceinline__ float load_one<uint16_t>(const uint16_t* row, int idx
 }
 
 struct RowShared {
-    float red[8][SW];                 // also the staging of a batch of slab sums
-    float slab_tot[MAX_SLABS];
-    float wave_tot[SW];
-    int wave_first[SW];
-    int wave_last[SW];
-    float bcast[8];
-    int ibcast[4];
+    __attribute__((aligned(16))) float red[8][SW];        // [slab][wavefront] of a batch of slab sums
+    __attribute__((aligned(16))) float slab_tot[MAX_SLABS];        // zero from the last slab to the end of its batch
+    __attribute__((aligned(16))) float wave_tot[SW];
+    __attribute__((aligned(16))) int wave_first[SW];
+    __attribute__((aligned(16))) int wave_last[SW];
+    int ibcast;
 };
 
 struct RowResult {
     int token;        // candidate token of this row (valid in every lane)
-    float p_x, q_x;   // normalised probabilities of the drafted token (lane 0 only, if x >= 0)
     int fallback;     // residual had no mass: drew from p instead
 };
 
-// NG: groups per lane held in registers (CACHED), else slabs read at a time.
+// Eight floats of LDS in two reads: a loop that adds them one read after the other is a trip of LDS each
+struct Eight { float v[SW]; };
+static_assert(SW == 8, "two float4 reads");
+__device__ __forceinline__ Eight lds_eight(const float* p) {
+    const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
+    return {{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}};
+}
+
 // Processes one row pair.  has_q = false: the draw is from softmax(p) (bonus token, draft draws).
-// x = drafted token for the acceptance test, or -1.
+// CACHED: the rows have at most NG slabs and stay in registers over the passes (no trip to memory between them; any V and alignment); otherwise NG
+// slabs are read at a time, and the deciding one once more.
 template <typename T, int NG, bool CACHED>
-__device__ RowResult process_row(const T* __restrict__ p, const T* __restrict__ q, bool has_q, int V, float inv_temp,
-                                 int x, float u_final, RowShared& sh, const float* known = nullptr) {
+__device__ __forceinline__ RowResult process_row(const T* __restrict__ p, const T* __restrict__ q, bool has_q, int V, float inv_temp,
+                                 float u_final, RowShared& sh, const float* known = nullptr) {
+    static_assert(NG <= 8, "sh.red");
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int ngroups = (V + GE - 1) / GE;
+    const int ngroups = (V + GE - 1) / GE, nfull = V / GE;       // nfull: groups that lie in the row as a whole
     const int nslabs = (ngroups + ST - 1) / ST;
 
     Raw<T> pv[CACHED ? NG : 1], qv[CACHED ? NG : 1];
@@ -164,18 +171,36 @@ __device__ RowResult process_row(const T* __restrict__ p, const T* __restrict__ 
         m = mn;
     };
     if constexpr (CACHED) {
+        // slabs that do not exist are passed over (k < nslabs is uniform): a vocabulary of 512 is one of eight
 #pragma unroll
         for (int k = 0; k < NG; ++k) {
-            const int g = tid + k * ST;
-            // the host launches this variant only for 16-byte aligned rows with V % 8 == 0
-            pv[k] = (g < ngroups) ? load_full(p, g) : neg_inf_raw(p);
-            qv[k] = (has_q && g < ngroups) ? load_full(q, g) : neg_inf_raw(p);
+            pv[k] = neg_inf_raw(p); qv[k] = neg_inf_raw(p);
+            if (k < nslabs && nfull > 0) {
+                const int g = min(tid + k * ST, nfull - 1);
+                pv[k] = load_full(p, g);
+                if (has_q) qv[k] = load_full(q, g);
+            }
+        }
+        if (nfull < NG * ST) {                       // past the whole groups: the row's last tokens (one lane's), or nothing
+            Raw<T> tp = neg_inf_raw(p), tq = neg_inf_raw(p);
+            if (nfull < ngroups && tid == nfull % ST) {
+                tp = load_raw(p, nfull, V);
+                if (has_q) tq = load_raw(q, nfull, V);
+            }
+#pragma unroll
+            for (int k = 0; k < NG; ++k)
+                if (tid + k * ST >= nfull) {
+                    pv[k] = tid + k * ST == nfull ? tp : neg_inf_raw(p);
+                    qv[k] = tid + k * ST == nfull ? tq : neg_inf_raw(p);
+                }
         }
         if (!known) {
 #pragma unroll
             for (int k = 0; k < NG; ++k) {
-                online(mp, sp, pv[k]);
-                if (has_q) online(mq, sq, qv[k]);
+                if (k < nslabs) {
+                    online(mp, sp, pv[k]);
+                    if (has_q) online(mq, sq, qv[k]);
+                }
                 __builtin_amdgcn_sched_barrier(0);   // one group at a time: keeps the live set small
             }
         }
@@ -194,31 +219,29 @@ __device__ RowResult process_row(const T* __restrict__ p, const T* __restrict__ 
     if (known) {
         mp = known[0]; sp = known[1]; mq = known[2]; sq = known[3];
     } else {
-        const float wmp = wave_max(mp), wmq = wave_max(mq);
+        const float wmp = wave_max(mp), wmq = has_q ? wave_max(mq) : -INFINITY;
         if (lane == 0) { sh.red[0][wid] = wmp; sh.red[1][wid] = wmq; }
         __syncthreads();
-        float bmp = sh.red[0][0], bmq = sh.red[1][0];
+        const Eight xp = lds_eight(sh.red[0]), xq = lds_eight(sh.red[1]);
+        float bmp = xp.v[0], bmq = xq.v[0];
 #pragma unroll
-        for (int w = 1; w < SW; ++w) { bmp = fmaxf(bmp, sh.red[0][w]); bmq = fmaxf(bmq, sh.red[1][w]); }
+        for (int w = 1; w < SW; ++w) { bmp = fmaxf(bmp, xp.v[w]); bmq = fmaxf(bmq, xq.v[w]); }
         const float rp = (mp == -INFINITY) ? 0.f : sp * __expf(mp - bmp);
         const float rq = (mq == -INFINITY) ? 0.f : sq * __expf(mq - bmq);
-        const float wsp = wave_sum(rp), wsq = wave_sum(rq);
+        const float wsp = wave_sum(rp), wsq = has_q ? wave_sum(rq) : 0.f;
         if (lane == 0) { sh.red[2][wid] = wsp; sh.red[3][wid] = wsq; }
         __syncthreads();
+        const Eight yp = lds_eight(sh.red[2]), yq = lds_eight(sh.red[3]);
         float zp = 0.f, zq = 0.f;
 #pragma unroll
-        for (int w = 0; w < SW; ++w) { zp += sh.red[2][w]; zq += sh.red[3][w]; }
+        for (int w = 0; w < SW; ++w) { zp += yp.v[w]; zq += yq.v[w]; }
         mp = bmp; mq = bmq; sp = zp; sq = zq;
     }
     const float inv_zp = 1.0f / sp;
     const float inv_zq = has_q ? 1.0f / sq : 0.f;
 
     RowResult res;
-    res.p_x = 0.f; res.q_x = 0.f; res.fallback = 0; res.token = 0;
-    if (tid == 0 && x >= 0) {
-        res.p_x = __expf(load_one<T>(p, x) * inv_temp - mp) * inv_zp;
-        res.q_x = has_q ? __expf(load_one<T>(q, x) * inv_temp - mq) * inv_zq : 0.f;
-    }
+    res.fallback = 0; res.token = 0;
 
     // ---- weights of the draw: [p - q]_+ (normalised probabilities) or exp(p - max) ----
     bool residual = has_q;
@@ -236,71 +259,74 @@ __device__ RowResult process_row(const T* __restrict__ p, const T* __restrict__ 
             for (int e = 0; e < GE; ++e) w[e] = __expf(a[e] - mp);
         }
     };
-    auto group_weights = [&](int k, int g, float w[GE]) {
+    auto group_weights = [&](int g, float w[GE]) {   // read from memory
         if (g >= ngroups) {
 #pragma unroll
             for (int e = 0; e < GE; ++e) w[e] = 0.f;
             return;
         }
-        if constexpr (CACHED) {
-            weights(pv[k], qv[k], w);
-        } else {
-            const Raw<T> ra = load_raw(p, g, V);
-            const Raw<T> rb = residual ? load_raw(q, g, V) : ra;
-            weights(ra, rb, w);
-        }
+        const Raw<T> ra = load_raw(p, g, V);
+        const Raw<T> rb = residual ? load_raw(q, g, V) : ra;
+        weights(ra, rb, w);
     };
-    auto group_sum = [&](int k, int g) {
-        float w[GE];
-        group_weights(k, g, w);
+    auto sum8 = [](const float w[GE]) {
         float s = 0.f;
 #pragma unroll
         for (int e = 0; e < GE; ++e) s += w[e];
         return s;
     };
+    auto group_sum = [&](int g) {
+        float w[GE];
+        group_weights(g, w);
+        return sum8(w);
+    };
 
-    float total = 0.f;
+    float total = 0.f, tot[CACHED ? NG : 1];         // CACHED: slab totals
 #pragma nounroll
     for (int attempt = 0; attempt < 2; ++attempt) {
         // ---- pass 2: slab totals ----
+        total = 0.f;
         if constexpr (CACHED) {
             float ss[NG];
 #pragma unroll
             for (int k = 0; k < NG; ++k) {
-                ss[k] = group_sum(k, tid + k * ST);
+                ss[k] = 0.f;
+                if (k < nslabs) {
+                    float w[GE];
+                    weights(pv[k], qv[k], w);
+                    ss[k] = tid + k * ST < ngroups ? sum8(w) : 0.f;
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if (nslabs > 1) {
 #pragma unroll
-            for (int k = 0; k < NG; ++k) ss[k] = wave_sum(ss[k]);
+                for (int k = 0; k < NG; ++k) ss[k] = wave_sum(ss[k]);
+            } else ss[0] = wave_sum(ss[0]);
             __syncthreads();
             if (lane == 0) {
 #pragma unroll
-                for (int k = 0; k < NG; ++k) sh.slab_tot[k * SW + wid] = ss[k];   // staging: [slab][wave]
+                for (int k = 0; k < NG; ++k) sh.red[k][wid] = ss[k];
             }
             __syncthreads();
-            float tot[NG];
 #pragma unroll
             for (int k = 0; k < NG; ++k) {
-                float t = 0.f;
+                tot[k] = 0.f;
+                if (k < nslabs) {
+                    const Eight x = lds_eight(sh.red[k]);
 #pragma unroll
-                for (int w = 0; w < SW; ++w) t += sh.slab_tot[k * SW + w];
-                tot[k] = t;
+                    for (int w = 0; w < SW; ++w) tot[k] += x.v[w];
+                }
+                total += tot[k];
             }
-            __syncthreads();
-            if (tid == 0) {
-#pragma unroll
-                for (int k = 0; k < NG; ++k) sh.slab_tot[k] = tot[k];
-            }
-            __syncthreads();
         } else {
             constexpr int NB = NG;
-            const int nfull = V / GE;                // groups that lie in the row as a whole
             for (int k0 = 0; k0 < nslabs; k0 += NB) {
                 float ss[NB];
                 if (NB > SLAB_BATCH && nfull > 0) {
                     Raw<T> ra[NB], rb[NB];
 #pragma unroll
                     for (int j = 0; j < NB; ++j) {
+                        if (k0 + j >= nslabs) break; // uniform
                         const int g = min(tid + (k0 + j) * ST, nfull - 1);
                         ra[j] = load_full(p, g);
                         rb[j] = residual ? load_full(q, g) : ra[j];
@@ -308,19 +334,19 @@ __device__ RowResult process_row(const T* __restrict__ p, const T* __restrict__ 
 #pragma unroll
                     for (int j = 0; j < NB; ++j) {
                         const int g = tid + (k0 + j) * ST;
-                        float w[GE], t = 0.f;
+                        ss[j] = 0.f;
+                        if (k0 + j >= nslabs) continue;
+                        float w[GE];
                         weights(ra[j], rb[j], w);
-#pragma unroll
-                        for (int e = 0; e < GE; ++e) t += w[e];
-                        ss[j] = g < nfull ? t : 0.f;
-                        if (g >= nfull && g < ngroups) ss[j] = group_sum(k0 + j, g);     // the row's last tokens: one lane
+                        ss[j] = g < nfull ? sum8(w) : 0.f;
+                        if (g >= nfull && g < ngroups) ss[j] = group_sum(g);     // the row's last tokens: one lane
                     }
 #pragma unroll
                     for (int j = 0; j < NB; ++j) ss[j] = wave_sum(ss[j]);
                 } else {
 #pragma unroll
                     for (int j = 0; j < NB; ++j)
-                        ss[j] = (k0 + j < nslabs) ? wave_sum(group_sum(k0 + j, tid + (k0 + j) * ST)) : 0.f;
+                        ss[j] = (k0 + j < nslabs) ? wave_sum(group_sum(tid + (k0 + j) * ST)) : 0.f;
                 }
                 __syncthreads();
                 if (lane == 0) {
@@ -328,17 +354,20 @@ __device__ RowResult process_row(const T* __restrict__ p, const T* __restrict__ 
                     for (int j = 0; j < NB; ++j) sh.red[j][wid] = ss[j];
                 }
                 __syncthreads();
-                if (tid < NB && k0 + tid < nslabs) {
+                if (tid < NB) {
+                    const Eight x = lds_eight(sh.red[tid]);
                     float t = 0.f;
 #pragma unroll
-                    for (int w = 0; w < SW; ++w) t += sh.red[tid][w];
-                    sh.slab_tot[k0 + tid] = t;
+                    for (int w = 0; w < SW; ++w) t += x.v[w];
+                    sh.slab_tot[k0 + tid] = k0 + tid < nslabs ? t : 0.f;
                 }
             }
             __syncthreads();
+            for (int k = 0; k < nslabs; k += 4) {    // behind the last slab: zeros
+                const float4 t = *reinterpret_cast<const float4*>(&sh.slab_tot[k]);
+                total += t.x; total += t.y; total += t.z; total += t.w;
+            }
         }
-        total = 0.f;
-        for (int k = 0; k < nslabs; ++k) total += sh.slab_tot[k];
         if (!residual || total > 0.f) break;
         // residual without mass (p == q up to rounding): draw from p instead
         residual = false;
@@ -346,7 +375,7 @@ __device__ RowResult process_row(const T* __restrict__ p, const T* __restrict__ 
         __syncthreads();
     }
 
-    // ---- locate the slab ----
+    // ---- locate the slab: the first whose end lies behind the threshold ----
     const float thr = u_final * total;
     int kstar = -1;
     float base = 0.f;
@@ -354,16 +383,25 @@ __device__ RowResult process_row(const T* __restrict__ p, const T* __restrict__ 
         float run = 0.f;
         int last_pos = 0;
         float last_base = 0.f;
-        for (int k = 0; k < nslabs; ++k) {
-            const float t = sh.slab_tot[k];
+        auto at = [&](int k, float t) {
+            if (kstar >= 0) return;
             if (t > 0.f) { last_pos = k; last_base = run; }
-            if (run + t > thr) { kstar = k; base = run; break; }
+            if (run + t > thr) { kstar = k; base = run; }
             run += t;
+        };
+        if constexpr (CACHED) {
+#pragma unroll
+            for (int k = 0; k < NG; ++k) at(k, tot[k]);
+        } else {
+            for (int k = 0; k < nslabs && kstar < 0; k += 4) {
+                const float4 t = *reinterpret_cast<const float4*>(&sh.slab_tot[k]);
+                at(k, t.x); at(k + 1, t.y); at(k + 2, t.z); at(k + 3, t.w);
+            }
         }
         if (kstar < 0) { kstar = last_pos; base = last_base; }   // thr >= total only through rounding
     }
 
-    // ---- pass 3: scan of the 1024 group sums of slab kstar ----
+    // ---- pass 3: scan of the 512 group sums of slab kstar ----
     float w[GE];
     {
         const int g = tid + kstar * ST;
@@ -386,7 +424,7 @@ __device__ RowResult process_row(const T* __restrict__ p, const T* __restrict__ 
                 for (int e = 0; e < GE; ++e) w[e] = 0.f;
             }
         } else {
-            group_weights(kstar, g, w);
+            group_weights(g, w);
         }
     }
     float gs = 0.f;
@@ -398,11 +436,14 @@ __device__ RowResult process_row(const T* __restrict__ p, const T* __restrict__ 
         const float v = __shfl_up(incl, o, 64);
         if (lane >= o) incl += v;
     }
-    __syncthreads();
     if (lane == 63) sh.wave_tot[wid] = incl;
     __syncthreads();
     float before = base;
-    for (int wv = 0; wv < wid; ++wv) before += sh.wave_tot[wv];
+    {
+        const Eight x = lds_eight(sh.wave_tot);
+#pragma unroll
+        for (int wv = 0; wv < SW; ++wv) before += wv < wid ? x.v[wv] : 0.f;
+    }
     incl += before;
     // The shuffled prefix is not monotone in fp32 (every lane sums in its own order), so an empty group can be the first
     // whose prefix exceeds thr: only groups that carry mass may be hit, and below only tokens that do.
@@ -415,9 +456,15 @@ __device__ RowResult process_row(const T* __restrict__ p, const T* __restrict__ 
     }
     __syncthreads();
     int tstar = -1, tlast = -1;
-    for (int wv = 0; wv < SW; ++wv) {
-        if (tstar < 0 && sh.wave_first[wv] < 64) tstar = wv * 64 + sh.wave_first[wv];
-        if (sh.wave_last[wv] >= 0) tlast = wv * 64 + sh.wave_last[wv];
+    {
+        const int4 f0 = *reinterpret_cast<const int4*>(&sh.wave_first[0]), f1 = *reinterpret_cast<const int4*>(&sh.wave_first[4]);
+        const int4 l0 = *reinterpret_cast<const int4*>(&sh.wave_last[0]), l1 = *reinterpret_cast<const int4*>(&sh.wave_last[4]);
+        const int f[SW] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w}, l[SW] = {l0.x, l0.y, l0.z, l0.w, l1.x, l1.y, l1.z, l1.w};
+#pragma unroll
+        for (int wv = 0; wv < SW; ++wv) {
+            if (tstar < 0 && f[wv] < 64) tstar = wv * 64 + f[wv];
+            if (l[wv] >= 0) tlast = wv * 64 + l[wv];
+        }
     }
     const bool forced = tstar < 0;            // rounding pushed thr past this slab's scan total
     if (forced) tstar = tlast;
@@ -431,11 +478,11 @@ __device__ RowResult process_row(const T* __restrict__ p, const T* __restrict__ 
             if (pick < 0 && !forced && run > thr && w[e] > 0.f) pick = e;
         }
         if (pick < 0) pick = lastpos;
-        sh.ibcast[0] = (tid + kstar * ST) * GE + pick;
+        sh.ibcast = (tid + kstar * ST) * GE + pick;
     }
-    if (tstar < 0 && tid == 0) sh.ibcast[0] = 0;   // only with non-finite input
+    if (tstar < 0 && tid == 0) sh.ibcast = 0;      // only with non-finite input
     __syncthreads();
-    res.token = min(sh.ibcast[0], V - 1);
+    res.token = min(sh.ibcast, V - 1);
     return res;
 }
 
@@ -538,46 +585,58 @@ struct DecideParams {
     float* margins;        // [B, gamma] or null
 };
 
-template <typename T, int NB>
+template <typename T, int NB, bool CACHED>
 __global__ __launch_bounds__(ST) void spec_decide_kernel(DecideParams a) {
     __shared__ RowShared sh;
-    __shared__ int s_acc[ST];
-    __shared__ float2 s_sp[ST + 1], s_sq[ST];     // row statistics of this sequence: no second trip to memory for them
+    __shared__ int s_acc[ST], s_tau;
     __shared__ float s_known[4];
     const int b = blockIdx.x, tid = threadIdx.x, gamma = a.gamma;
     const T* P = reinterpret_cast<const T*>(a.p_logits) + (size_t)b * (gamma + 1) * a.V;
     const T* Q = reinterpret_cast<const T*>(a.q_logits) + (size_t)b * gamma * a.V;
     const uint32_t t = a.round_ptr ? *a.round_ptr : a.round;
-    if (tid == 0) s_sp[gamma] = a.stats[(size_t)b * (gamma + 1) + gamma];
-    for (int i = tid; i < gamma; i += ST) {
+    const float2 bonus = a.stats[(size_t)b * (gamma + 1) + gamma];
+    float2 sp = make_float2(0.f, 1.f), sq = sp;   // of position tid
+    int acc = 0;
+    if (tid < gamma) {                            // gamma <= ST (host check)
+        const int i = tid;
         int x = a.draft_tokens[(size_t)b * gamma + i];
         const bool okx = x >= 0 && x < a.V;
         if (!okx) x = 0;
-        const float2 sp = a.stats[(size_t)b * (gamma + 1) + i], sq = a.stats[a.n_p_rows + (size_t)b * gamma + i];
-        s_sp[i] = sp; s_sq[i] = sq;
+        sp = a.stats[(size_t)b * (gamma + 1) + i]; sq = a.stats[a.n_p_rows + (size_t)b * gamma + i];
         const float px = __expf(load_one<T>(P + (size_t)i * a.V, x) * a.inv_temp - sp.x) / sp.y;
         const float qx = __expf(load_one<T>(Q + (size_t)i * a.V, x) * a.inv_temp - sq.x) / sq.y;
         const float u = a.uniforms ? a.uniforms[(size_t)b * (gamma + 1) + i]
                                    : u_open_closed(philox_word(a.seed, (uint32_t)b, t, (uint32_t)i, PURPOSE_ACCEPT));
-        const int acc = okx && (u * qx <= px);
-        s_acc[i] = acc;
+        acc = okx && (u * qx <= px);
         if (a.flags) a.flags[(size_t)b * (gamma + 1) + i] = acc;
         if (a.margins) a.margins[(size_t)b * gamma + i] = okx ? ((qx > 0.f) ? fminf(1.f, px / qx) : 1.f) - u : -1.f;
     }
-    __syncthreads();
-    int tau = 0;
-    while (tau < gamma && s_acc[tau]) ++tau;
-    const bool has_q = tau < gamma;
-    if (tid == 0) {
-        const float2 sp = s_sp[tau];
-        s_known[0] = sp.x; s_known[1] = sp.y; s_known[2] = 0.f; s_known[3] = 1.f;
-        if (has_q) { const float2 sq = s_sq[tau]; s_known[2] = sq.x; s_known[3] = sq.y; }
+    // tau leading acceptances; the lane of the deciding position hands its row statistics on
+    auto hand_on = [&](int tau) {
+        if (tid == tau && tau < gamma) { s_known[0] = sp.x; s_known[1] = sp.y; s_known[2] = sq.x; s_known[3] = sq.y; }
+        if (tid == 0 && tau == gamma) { s_known[0] = bonus.x; s_known[1] = bonus.y; s_known[2] = 0.f; s_known[3] = 1.f; }
+    };
+    if (gamma < 64) {                             // the first wavefront has them all
+        if (tid < 64) {
+            const int tau = __ffsll((long long)~__ballot(acc)) - 1;
+            hand_on(tau);
+            if (tid == 0) s_tau = tau;
+        }
+    } else {
+        s_acc[tid] = acc;
+        __syncthreads();
+        int tau = 0;
+        while (tau < gamma && s_acc[tau]) ++tau;
+        hand_on(tau);
+        if (tid == 0) s_tau = tau;
     }
     __syncthreads();
+    const int tau = s_tau;
+    const bool has_q = tau < gamma;
     const float u_final = a.uniforms ? a.uniforms[(size_t)b * (gamma + 1) + gamma]
                                      : u_closed_open(philox_word(a.seed, (uint32_t)b, t, 0u, PURPOSE_FINAL));
-    const RowResult r = process_row<T, NB, false>(P + (size_t)tau * a.V, has_q ? Q + (size_t)tau * a.V : nullptr, has_q,
-                                                   a.V, a.inv_temp, -1, u_final, sh, s_known);
+    const T *p = P + (size_t)tau * a.V, *q = has_q ? Q + (size_t)tau * a.V : nullptr;
+    const RowResult r = process_row<T, NB, CACHED>(p, q, has_q, a.V, a.inv_temp, u_final, sh, s_known);
     if (tid == 0) {
         if (a.flags) a.flags[(size_t)b * (gamma + 1) + tau] = (r.fallback << 1);     // bit 0 clear: not accepted / bonus row
         if (a.cand) a.cand[(size_t)b * (gamma + 1) + tau] = r.token;
@@ -676,13 +735,12 @@ __global__ __launch_bounds__(ST) void draw_kernel(DrawParams a) {
     // rows of up to 32768 logits stay in registers (eight groups per lane): one trip to memory instead of one per
     // pass over the row -- with a single sequence this kernel is one workgroup and nothing else hides its latency
     // (draft step at V = 32000: 6 us shorter); one group per lane where that is the whole row (V = 512: 7.6 -> 4.6 us)
-    const bool whole = a.V % GE == 0 && a.row_stride % 4 == 0 && ((uintptr_t)a.logits & 15) == 0;
-    if (whole && a.V <= ST * GE)
-        r = process_row<float, 1, true>(p, nullptr, false, a.V, a.inv_temp, -1, u, sh);
-    else if (whole && a.V <= 8 * ST * GE)
-        r = process_row<float, 8, true>(p, nullptr, false, a.V, a.inv_temp, -1, u, sh);
+    if (a.V <= ST * GE)
+        r = process_row<float, 1, true>(p, nullptr, false, a.V, a.inv_temp, u, sh);
+    else if (a.V <= 8 * ST * GE)
+        r = process_row<float, 8, true>(p, nullptr, false, a.V, a.inv_temp, u, sh);
     else
-        r = process_row<float, SLAB_BATCH, false>(p, nullptr, false, a.V, a.inv_temp, -1, u, sh);
+        r = process_row<float, SLAB_BATCH, false>(p, nullptr, false, a.V, a.inv_temp, u, sh);
     if (threadIdx.x == 0) {
         if (a.out0) a.out0[(size_t)b * a.stride0 + a.off0] = r.token;
         if (a.out1) a.out1[(size_t)b * a.stride1 + a.off1] = r.token;
@@ -735,14 +793,13 @@ int launch_spec_sample(const void* p_logits, const void* q_logits, const int32_t
     // than compute units it is other sequences on the same compute unit that hide this kernel's chain of dependent loads
     // (256 instead of 50 registers at B = 1024, bf16: 77 against 42 us); up to that deeper batches do, see DEEP_SEQS.
     const dim3 grid(B), block(ST);
-    const bool deep = B <= DEEP_SEQS;
-    if (dtype == BS_BF16) {
-        if (deep) hipLaunchKernelGGL((spec_decide_kernel<uint16_t, DEEP_BATCH>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((spec_decide_kernel<uint16_t, SLAB_BATCH>), grid, block, 0, stream, a);
-    } else {
-        if (deep) hipLaunchKernelGGL((spec_decide_kernel<float, DEEP_BATCH>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((spec_decide_kernel<float, SLAB_BATCH>), grid, block, 0, stream, a);
-    }
+    // bf16 rows of up to 32768 logits stay in registers (64 sequences, gamma 8, V = 32000 27.4 -> 25.7 us); float rows take twice as many and spill there
+#define BS_DECIDE(T) do { if (B > DEEP_SEQS) hipLaunchKernelGGL((spec_decide_kernel<T, SLAB_BATCH, false>), grid, block, 0, stream, a); \
+                         else if (sizeof(T) == 2 && V <= DEEP_BATCH * ST * GE) hipLaunchKernelGGL((spec_decide_kernel<T, DEEP_BATCH, sizeof(T) == 2>), grid, block, 0, stream, a); \
+                         else hipLaunchKernelGGL((spec_decide_kernel<T, DEEP_BATCH, false>), grid, block, 0, stream, a); } while (0)
+    if (dtype == BS_BF16) BS_DECIDE(uint16_t);
+    else BS_DECIDE(float);
+#undef BS_DECIDE
     BS_LAUNCH_CHECK();
     return BS_OK;
 }

@@ -204,3 +204,10 @@ def test_row_batches_and_alignment_change_nothing(V, dtype):
         while tau < gamma and toks_h[b, tau] == best[b, tau]:
             tau += 1
         assert (acc[b], tok[b]) == (tau, best[b, tau]), b
+
+
+# leading acceptances of up to 63 positions are counted by one wavefront, of more by a walk; rows of 32768 logits stay in registers (bf16), 32776 do not
+@pytest.mark.parametrize("gamma,V,dtype", [(62, 5, "f32"), (63, 9, "bf16"), (64, 6, "bf16"), (65, 33, "f32"), (130, 5, "f32"), (2, 32761, "bf16"), (2, 32776, "bf16"), (2, 4100, "bf16")])
+def test_many_positions_and_rows_at_the_edges_of_the_register_path(gamma, V, dtype):
+    for noise in (0.0, 0.02, 0.5):                       # everything accepted, a late rejection as a rule, an early one
+        run_case(3, gamma, V, dtype, seed=gamma + V, noise=noise)
