@@ -14,6 +14,7 @@ struct GemmArgs {
     size_t ks_stride;
     int M, N, K, ldo, KS;
     int tiled;            // weights are in the 64x32-block layout written by launch_pack_weights
+    int stream;           // many-row GEMM: the model's weights are more than the memory-side cache holds (streams_past_cache)
     int x_tiled;          // many-row GEMM: R = many_tiled(M) if the planes of x are tiled (xt_index, x_plane = R K), else 0 (row-major)
 };
 
@@ -90,13 +91,13 @@ int launch_gemm_big(const GemmArgs& a, hipStream_t s);   // 33 rows and more, K 
 // of columns, also the sums of squares per row that EPI_RESID leaves), the bytes of partial sums that needs, and whether it is
 // expected to beat launch_gemm with a consumer kernel.
 // epi: EPI_QKV, N = stacked columns; EPI_SWIGLU, N = columns of one matrix; EPI_RESID.
-struct BigPlan { int nt, mt, wm, n_mb, full, rem, ks, n_tiles; size_t part_bytes; bool fused; };
+struct BigPlan { int nt, mt, wm, n_mb, full, rem, ks, n_tiles; size_t part_bytes; bool once, fused; };
 // How launch_gemm_big cuts the output: n_tiles x n_mb tiles of `cols` columns and 16 mt rows, eight wavefronts as 8 / wm columns x wm rows.
 struct BigTiles { int wm, mt, n_mb, cols, n_tiles; };
-BigTiles big_tiles(int N, int K, int M, int ks);
+BigTiles big_tiles(int N, int K, int M, int ks, bool stream);
 int big_splits(int N, int K, int M);                     // ranges of K it is given
 bool big_fused_applies(int epi, int N, int K, int M);
-BigPlan big_plan(int epi, int N, int K, int M);
+BigPlan big_plan(int epi, int N, int K, int M, bool stream);
 int launch_gemm_big_fused(int epi, const GemmArgs& g, const DecArgs& e, const BigPlan& p, float* part,     // p = big_plan of the same sizes
                           size_t part_bytes, hipStream_t s);
 size_t packed_elems(int N, int K);                       // elements of the tiled copy of an [N][K] matrix

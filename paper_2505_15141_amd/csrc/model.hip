@@ -159,6 +159,7 @@ struct FwdWs {
     int ks_qkv, ks_o, ks_gu, ks_d;
     BigPlan big_qkv, big_gu, big_o, big_d;    // many-row projections whose epilogue does the consumer's work (fused)
     size_t part_qkv_bytes, part_gu_bytes, part_o_bytes, part_d_bytes;
+    bool weights_stream;      // the weights alone are more than the memory-side cache holds
     size_t total;
 };
 
@@ -176,6 +177,7 @@ static bool streams_past_cache(const bs_model_cfg& c, size_t kv_bytes) {
 static FwdWs carve(const bs_model_cfg& c, int B, int q_len, int max_len, char* base) {
     FwdWs w;
     const size_t M = (size_t)B * q_len;
+    w.weights_stream = streams_past_cache(c, 0);
     const size_t Mp = M <= ROWS_MAX ? rows_tiled((int)M) : many_tiled((int)M);     // planes in a tiled layout (xt_index)
     const size_t nq = (size_t)c.n_heads * c.head_dim, nkv = (size_t)c.n_kv_heads * c.head_dim;
     w.ks_qkv = gemm_splits(c.dtype, (int)(nq + 2 * nkv), c.d_model, (int)M);
@@ -213,7 +215,7 @@ static FwdWs carve(const bs_model_cfg& c, int B, int q_len, int max_len, char* b
     }
     // partial sums: those of launch_gemm, or of the items that a many-row projection with its consumer's work splits (big_plan)
     auto big = [&](int epi, size_t N, size_t K, int ks, BigPlan& p) -> size_t {
-        p = c.dtype == BS_BF16 && big_fused_applies(epi, (int)N, (int)K, (int)M) ? big_plan(epi, (int)N, (int)K, (int)M) : BigPlan{};
+        p = c.dtype == BS_BF16 && big_fused_applies(epi, (int)N, (int)K, (int)M) ? big_plan(epi, (int)N, (int)K, (int)M, w.weights_stream) : BigPlan{};
         return p.fused ? p.part_bytes : M * (epi == EPI_SWIGLU ? 2 * N : N) * 4 * ks;
     };
     w.part_qkv_bytes = big(EPI_QKV, nq + 2 * nkv, c.d_model, w.ks_qkv, w.big_qkv);
@@ -426,7 +428,7 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
             BS_TRY(launch_rmsnorm(dt, w.x, pend, w.ks_d, (size_t)M * d, L.attn_norm, d, c.norm_eps, B, q_len, q_len,
                                   (size_t)M * d, w.h, 0, s));
         GemmArgs g;
-        g.tiled = m->packed ? 1 : 0; g.x_tiled = many ? RT : 0;
+        g.tiled = m->packed ? 1 : 0; g.x_tiled = many ? RT : 0; g.stream = w.weights_stream;
         g.x = w.h; g.x_plane = (size_t)MP * d; g.w[0] = L.wq; g.w[1] = L.wk; g.w[2] = L.wv; g.seg_rows[0] = nq; g.seg_rows[1] = nkv;
         g.out = w.part_qkv; g.ks_stride = (size_t)M * nqkv; g.M = M; g.N = nqkv; g.K = d; g.ldo = nqkv; g.KS = w.ks_qkv;
         if (fuse_qkv) {
@@ -521,7 +523,7 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
         BS_TRY(launch_rmsnorm(dt, w.x, pend, w.ks_d, (size_t)M * d, m->final_norm, d, c.norm_eps, B, q_len, logit_rows,
                               (size_t)LP * d, w.h, LT, s));
         GemmArgs g;
-        g.tiled = m->packed ? 1 : 0; g.x_tiled = LT;
+        g.tiled = m->packed ? 1 : 0; g.x_tiled = LT; g.stream = w.weights_stream;
         g.x_plane = (size_t)LP * d;
         g.w[0] = m->lm_head; g.w[1] = g.w[2] = nullptr; g.seg_rows[0] = c.vocab; g.seg_rows[1] = 0;
         g.N = c.vocab; g.K = d; g.KS = 1; g.ks_stride = 0;

@@ -773,6 +773,32 @@ def test_blocks_of_rows_from_129_rows_on(c, B, n):
         assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
 
 
+# 33 to 256 rows of a model whose weights are more than the memory-side cache holds: eight wavefronts in a row with two, three or four weight tiles
+# each, 3 to 8 row tiles full and not, one block of rows and two; the tiled copy of the weights and the weights as they are
+@pytest.fixture(scope="module")
+def past_cache():
+    c = synth.cfg(1, 1024, 16, 64, 28672, 70001, n_kv_heads=4)
+    W = synth.make_weights(c, 97, 0.04)
+    return c, {k: (v if k.endswith("norm") else synth.to_bf16_grid(v)) for k, v in W.items()}
+
+
+@pytest.mark.parametrize("B,n,packed", [(1, 33, True), (3, 16, True), (1, 49, False), (2, 40, True), (9, 9, True), (1, 96, True), (1, 97, False),
+                                        (1, 128, True), (3, 43, True), (1, 160, True), (2, 128, False), (1, 257, True)])
+def test_rows_of_a_model_that_streams(past_cache, B, n, packed):
+    c, W = past_cache
+    m = bs().Model.from_numpy(c, W)
+    if packed:
+        m.pack(release_originals=True)
+    kv = bs().KV(m, B, n + 8)
+    toks = synth.make_prompts(B, n, c["vocab"], seed=98)
+    dt = torch.from_numpy(toks.astype(np.int32)).cuda()
+    rows = min(n, 40)
+    logits = bs().verify_forward(m, kv, dt, torch.zeros(B, dtype=torch.int32, device="cuda"), rows)
+    for b in {0, B - 1}:
+        ref = forward(c, W, toks[b], storage="bf16", last_rows=rows)
+        assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
+
+
 # fp32 projections with the work around them: rows and columns that four and eight do not divide, a vocabulary of an odd size, an embedding and an
 # LM head at addresses that 16 does not divide, trailing logit rows, a sequence left out; short caches and one in several splits
 @pytest.mark.parametrize("shift", [0, 1])
