@@ -1366,7 +1366,7 @@ __global__ __launch_bounds__(256) void f32_fused_kernel(F32Args a) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) xv[r] = *reinterpret_cast<const float4*>(xr[r] + k);
             if (EPI != F32_RESID) {
-                const float4 g = *reinterpret_cast<const float4*>(a.gain + k);
+                const float4 g = VEC ? *reinterpret_cast<const float4*>(a.gain + k) : make_float4(a.gain[k], a.gain[k + 1], a.gain[k + 2], a.gain[k + 3]);
                 u0 = make_float4(u0.x * g.x, u0.y * g.y, u0.z * g.z, u0.w * g.w);
                 u1 = make_float4(u1.x * g.x, u1.y * g.y, u1.z * g.z, u1.w * g.w);
             }
@@ -2292,8 +2292,8 @@ int launch_f32_fused(int epi, const F32Args& a, hipStream_t s) {
     BS_REQUIRE(epi != F32_RESID || !a.tok || a.x_old, BS_EINVAL, "f32_fused: residual rows missing");
     const int pairs = epi == F32_SWIGLU ? a.N : (a.N + 1) / 2, groups = (a.M + 3) / 4;
     const dim3 grid((pairs + 3) / 4, groups < 65535 ? groups : 65535), block(256);
-    // a caller's LM head need not be 16-byte aligned (the layers' matrices and the activations are)
-    const bool vec = (reinterpret_cast<uintptr_t>(a.w[0]) & 15) == 0;
+    // a caller's LM head and final norm need not be 16-byte aligned (the layers' weights and the activations are)
+    const bool vec = ((reinterpret_cast<uintptr_t>(a.w[0]) | reinterpret_cast<uintptr_t>(a.gain)) & 15) == 0;
     if (epi == F32_QKV) hipLaunchKernelGGL((f32_fused_kernel<F32_QKV, true>), grid, block, 0, s, a);
     else if (epi == F32_SWIGLU) hipLaunchKernelGGL((f32_fused_kernel<F32_SWIGLU, true>), grid, block, 0, s, a);
     else if (epi == F32_RESID) hipLaunchKernelGGL((f32_fused_kernel<F32_RESID, true>), grid, block, 0, s, a);

@@ -799,7 +799,7 @@ def test_rows_of_a_model_that_streams(past_cache, B, n, packed):
         assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
 
 
-# fp32 projections with the work around them: rows and columns that four and eight do not divide, a vocabulary of an odd size, an embedding and an
+# fp32 projections with the work around them: rows and columns that four and eight do not divide, a vocabulary of an odd size, an embedding, a final norm and an
 # LM head at addresses that 16 does not divide, trailing logit rows, a sequence left out; short caches and one in several splits
 @pytest.mark.parametrize("shift", [0, 1])
 @pytest.mark.parametrize("c,B,n,q_len,rows,max_len", [
@@ -809,7 +809,7 @@ def test_rows_of_a_model_that_streams(past_cache, B, n, packed):
 def test_f32_projections_with_the_work_around_them(c, B, n, q_len, rows, max_len, shift):
     W = synth.make_weights(c, 33)
     dev = {k: torch.from_numpy(v).cuda() for k, v in W.items()}
-    for k in ("embed", "lm_head"):
+    for k in ("embed", "lm_head", "final_norm"):
         dev[k] = torch.empty(dev[k].numel() + shift, device="cuda")[shift:].view(dev[k].shape).copy_(dev[k])
     m = bs().Model(c, dev)
     kv = bs().KV(m, B, max_len)
