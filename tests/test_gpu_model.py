@@ -840,3 +840,26 @@ def test_f32_kernel_per_step_under_wide_feed_forward_matrices(B, q_len):
     for b in range(B):
         ref = forward(c, W, toks[b], storage="f32")
         assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["f32"], b
+
+
+# QKV: the number of ranges of K decides how the sums round, so two passes that are cut into as many leave the same bits in the first layer's cache,
+# whatever blocks of rows and arrangement of wavefronts each of them takes: here one of up to 128 rows or fewer blocks, and one of more
+@pytest.mark.parametrize("c,n,fewer", [
+    (synth.cfg(1, 4096, 32, 128, 512, 512), 240, 140), (synth.cfg(1, 4096, 32, 128, 512, 512), 490, 400),
+    (synth.cfg(1, 4096, 32, 128, 512, 512, n_kv_heads=8), 240, 140), (synth.cfg(1, 768, 12, 64, 512, 512), 240, 100),
+    (synth.cfg(1, 768, 12, 64, 512, 512), 1000, 800), (synth.cfg(1, 1024, 8, 128, 512, 512), 240, 100), (synth.cfg(1, 1024, 8, 128, 512, 512), 640, 760)],
+    ids=["4096, 240", "4096, 490", "4096 grouped, 240", "768, 240", "768, 1000", "1024, 240", "1024, 640"])
+def test_keys_and_values_of_a_pass_have_the_sums_of_a_shorter_one(c, n, fewer):
+    m = bs().Model(c, synth.make_weights_device(c, 41, "cuda")).pack(release_originals=True)
+    toks = torch.from_numpy(synth.make_prompts(1, max(n, fewer), c["vocab"], seed=42).astype(np.int32)).cuda()
+    caches = []
+    for rows in (n, fewer):
+        kv = bs().KV(m, 1, 1024)
+        kv.buf.zero_()
+        bs().verify_forward(m, kv, toks[:, :rows].contiguous(), torch.zeros(1, dtype=torch.int32, device="cuda"), 1)
+        k, v = kv.buf.view(torch.int16).view(2, c["n_kv_heads"], 1024, c["head_dim"])
+        # values: blocks of 32 keys, key 16t + 4q + e of a block at slot 8q + 4t + e
+        v = v.reshape(c["n_kv_heads"], 32, c["head_dim"], 4, 2, 4).permute(0, 1, 4, 3, 5, 2).reshape(c["n_kv_heads"], 1024, c["head_dim"])
+        caches.append((k[:, :min(n, fewer)], v[:, :min(n, fewer)]))
+    for a, b in zip(*caches):
+        assert a.ne(0).any() and torch.equal(a, b), int(a.ne(b).sum())
