@@ -88,7 +88,7 @@ void prof_record(hipEvent_t e0, hipEvent_t e1, double bytes, int cls);
 int launch_gemm(int dtype, GemmArgs a, hipStream_t s);
 int launch_gemm_big(const GemmArgs& a, hipStream_t s);   // 33 rows and more, K % 32 == 0
 // The many-row projections with their consumer's work behind them (gemm_big.hip): how the work items are cut (n_tiles: tiles
-// of columns, also the sums of squares per row that EPI_RESID leaves), the bytes of partial sums that needs, and whether it is
+// of columns; EPI_RESID leaves 2 / wm sums of squares per row and tile), the bytes of partial sums that needs, and whether it is
 // expected to beat launch_gemm with a consumer kernel.
 // epi: EPI_QKV, N = stacked columns; EPI_SWIGLU, N = columns of one matrix; EPI_RESID.
 struct BigPlan { int nt, mt, wm, n_mb, full, rem, ks, n_tiles; size_t part_bytes; bool once, fused; };

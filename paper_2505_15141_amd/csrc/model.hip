@@ -465,7 +465,7 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
             DecArgs a = {};
             a.N = d; a.x = w.x; a.gain_next = L.ffn_norm; a.out_planes = reinterpret_cast<uint16_t*>(w.h); a.out_plane = (size_t)MP * d; a.out_tiled = g.x_tiled; a.ssq_out = w.ssq;
             BS_TRY(launch_gemm_big_fused(EPI_RESID, g, a, w.big_o, w.part_o, w.part_o_bytes, s));
-            ssq_n = w.big_o.n_tiles;
+            ssq_n = w.big_o.n_tiles * (2 / w.big_o.wm);
         } else {
         BS_TRY(launch_gemm(dt, g, s));
         if (defer) {
@@ -509,7 +509,7 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
             a.N = d; a.x = w.x; a.gain_next = l + 1 < c.n_layers ? m->layers[l + 1].attn_norm : nullptr;
             a.out_planes = reinterpret_cast<uint16_t*>(w.h); a.out_plane = (size_t)MP * d; a.out_tiled = g.x_tiled; a.ssq_out = a.gain_next ? w.ssq : nullptr;
             BS_TRY(launch_gemm_big_fused(EPI_RESID, g, a, w.big_d, w.part_d, w.part_d_bytes, s));
-            ssq_n = w.big_d.n_tiles;
+            ssq_n = w.big_d.n_tiles * (2 / w.big_d.wm);
         } else {
         BS_TRY(launch_gemm(dt, g, s));
         pend = w.part_d;

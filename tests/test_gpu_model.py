@@ -855,7 +855,6 @@ def test_keys_and_values_of_a_pass_have_the_sums_of_a_shorter_one(c, n, fewer):
     caches = []
     for rows in (n, fewer):
         kv = bs().KV(m, 1, 1024)
-        kv.buf.zero_()
         bs().verify_forward(m, kv, toks[:, :rows].contiguous(), torch.zeros(1, dtype=torch.int32, device="cuda"), 1)
         k, v = kv.buf.view(torch.int16).view(2, c["n_kv_heads"], 1024, c["head_dim"])
         # values: blocks of 32 keys, key 16t + 4q + e of a block at slot 8q + 4t + e
@@ -863,3 +862,17 @@ def test_keys_and_values_of_a_pass_have_the_sums_of_a_shorter_one(c, n, fewer):
         caches.append((k[:, :min(n, fewer)], v[:, :min(n, fewer)]))
     for a, b in zip(*caches):
         assert a.ne(0).any() and torch.equal(a, b), int(a.ne(b).sum())
+
+
+def test_a_row_of_wavefronts_leaves_the_sums_of_squares_of_two():
+    """4096 rows take O and down in whole items of 512 columns (eight wavefronts in a row), 2048 rows in items of 256 (four by two): the rows' sums of
+    squares, and with them the second layer's keys and values, have the same bits."""
+    c = synth.cfg(2, 4096, 32, 64, 2048, 512)
+    m = bs().Model(c, synth.make_weights_device(c, 43, "cuda")).pack(release_originals=True)
+    toks = torch.from_numpy(synth.make_prompts(4, 1024, c["vocab"], seed=44).astype(np.int32)).cuda()
+    caches = []
+    for B in (4, 2):
+        kv = bs().KV(m, B, 1024)
+        bs().verify_forward(m, kv, toks[:B].contiguous(), torch.zeros(B, dtype=torch.int32, device="cuda"), 1)
+        caches.append(kv.buf.view(torch.int16).view(2, 2, B, -1)[:, :, :2])
+    assert caches[0].ne(0).any() and torch.equal(*caches), int(caches[0].ne(caches[1]).sum())
