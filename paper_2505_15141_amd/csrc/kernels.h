@@ -90,8 +90,8 @@ int launch_gemm_big(const GemmArgs& a, hipStream_t s);   // 33 rows and more, K 
 // The many-row projections with their consumer's work behind them (gemm_big.hip): how the work items are cut (n_tiles: tiles
 // of columns; EPI_RESID leaves 2 / wm sums of squares per row and tile), the bytes of partial sums that needs, and whether it is
 // expected to beat launch_gemm with a consumer kernel.
-// epi: EPI_QKV, N = stacked columns; EPI_SWIGLU, N = columns of one matrix; EPI_RESID.
-struct BigPlan { int nt, mt, wm, n_mb, full, rem, ks, n_tiles; size_t part_bytes; bool once, fused; };
+// epi: EPI_QKV, N = stacked columns; EPI_SWIGLU, N = columns of one matrix; EPI_RESID.  plain_ks: the ranges of K launch_gemm takes if not fused.
+struct BigPlan { int nt, mt, wm, n_mb, full, rem, ks, n_tiles, plain_ks; size_t part_bytes; bool once, fused; };
 // How launch_gemm_big cuts the output: n_tiles x n_mb tiles of `cols` columns and 16 mt rows, eight wavefronts as 8 / wm columns x wm rows.
 struct BigTiles { int wm, mt, n_mb, cols, n_tiles; };
 BigTiles big_tiles(int N, int K, int M, int ks, bool stream);

@@ -150,14 +150,15 @@ static int attn_splits(int B, int H, int max_len) {
     return s;
 }
 
-struct FwdWs {
+// How the projections of a pass are cut: ranges of K of launch_gemm, or the plans of the many-row projections whose epilogue does the consumer's
+// work (fused).  The same for 16 row counts in a row.
+struct RowPlans { int ks_qkv, ks_o, ks_gu, ks_d; BigPlan big_qkv, big_o, big_gu, big_d; };
+struct FwdWs : RowPlans {
     int32_t* status; int32_t* pos; int32_t* tok; float2* rope; float* x; void* h; float* q; void* att; void* act; float* ssq;
     char* xch; size_t xch_bytes;    // resident step kernel: exchange cells (one or two rows only)
     char* acells; size_t acells_bytes;   // attention: exchange cells of key splits combined in the kernel, and tickets
     AttnPlan att_plan; AttnParts att_parts;    // more than two rows; parts == nullptr: the same splits for every sequence
     float *part_qkv, *part_o, *part_gu, *part_d, *part_attn;
-    int ks_qkv, ks_o, ks_gu, ks_d;
-    BigPlan big_qkv, big_gu, big_o, big_d;    // many-row projections whose epilogue does the consumer's work (fused)
     size_t part_qkv_bytes, part_gu_bytes, part_o_bytes, part_d_bytes;
     bool weights_stream;      // the weights alone are more than the memory-side cache holds
     size_t total;
@@ -173,17 +174,30 @@ static bool streams_past_cache(const bs_model_cfg& c, size_t kv_bytes) {
     return weights + (double)kv_bytes > 256.0 * (1 << 20);
 }
 
-// Activations take 4 bytes per element in either dtype: float, or a bf16 (hi, lo) pair of planes.
-static FwdWs carve(const bs_model_cfg& c, int B, int q_len, int max_len, char* base) {
+static RowPlans row_plans(const bs_model_cfg& c, int M) {
+    RowPlans r = {};
+    const int nq = c.n_heads * c.head_dim, nkv = c.n_kv_heads * c.head_dim;
+    const bool stream = streams_past_cache(c, 0);
+    auto plan = [&](int epi, int N, int K, BigPlan& p) {
+        if (c.dtype != BS_BF16 || !big_fused_applies(epi, N, K, M)) return gemm_splits(c.dtype, epi == EPI_SWIGLU ? 2 * N : N, K, M);
+        p = big_plan(epi, N, K, M, stream);
+        return p.plain_ks;
+    };
+    r.ks_qkv = plan(EPI_QKV, nq + 2 * nkv, c.d_model, r.big_qkv);
+    r.ks_o = plan(EPI_RESID, c.d_model, nq, r.big_o);
+    r.ks_gu = plan(EPI_SWIGLU, c.d_ff, c.d_model, r.big_gu);
+    r.ks_d = plan(EPI_RESID, c.d_model, c.d_ff, r.big_d);
+    return r;
+}
+
+// Activations take 4 bytes per element in either dtype: float, or a bf16 (hi, lo) pair of planes.  plans = row_plans(B * q_len)
+static FwdWs carve(const bs_model_cfg& c, int B, int q_len, int max_len, const RowPlans& plans, char* base) {
     FwdWs w;
+    static_cast<RowPlans&>(w) = plans;
     const size_t M = (size_t)B * q_len;
     w.weights_stream = streams_past_cache(c, 0);
     const size_t Mp = M <= ROWS_MAX ? rows_tiled((int)M) : many_tiled((int)M);     // planes in a tiled layout (xt_index)
     const size_t nq = (size_t)c.n_heads * c.head_dim, nkv = (size_t)c.n_kv_heads * c.head_dim;
-    w.ks_qkv = gemm_splits(c.dtype, (int)(nq + 2 * nkv), c.d_model, (int)M);
-    w.ks_o = gemm_splits(c.dtype, c.d_model, (int)nq, (int)M);
-    w.ks_gu = gemm_splits(c.dtype, 2 * c.d_ff, c.d_model, (int)M);
-    w.ks_d = gemm_splits(c.dtype, c.d_model, c.d_ff, (int)M);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return base ? base + o : (char*)nullptr; };
     w.status = (int32_t*)take(256);
@@ -214,14 +228,11 @@ static FwdWs carve(const bs_model_cfg& c, int B, int q_len, int max_len, char* b
         w.att_parts.items = (long long*)take((size_t)w.att_plan.n_items * 8);
     }
     // partial sums: those of launch_gemm, or of the items that a many-row projection with its consumer's work splits (big_plan)
-    auto big = [&](int epi, size_t N, size_t K, int ks, BigPlan& p) -> size_t {
-        p = c.dtype == BS_BF16 && big_fused_applies(epi, (int)N, (int)K, (int)M) ? big_plan(epi, (int)N, (int)K, (int)M, w.weights_stream) : BigPlan{};
-        return p.fused ? p.part_bytes : M * (epi == EPI_SWIGLU ? 2 * N : N) * 4 * ks;
-    };
-    w.part_qkv_bytes = big(EPI_QKV, nq + 2 * nkv, c.d_model, w.ks_qkv, w.big_qkv);
-    w.part_o_bytes = big(EPI_RESID, c.d_model, nq, w.ks_o, w.big_o);
-    w.part_gu_bytes = big(EPI_SWIGLU, c.d_ff, c.d_model, w.ks_gu, w.big_gu);
-    w.part_d_bytes = big(EPI_RESID, c.d_model, c.d_ff, w.ks_d, w.big_d);
+    auto part = [&](const BigPlan& p, size_t N, int ks) { return p.fused ? p.part_bytes : M * N * 4 * ks; };
+    w.part_qkv_bytes = part(w.big_qkv, nq + 2 * nkv, w.ks_qkv);
+    w.part_o_bytes = part(w.big_o, c.d_model, w.ks_o);
+    w.part_gu_bytes = part(w.big_gu, 2 * (size_t)c.d_ff, w.ks_gu);
+    w.part_d_bytes = part(w.big_d, c.d_model, w.ks_d);
     w.part_qkv = (float*)take(w.part_qkv_bytes);
     w.part_o = (float*)take(w.part_o_bytes);
     w.part_gu = (float*)take(w.part_gu_bytes);
@@ -232,11 +243,21 @@ static FwdWs carve(const bs_model_cfg& c, int B, int q_len, int max_len, char* b
     return w;
 }
 
+// What passes of ascending lengths need, one after the other; lengths that share their plans share them here too.
+struct Needs {
+    const bs_model_cfg& c; int B, max_len, tiles = 0; RowPlans plans;
+    size_t of(int q_len) {
+        const int M = B * q_len;
+        if ((M + 15) / 16 != tiles) { tiles = (M + 15) / 16; plans = row_plans(c, M); }
+        return carve(c, B, q_len, max_len, plans, nullptr).total;
+    }
+};
 // The split-K factors depend on the row count, so the need is not monotone in q_len: take the largest.
 static size_t carve_max(const bs_model_cfg& c, int B, int max_q_len, int max_len) {
+    Needs needs = {c, B, max_len};
     size_t need = 0;
     for (int q = 1; q <= max_q_len; ++q) {
-        const size_t t = carve(c, B, q, max_len, nullptr).total;
+        const size_t t = needs.of(q);
         if (t > need) need = t;
     }
     return need;
@@ -264,7 +285,7 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
                    hipStream_t s) {
     const bs_model_cfg& c = m->cfg;
     const int B = kv->B, M = B * q_len, dt = c.dtype;
-    const FwdWs w = carve(c, B, q_len, kv->max_len, reinterpret_cast<char*>(ws));
+    const FwdWs w = carve(c, B, q_len, kv->max_len, row_plans(c, M), reinterpret_cast<char*>(ws));
     BS_REQUIRE(ws_bytes >= w.total, BS_EWORKSPACE, "forward: workspace %zu < %zu bytes", ws_bytes, w.total);
     BS_REQUIRE((reinterpret_cast<uintptr_t>(ws) & 255) == 0, BS_EWORKSPACE, "forward: workspace not 256-byte aligned");
     const int H = c.n_heads, KVH = c.n_kv_heads, hd = c.head_dim, d = c.d_model, ff = c.d_ff;
@@ -574,11 +595,12 @@ static int prefill_chunk(int B, int n) {
     const int cap = (long long)B * 128 > PREFILL_ROWS ? 128 : PREFILL_ROWS / B;
     return n < cap ? n : cap;
 }
-// n tokens in such chunks are passes of two lengths, and only these are asked for: all lengths up to 4096 are 1.4 to 1.9 ms of host
-// work ahead of the first launch.
+// n tokens in such chunks are passes of two lengths, and only these are asked for: all lengths up to 4096 would be 0.2 ms
+// of host work ahead of the first launch (a workspace that holds no such chunk costs that: the largest length that fits is looked for).
 static size_t prefill_need(const bs_model_cfg& c, int B, int n, int max_len) {
+    Needs needs = {c, B, max_len};
     const int chunk = prefill_chunk(B, n), rest = n % chunk;
-    const size_t a = carve(c, B, chunk, max_len, nullptr).total, b = rest ? carve(c, B, rest, max_len, nullptr).total : 0;
+    const size_t a = rest ? needs.of(rest) : 0, b = needs.of(chunk);
     return a > b ? a : b;
 }
 
@@ -596,8 +618,9 @@ extern "C" __attribute__((visibility("default"))) int bs_prefill(const bs_model*
     int chunk = prefill_chunk(kv->B, n);
     if (prefill_need(m->cfg, kv->B, n, kv->max_len) > ws_bytes) {      // the largest chunk up to which every length fits
         const int cap = chunk;
+        Needs needs = {m->cfg, kv->B, kv->max_len};
         chunk = 0;
-        for (int q = 1; q <= cap && carve(m->cfg, kv->B, q, kv->max_len, nullptr).total <= ws_bytes; ++q) chunk = q;
+        for (int q = 1; q <= cap && needs.of(q) <= ws_bytes; ++q) chunk = q;
     }
     BS_REQUIRE(chunk >= 1, BS_EWORKSPACE, "bs_prefill: workspace %zu bytes too small even for one row per sequence", ws_bytes);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);

@@ -876,3 +876,17 @@ def test_a_row_of_wavefronts_leaves_the_sums_of_squares_of_two():
         bs().verify_forward(m, kv, toks[:B].contiguous(), torch.zeros(B, dtype=torch.int32, device="cuda"), 1)
         caches.append(kv.buf.view(torch.int16).view(2, 2, B, -1)[:, :, :2])
     assert caches[0].ne(0).any() and torch.equal(*caches), int(caches[0].ne(caches[1]).sum())
+
+
+def test_workspace_of_every_length_is_planned_in_little_time():
+    """A workspace query plans the pass of every length up to its limit: 4096 lengths of the 7B shape in under 2 ms of host work."""
+    import ctypes
+    import time
+    c = synth.LLAMA7B_TARGET
+    cfg = bs().ModelCfg(c["n_layers"], c["d_model"], c["n_heads"], c["n_kv_heads"], c["head_dim"], c["d_ff"], c["vocab"], 1, c["rope_base"], c["norm_eps"])
+    best = 1.0
+    for _ in range(10):
+        t = time.perf_counter()
+        assert bs().lib.bs_forward_workspace_bytes(ctypes.byref(cfg), 1, 4096, 4352) > 0
+        best = min(best, time.perf_counter() - t)
+    assert best < 2e-3, best
