@@ -97,7 +97,7 @@ struct BigTiles { int wm, mt, n_mb, cols, n_tiles; };
 BigTiles big_tiles(int N, int K, int M, int ks, bool stream);
 int big_splits(int N, int K, int M);                     // ranges of K it is given
 bool big_fused_applies(int epi, int N, int K, int M);
-BigPlan big_plan(int epi, int N, int K, int M, bool stream);
+BigPlan big_plan(int epi, int N, int K, int M, bool stream, bool tiled);
 int launch_gemm_big_fused(int epi, const GemmArgs& g, const DecArgs& e, const BigPlan& p, float* part,     // p = big_plan of the same sizes
                           size_t part_bytes, hipStream_t s);
 size_t packed_elems(int N, int K);                       // elements of the tiled copy of an [N][K] matrix

@@ -174,13 +174,13 @@ static bool streams_past_cache(const bs_model_cfg& c, size_t kv_bytes) {
     return weights + (double)kv_bytes > 256.0 * (1 << 20);
 }
 
-static RowPlans row_plans(const bs_model_cfg& c, int M) {
+static RowPlans row_plans(const bs_model_cfg& c, int M, bool packed) {
     RowPlans r = {};
     const int nq = c.n_heads * c.head_dim, nkv = c.n_kv_heads * c.head_dim;
     const bool stream = streams_past_cache(c, 0);
     auto plan = [&](int epi, int N, int K, BigPlan& p) {
         if (c.dtype != BS_BF16 || !big_fused_applies(epi, N, K, M)) return gemm_splits(c.dtype, epi == EPI_SWIGLU ? 2 * N : N, K, M);
-        p = big_plan(epi, N, K, M, stream);
+        p = big_plan(epi, N, K, M, stream, packed);
         return p.plain_ks;
     };
     r.ks_qkv = plan(EPI_QKV, nq + 2 * nkv, c.d_model, r.big_qkv);
@@ -243,18 +243,26 @@ static FwdWs carve(const bs_model_cfg& c, int B, int q_len, int max_len, const R
     return w;
 }
 
-// What passes of ascending lengths need, one after the other; lengths that share their plans share them here too.
+// What passes of ascending lengths need, of a model with packed weights, of one without, or of either (sizes are asked for by configuration); lengths
+// that share their plans share them here too.
+enum { NEED_UNPACKED, NEED_PACKED, NEED_EITHER };
 struct Needs {
-    const bs_model_cfg& c; int B, max_len, tiles = 0; RowPlans plans;
+    const bs_model_cfg& c; int B, max_len, weights, tiles = 0; RowPlans plans, other;
     size_t of(int q_len) {
         const int M = B * q_len;
-        if ((M + 15) / 16 != tiles) { tiles = (M + 15) / 16; plans = row_plans(c, M); }
-        return carve(c, B, q_len, max_len, plans, nullptr).total;
+        const bool both = weights == NEED_EITHER && c.dtype == BS_BF16 && M > 128 && streams_past_cache(c, 0);       // else the plans are the same
+        if ((M + 15) / 16 != tiles) {
+            tiles = (M + 15) / 16;
+            plans = row_plans(c, M, weights != NEED_UNPACKED);
+            if (both) other = row_plans(c, M, false);
+        }
+        const size_t need = carve(c, B, q_len, max_len, plans, nullptr).total, second = both ? carve(c, B, q_len, max_len, other, nullptr).total : 0;
+        return need > second ? need : second;
     }
 };
 // The split-K factors depend on the row count, so the need is not monotone in q_len: take the largest.
 static size_t carve_max(const bs_model_cfg& c, int B, int max_q_len, int max_len) {
-    Needs needs = {c, B, max_len};
+    Needs needs = {c, B, max_len, NEED_EITHER};
     size_t need = 0;
     for (int q = 1; q <= max_q_len; ++q) {
         const size_t t = needs.of(q);
@@ -285,7 +293,7 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
                    hipStream_t s) {
     const bs_model_cfg& c = m->cfg;
     const int B = kv->B, M = B * q_len, dt = c.dtype;
-    const FwdWs w = carve(c, B, q_len, kv->max_len, row_plans(c, M), reinterpret_cast<char*>(ws));
+    const FwdWs w = carve(c, B, q_len, kv->max_len, row_plans(c, M, m->packed), reinterpret_cast<char*>(ws));
     BS_REQUIRE(ws_bytes >= w.total, BS_EWORKSPACE, "forward: workspace %zu < %zu bytes", ws_bytes, w.total);
     BS_REQUIRE((reinterpret_cast<uintptr_t>(ws) & 255) == 0, BS_EWORKSPACE, "forward: workspace not 256-byte aligned");
     const int H = c.n_heads, KVH = c.n_kv_heads, hd = c.head_dim, d = c.d_model, ff = c.d_ff;
@@ -595,10 +603,10 @@ static int prefill_chunk(int B, int n) {
     const int cap = (long long)B * 128 > PREFILL_ROWS ? 128 : PREFILL_ROWS / B;
     return n < cap ? n : cap;
 }
-// n tokens in such chunks are passes of two lengths, and only these are asked for: all lengths up to 4096 would be 0.2 ms
+// n tokens in such chunks are passes of two lengths, and only these are asked for: all lengths up to 4096 would be 0.2 to 0.4 ms
 // of host work ahead of the first launch (a workspace that holds no such chunk costs that: the largest length that fits is looked for).
-static size_t prefill_need(const bs_model_cfg& c, int B, int n, int max_len) {
-    Needs needs = {c, B, max_len};
+static size_t prefill_need(const bs_model_cfg& c, int B, int n, int max_len, int weights) {
+    Needs needs = {c, B, max_len, weights};
     const int chunk = prefill_chunk(B, n), rest = n % chunk;
     const size_t a = rest ? needs.of(rest) : 0, b = needs.of(chunk);
     return a > b ? a : b;
@@ -606,7 +614,7 @@ static size_t prefill_need(const bs_model_cfg& c, int B, int n, int max_len) {
 
 extern "C" __attribute__((visibility("default"))) size_t bs_prefill_workspace_bytes(const bs_model_cfg* c, int B, int n, int max_len) {
     if (!c || B < 1 || n < 1 || max_len < 1) return 0;
-    return prefill_need(*c, B, n, max_len);
+    return prefill_need(*c, B, n, max_len, NEED_EITHER);
 }
 
 extern "C" __attribute__((visibility("default"))) int bs_prefill(const bs_model* m, const bs_kv* kv, const int32_t* dev_tokens, int token_stride, int n,
@@ -616,9 +624,10 @@ extern "C" __attribute__((visibility("default"))) int bs_prefill(const bs_model*
     BS_REQUIRE(dev_tokens && ws, BS_EINVAL, "bs_prefill: NULL pointer");
     BS_REQUIRE(n >= 1 && n <= token_stride && n <= kv->max_len, BS_ESHAPE, "bs_prefill: n=%d, stride=%d, max_len=%d", n, token_stride, kv->max_len);
     int chunk = prefill_chunk(kv->B, n);
-    if (prefill_need(m->cfg, kv->B, n, kv->max_len) > ws_bytes) {      // the largest chunk up to which every length fits
+    const int weights = m->packed ? NEED_PACKED : NEED_UNPACKED;
+    if (prefill_need(m->cfg, kv->B, n, kv->max_len, weights) > ws_bytes) {      // the largest chunk up to which every length fits
         const int cap = chunk;
-        Needs needs = {m->cfg, kv->B, kv->max_len};
+        Needs needs = {m->cfg, kv->B, kv->max_len, weights};
         chunk = 0;
         for (int q = 1; q <= cap && needs.of(q) <= ws_bytes; ++q) chunk = q;
     }

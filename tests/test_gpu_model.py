@@ -783,7 +783,7 @@ def past_cache():
 
 
 @pytest.mark.parametrize("B,n,packed", [(1, 33, True), (3, 16, True), (1, 49, False), (2, 40, True), (9, 9, True), (1, 96, True), (1, 97, False),
-                                        (1, 128, True), (3, 43, True), (1, 160, True), (2, 128, False), (1, 257, True)])
+                                        (1, 128, True), (3, 43, True), (1, 160, True), (2, 128, False), (1, 257, True), (3, 100, False)])
 def test_rows_of_a_model_that_streams(past_cache, B, n, packed):
     c, W = past_cache
     m = bs().Model.from_numpy(c, W)
