@@ -1432,8 +1432,11 @@ __device__ __forceinline__ void load8<uint16_t>(const uint16_t* p, float out[8])
     out[6] = __uint_as_float(a.w << 16); out[7] = __uint_as_float(a.w & 0xFFFF0000u);
 }
 
-// SHORT, for caches of up to 512 keys: the longer ones' workgroups are many and each has many turns, what counts there is how many fit a
-// compute unit (20 rows of 8 heads of 32 at 5000 keys: a pass of two layers 121 us without, 163 with).
+// SHORT, for launches of at most one workgroup per compute unit over caches of up to 512 keys: its loads ahead take 258 registers, one workgroup a compute
+// unit instead of four.  Passes of two layers of 512 columns, 8 heads, without -> with: 1 x 1 row at 48 / 120 / 400 keys 59.0 / 60.0 / 71.5 -> 54.6 / 58.5 /
+// 71.9 us, 32 x 1 (256 workgroups) 80.7 / 80.8 / 93.2 -> 76.0 / 79.6 / 94.0; with more workgroups what counts is how many fit: 64 x 1 112 / 114 / 140 -> 116 / 123 /
+// 155, 16 x 5 at 48 keys 127.8 -> 129.8, prompts of 100 / 300 / 500 tokens 132 / 315 / 494 -> 140 / 370 / 592, 8 of 500 3.60 -> 4.50 ms; 20 rows of 8 heads of 32
+// at 5000 keys 121 -> 163.
 template <typename T, bool SHORT>
 __global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, const T* __restrict__ k_cache,
                                                    const T* __restrict__ v_cache, const int32_t* __restrict__ pos,
@@ -2446,10 +2449,10 @@ int launch_attention(int dtype, const float* q, const void* k_cache, const void*
         }
     } else {
         float* direct = n_splits == 1 ? reinterpret_cast<float*>(out) : nullptr;
-        if (max_len <= 512) hipLaunchKernelGGL((attn_kernel<float, true>), dim3(n_splits * ((q_len + ATT_RB - 1) / ATT_RB), H, B), block, 0, s, q, (const float*)k_cache,
-                           (const float*)v_cache, pos, q_len, H, KVH, hd, max_len, scale, n_splits, part, direct);
-        else hipLaunchKernelGGL((attn_kernel<float, false>), dim3(n_splits * ((q_len + ATT_RB - 1) / ATT_RB), H, B), block, 0, s, q, (const float*)k_cache,
-                           (const float*)v_cache, pos, q_len, H, KVH, hd, max_len, scale, n_splits, part, direct);
+        const dim3 grid(n_splits * ((q_len + ATT_RB - 1) / ATT_RB), H, B);
+        const bool few = max_len <= 512 && (long long)grid.x * H * B <= device_cus();       // SHORT, see there
+        if (few) hipLaunchKernelGGL((attn_kernel<float, true>), grid, block, 0, s, q, (const float*)k_cache, (const float*)v_cache, pos, q_len, H, KVH, hd, max_len, scale, n_splits, part, direct);
+        else hipLaunchKernelGGL((attn_kernel<float, false>), grid, block, 0, s, q, (const float*)k_cache, (const float*)v_cache, pos, q_len, H, KVH, hd, max_len, scale, n_splits, part, direct);
         BS_LAUNCH_CHECK();
         if (n_splits > 1) hipLaunchKernelGGL((attn_merge_kernel<float, false>), dim3(B * q_len * H), dim3(hd), 0, s, part, n_splits, hd, plane, out, out_tiled ? H : 0, out_tiled, (const int32_t*)nullptr, 1);
     }
