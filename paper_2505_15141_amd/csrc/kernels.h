@@ -123,7 +123,8 @@ int launch_resid_sum(float* x, const float* pend, int pend_ks, size_t pend_strid
                      size_t plane, void* out, float* ssq, int tiled, hipStream_t s);
 int launch_swiglu(int dtype, const float* part, int ks, size_t ks_stride, int M, int ff, size_t plane, void* out, int tiled,
                   const float* ssq, int ssq_n, int d, float eps, hipStream_t s);
-// fp32 projections with the work around them (f32_fused_kernel), for passes where f32_fused_applies
+// fp32 projections with the work around them (f32_fused_kernel), for the layers of passes where f32_fused_applies, and for the LM head of those where
+// f32_head_applies (M: logit rows)
 enum { F32_QKV, F32_SWIGLU, F32_RESID, F32_HEAD };
 struct F32Args {
     const float* x; const int32_t* tok;       // input rows [.][K]: row m, or where tok is given (QKV) row tok[m] of the embedding
@@ -135,7 +136,8 @@ struct F32Args {
     const int32_t* pos; const float2* rope; int q_len, nq, nkv, hd, cache_len;      // QKV
     float* k_cache; float* v_cache;
 };
-bool f32_fused_applies(int M, int d, int ff);
+bool f32_fused_applies(int M, int d, int ff, int nqkv, int nq);
+bool f32_head_applies(int M, int vocab, int d);
 int launch_f32_fused(int epi, const F32Args& a, hipStream_t s);
 int launch_rope_kv(int dtype, const float* part, int ks, size_t ks_stride, const int32_t* pos, const float2* rope, int M,
                    int q_len, int H, int KVH, int hd, int max_len, float* q_out, void* k_cache, void* v_cache,

@@ -2282,10 +2282,18 @@ int launch_rope_kv(int dtype, const float* part, int ks, size_t ks_stride, const
     return BS_OK;
 }
 
-// The fused fp32 projections read the weights once per four rows.  Against a kernel per step: 128 to 1536 columns, 1 to 1024 rows a pass 1.1 to 1.5
-// times as fast, 2048 columns 1.2 (4 rows) to 1.04 (1024 rows), 4096 columns 1.27 up to 40 rows; from 48 rows on gemm_f32_kernel's groups of
-// eight beat them there (48 rows 1551 us against 1752, 1024 rows 28.5 against 36.2 ms), whose feed-forward matrices are 180 MB each.
-bool f32_fused_applies(int M, int d, int ff) { return M < 48 || (size_t)d * ff <= 12000000; }
+// The fused fp32 projections read a matrix once per four rows, from the second time on out of the memory-side cache if it fits there (256 MB).  Against a
+// kernel per step: 128 to 1536 columns, 1 to 1024 rows a pass 1.1 to 1.5 times as fast, 2048 columns 1.2 (4 rows) to 1.04 (1024 rows), 4096 columns
+// 1.27 up to 40 rows; from 48 rows on gemm_f32_kernel's groups of eight beat them there (48 rows 1551 us against 1752, 1024 rows 28.5 against
+// 36.2 ms), whose gate and up matrices are 360 MB.  By a matrix alone, passes of one layer and the LM head of 64 to 131 million elements, kernel per
+// step -> fused: 131 million, 32 rows 1091 -> 985 us, 48 rows 1115 -> 1465, 512 rows 9.4 -> 15.4 ms; 66 million, 64 rows 644 -> 628 us, 192 rows 1881 -> 1870, 256 rows
+// 2390 -> 2497, 512 rows 4790 -> 5076; 33 million, 192 rows 1008 -> 1001, 256 rows 1287 -> 1322; 16 million, 512 rows 1256 -> 1249.  QKV, which saves
+// the launches around it as well, 50 million in two layers: 64 rows 1560 -> 1369, 256 rows 5330 -> 5166, 512 rows 10212 -> 10300.
+static bool f32_fits(int M, size_t elems, int rows) { return M < 48 || elems <= 24000000 || (elems <= (size_t)64 << 20 && M < rows); }
+bool f32_fused_applies(int M, int d, int ff, int nqkv, int nq) {
+    return M < 48 || ((size_t)d * ff <= 12000000 && f32_fits(M, (size_t)nqkv * d, 512) && f32_fits(M, (size_t)nq * d, 512));
+}
+bool f32_head_applies(int M, int vocab, int d) { return f32_fits(M, (size_t)vocab * d, 256); }
 
 int launch_f32_fused(int epi, const F32Args& a, hipStream_t s) {
     if (a.M <= 0 || a.N <= 0) return BS_OK;

@@ -336,7 +336,7 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
         BS_TRY(launch_step(a, s));
         return BS_OK;
     }
-    const bool f32_fused = dt == BS_F32 && f32_fused_applies(M, d, ff);
+    const bool f32_fused = dt == BS_F32 && f32_fused_applies(M, d, ff, nqkv, nq);
     if (few_rows) {
         const size_t pd = (size_t)M * d;
         uint16_t* hp = reinterpret_cast<uint16_t*>(w.h);
@@ -398,7 +398,8 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
             a.x = reinterpret_cast<const float*>(w.act); a.w[0] = mat(L.w_down); a.N = d; a.K = ff; a.out = w.x;
             BS_TRY(launch_f32_fused(F32_RESID, a, s));
         }
-        if (logit_rows > 0) {
+        if (logit_rows == 0) return BS_OK;
+        if (f32_head_applies(B * logit_rows, c.vocab, d)) {
             F32Args a = {};
             a.x = w.x; a.gain = m->final_norm; a.eps = c.norm_eps; a.w[0] = mat(m->lm_head); a.K = d; a.N = c.vocab; a.rows_in = q_len; a.rows_out = logit_rows; a.ldo = c.vocab;
             if (logits_bstride == (size_t)logit_rows * c.vocab || logit_rows == 1) {
@@ -411,8 +412,8 @@ static int forward(const bs_model* m, const bs_kv* kv, const int32_t* q_tokens, 
                     BS_TRY(launch_f32_fused(F32_HEAD, a, s));
                 }
             }
+            return BS_OK;
         }
-        return BS_OK;
     } else {
     // Up to 32 rows of a wide model (verification of one to a few sequences): whole-K projections with the consumer's work in the
     // epilogue (gemm_rows_kernel), where the 16-column units of a projection fill at least four fifths of the compute units'

@@ -890,3 +890,18 @@ def test_workspace_of_every_length_is_planned_in_little_time():
         assert bs().lib.bs_forward_workspace_bytes(ctypes.byref(cfg), 1, 4096, 4352) > 0
         best = min(best, time.perf_counter() - t)
     assert best < 2e-3, best
+
+
+@pytest.mark.parametrize("c,B,q_len,rows", [(synth.cfg(1, 1024, 2, 32, 96, 24001, dtype="f32"), 8, 32, 32), (synth.cfg(1, 1024, 2, 32, 96, 24001, dtype="f32"), 8, 33, 31),
+                                            (synth.cfg(1, 1024, 64, 128, 256, 999, dtype="f32"), 2, 256, 3)],
+                         ids=["head by itself", "head with the norm", "layers by themselves"])
+def test_f32_matrices_of_more_than_24_million_elements(c, B, q_len, rows):
+    """Many rows leave the fused projections where a matrix is large: an LM head from 256 logit rows on, a layer from 512 rows on."""
+    W = synth.make_weights(c, 37)
+    m = bs().Model(c, {k: torch.from_numpy(v).cuda() for k, v in W.items()})
+    kv = bs().KV(m, B, q_len)
+    toks = synth.make_prompts(B, q_len, c["vocab"], seed=38)
+    logits = bs().verify_forward(m, kv, torch.from_numpy(toks.astype(np.int32)).cuda(), torch.zeros(B, dtype=torch.int32, device="cuda"), rows)
+    for b in (0, B - 1):
+        ref = forward(c, W, toks[b], storage="f32", last_rows=rows)
+        assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["f32"], b
