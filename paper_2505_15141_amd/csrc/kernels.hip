@@ -18,6 +18,7 @@
 //   attention   q_len causal query rows per head against the contiguous KV cache, split along the
 //               keys with online softmax; merge kernel combines the splits
 #include <math.h>
+#include <initializer_list>
 #include <mutex>
 #include <vector>
 #include <hip/hip_ext.h>
@@ -2320,18 +2321,25 @@ size_t attn_cells_bytes(int rows, int H, int hd, int n_splits) {
     return b < 2147483648.0 ? (size_t)b : 0;           // 32-bit cell offsets
 }
 
-// workgroups of the one-tile attention kernel that the device holds at the same time; without a device (sizes asked for ahead)
-// those of a whole one, 2 and 4 a compute unit
+// workgroups of the one-tile attention kernel that the device holds at the same time, whichever of its variants runs (launch_attention: by the
+// length of a split and by what the pass reads): of the variant with the fewest.  Never more than the 2 and 4 a compute unit of its launch bounds, which are
+// also the answer without a device (sizes asked for ahead).
 static size_t attn_resident_workgroups(int hd) {
-    auto ask = [](bool wide) -> size_t {
-        int per_cu = 0;
+    auto ask = [](int bound, std::initializer_list<const void*> variants) -> size_t {
         const int cus = step_grid();
-        if (cus <= 0) return (size_t)device_cus() * (wide ? 2 : 4);
-        const hipError_t e = wide ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_mfma_kernel<128, 1, true, true, false>, 256, 0)
-                                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_mfma_kernel<64, 1, true, true, false>, 256, 0);
-        return (e == hipSuccess && per_cu > 0) ? (size_t)per_cu * cus : 1;   // 1: never enough, the merge kernel runs
+        if (cus <= 0) return (size_t)device_cus() * bound;
+        int least = bound;
+        for (const void* kernel : variants) {
+            int per_cu = 0;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess || per_cu < 1) return 1;   // 1: never enough, the merge kernel runs
+            if (per_cu < least) least = per_cu;
+        }
+        return (size_t)least * cus;
     };
-    static const size_t c128 = ask(true), c64 = ask(false);      // asked once (initialisation of a local static is thread-safe)
+#define BS_ONE_TILE(HD) {(const void*)&attn_mfma_kernel<HD, 1, true, true, false>, (const void*)&attn_mfma_kernel<HD, 1, false, true, false>, \
+                         (const void*)&attn_mfma_kernel<HD, 1, true, false, false>, (const void*)&attn_mfma_kernel<HD, 1, false, false, false>}
+    static const size_t c128 = ask(2, BS_ONE_TILE(128)), c64 = ask(4, BS_ONE_TILE(64));      // asked once (initialisation of a local static is thread-safe)
+#undef BS_ONE_TILE
     return hd == 128 ? c128 : c64;
 }
 
