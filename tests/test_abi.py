@@ -102,7 +102,7 @@ def test_prompt_workspace_is_that_of_its_two_chunk_lengths(B, n):
 
 
 def test_key_splits_follow_what_combining_them_costs():
-    """The 7B shape and a grouped-query one.  In the kernel every workgroup combines its share of a group's rows one after the other: a
+    """The 7B shape and a grouped-query one.  In the kernel every workgroup combines its share of a group's rows, 256 / head_dim at a time: a
     cache of 900 rows is worth two parts with 3 and 5 rows, not with 9 or 16; a merge kernel behind 20 rows costs less than one behind 144."""
     c, g = synth.LLAMA7B_TARGET, synth.LLAMA3_8B_TARGET
     for B, q_len, max_len, want in [(1, 3, 900, (2, 2, True)), (1, 5, 900, (2, 2, True)), (1, 9, 900, (1, 1, False)), (1, 9, 1280, (3, 3, True)),

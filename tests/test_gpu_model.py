@@ -39,6 +39,14 @@ def setup(c, B, max_len, seed, std=None, packed=False):
     return W, m, kv
 
 
+def off(got, ref):
+    """Relative error in the 2-norm.  Activations are two bf16 planes; a second plane left out, or taken from the row beside it, in front of a single
+    projection costs 1.6e-3 and more in the models below (1.6e-3 in front of down or the LM head, 2.3e-3 of O and gate/up, 6e-3 of QKV: the oracle with
+    that projection's input rounded), which stays within the absolute tolerance."""
+    got = got.cpu().numpy().astype(np.float64)
+    return np.linalg.norm(got - ref) / np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("c,B,n_prefix,q_len,packed", [
     (synth.TINY_TARGET, 1, 32, 5, False), (synth.TINY_DRAFT, 2, 9, 3, False), (ODD_F32, 3, 17, 4, False),
     (MID, 1, 70, 9, False), (MID_GQA, 2, 130, 5, False), (WIDE, 1, 200, 9, False), (MID, 3, 1, 2, False),
@@ -393,6 +401,24 @@ def test_splits_combined_in_the_kernel_with_blocks_requested_ahead(heads, kv_hea
             assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
 
 
+# The workgroup of a split combines 256 / head_dim rows side by side: four, two and one of head_dim 64, two and one of 128, with rows left over in
+# the last turn, splits without keys, and an even and an odd number of blocks a wavefront
+@pytest.mark.parametrize("heads,kv_heads,hd,B,q_len,n,max_len,splits", [
+    (8, 8, 64, 1, 16, 1001, 1100, 3), (8, 8, 64, 1, 7, 40, 1100, 3), (8, 2, 64, 1, 4, 640, 1100, 3), (8, 8, 64, 3, 5, 333, 1100, 3), (8, 8, 64, 1, 16, 650, 700, 2),
+    (8, 8, 128, 1, 16, 1500, 2100, 5), (8, 8, 128, 1, 16, 129, 1600, 4), (8, 8, 128, 2, 5, 900, 1100, 3), (8, 2, 128, 1, 4, 1900, 2100, 5)])
+def test_rows_combined_side_by_side(heads, kv_heads, hd, B, q_len, n, max_len, splits):
+    c = synth.cfg(1, 256, heads, hd, 256, 512, n_kv_heads=kv_heads)
+    assert bs().attention_splits(c, B, q_len, max_len) == (splits, splits, True)
+    W, m, kv = setup(c, B, max_len, seed=81, packed=True)
+    toks = synth.make_prompts(B, n + q_len, c["vocab"], seed=82)
+    dt = torch.from_numpy(toks.astype(np.int32)).cuda()
+    bs().prefill(m, kv, dt, n, want_logits=False)
+    logits = bs().verify_forward(m, kv, dt[:, n:].contiguous(), torch.full((B,), n, dtype=torch.int32, device="cuda"))
+    for b in range(B):
+        ref = forward(c, W, toks[b], storage="bf16", last_rows=q_len)
+        assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"] and off(logits[b], ref) < 5e-4, (b, off(logits[b], ref))
+
+
 # A batch with sequences much longer than the others: these are cut into more parts, up to `most`, the others into `few`.
 @pytest.mark.parametrize("c,B,q_len,max_len,few,most,long_len", [
     (synth.cfg(2, 256, 16, 128, 256, 512), 16, 5, 2304, 1, 4, 1500),                       # parts combined by the last workgroup
@@ -744,7 +770,8 @@ def test_resident_step_with_a_sequence_left_out():
 
 
 # Passes of 33 rows and more: tiled activation planes (rows rounded up to 16) in the layers, and in front of the LM head where it has that many rows
-@pytest.mark.parametrize("c", [MID_GQA, synth.cfg(2, 96, 2, 64, 168, 1000, dtype="bf16")], ids=["tiled", "d_ff of 168: row by row"])
+# Measured: at most 7.7e-4 (keys and values that round the other way in early tokens), as a rule 1e-4.
+@pytest.mark.parametrize("c", [dict(MID_GQA, n_layers=2), synth.cfg(2, 96, 2, 64, 168, 1000, dtype="bf16")], ids=["tiled", "d_ff of 168: row by row"])
 @pytest.mark.parametrize("B,q_len,rows", [(11, 3, 3), (9, 5, 4), (9, 5, 1), (35, 1, 1), (3, 16, 16), (29, 9, 9)])
 def test_planes_of_33_rows_and_more(c, B, q_len, rows):
     n, max_len = 20, 40
@@ -755,7 +782,7 @@ def test_planes_of_33_rows_and_more(c, B, q_len, rows):
     logits = bs().verify_forward(m, kv, dt[:, n:].contiguous(), torch.full((B,), n, dtype=torch.int32, device="cuda"), rows)
     for b in {0, 1, B // 2, B - 1}:
         ref = forward(c, W, toks[b], storage="bf16", last_rows=rows)
-        assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
+        assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"] and off(logits[b], ref) < 1.2e-3, (b, off(logits[b], ref))
 
 
 # 129 rows and more: blocks of up to 128 rows, wavefronts in one row (5 to 8 row tiles) or two (6, 8); columns beside 384 and 512, a last block that is not full
@@ -770,7 +797,7 @@ def test_blocks_of_rows_from_129_rows_on(c, B, n):
     logits = bs().verify_forward(m, kv, dt, torch.zeros(B, dtype=torch.int32, device="cuda"), rows)
     for b in {0, B - 1}:
         ref = forward(c, W, toks[b], storage="bf16", last_rows=rows)
-        assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
+        assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"] and off(logits[b], ref) < 5e-4, (b, off(logits[b], ref))      # measured: at most 1.3e-4
 
 
 # 33 to 256 rows of a model whose weights are more than the memory-side cache holds: eight wavefronts in a row with two, three or four weight tiles
@@ -796,7 +823,7 @@ def test_rows_of_a_model_that_streams(past_cache, B, n, packed):
     logits = bs().verify_forward(m, kv, dt, torch.zeros(B, dtype=torch.int32, device="cuda"), rows)
     for b in {0, B - 1}:
         ref = forward(c, W, toks[b], storage="bf16", last_rows=rows)
-        assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"], b
+        assert np.max(np.abs(logits[b].cpu().numpy() - ref)) < TOL["bf16"] and off(logits[b], ref) < 5e-4, (b, off(logits[b], ref))      # measured: at most 1.3e-4
 
 
 # fp32 projections with the work around them: rows and columns that four and eight do not divide, a vocabulary of an odd size, an embedding, a final norm and an
