@@ -150,10 +150,6 @@ __device__ __forceinline__ void st_cells4(DevBuf b, int c, float v0, float v1, f
     st_cells2(b, c, v0, v1, flag);
     st_cells2(b, c + 2, v2, v3, flag);
 }
-__device__ __forceinline__ void st_cell1(DevBuf b, int c, float v, unsigned flag) {
-    const u32x2 u = {__float_as_uint(v), flag};
-    __builtin_amdgcn_raw_buffer_store_b64(u, b.r, c * 8, 0, AUX_SC1);
-}
 __device__ __forceinline__ u32x4 ld_cells2(DevBuf b, int c) { return __builtin_amdgcn_raw_buffer_load_b128(b.r, c * 8, 0, AUX_SC1); }
 __device__ __forceinline__ u32x2 ld_cell1(DevBuf b, int c) { return __builtin_amdgcn_raw_buffer_load_b64(b.r, c * 8, 0, AUX_SC1); }
 

@@ -788,12 +788,11 @@ int launch_spec_sample(const void* p_logits, const void* q_logits, const int32_t
     a.p_logits = p_logits; a.q_logits = q_logits; a.draft_tokens = draft_tokens; a.uniforms = uniforms; a.seed = seed;
     a.round_ptr = round_ptr; a.round = round; a.gamma = gamma; a.V = V; a.n_p_rows = n_p; a.inv_temp = inv_temp;
     a.stats = stats; a.flags = flags; a.cand = cand; a.accept_len = accept_len; a.next_token = next_token; a.margins = margins;
-    // The deciding row pair is streamed again (it was read a moment ago by phase A: L2 / memory-side cache), not kept
-    // in registers over the passes (256 registers per lane, slower at every batch size).  Where there are more sequences
-    // than compute units it is other sequences on the same compute unit that hide this kernel's chain of dependent loads
-    // (256 instead of 50 registers at B = 1024, bf16: 77 against 42 us); up to that deeper batches do, see DEEP_SEQS.
+    // The deciding row pair is read again (it was read a moment ago by phase A: L2 / memory-side cache).  Where there are more sequences
+    // than compute units it is other sequences on the same compute unit that hide this kernel's chain of dependent loads, and registers cost those
+    // (256 instead of 50 at B = 1024, bf16: 77 against 42 us); up to that deeper batches hide it, see DEEP_SEQS, and bf16 rows of up to 32768 logits
+    // stay in registers over the passes (64 sequences, gamma 8, V = 32000 27.4 -> 25.7 us); float rows take twice as many and spill there.
     const dim3 grid(B), block(ST);
-    // bf16 rows of up to 32768 logits stay in registers (64 sequences, gamma 8, V = 32000 27.4 -> 25.7 us); float rows take twice as many and spill there
 #define BS_DECIDE(T) do { if (B > DEEP_SEQS) hipLaunchKernelGGL((spec_decide_kernel<T, SLAB_BATCH, false>), grid, block, 0, stream, a); \
                          else if (sizeof(T) == 2 && V <= DEEP_BATCH * ST * GE) hipLaunchKernelGGL((spec_decide_kernel<T, DEEP_BATCH, sizeof(T) == 2>), grid, block, 0, stream, a); \
                          else hipLaunchKernelGGL((spec_decide_kernel<T, DEEP_BATCH, false>), grid, block, 0, stream, a); } while (0)
