@@ -16,6 +16,7 @@
 // scan of the 512 group sums locates the group, a serial scan of 8 weights locates the token.
 #include <math.h>
 #include <mutex>
+#include <type_traits>
 #include "common.h"
 #include "sample.h"
 
@@ -27,7 +28,7 @@ constexpr int GE = 8;             // tokens per group
 constexpr int MAX_SLABS = 256;    // V <= 2^20
 // Slabs of the row pair that the deciding workgroup reads at a time.  What bounds it is the trips to memory one behind the other
 // (a pair of 32000 logits is 8 slabs, one trip with DEEP_BATCH), which only other workgroups on the compute unit hide; the
-// registers (149 instead of 104 per lane with float logits) cost those.  So up to DEEP_SEQS sequences, one workgroup per
+// registers (172 instead of 55 per lane with float logits) cost those.  So up to DEEP_SEQS sequences, one workgroup per
 // compute unit: both kernels together, us before -> after: 1 sequence, gamma 4, V = 32000 float 17.9 -> 15.8; 64, gamma 8,
 // bf16 30.1 -> 27.4; 64, gamma 4, V = 128256 bf16 68 -> 59; 256, gamma 2, V = 128256 float 170 -> 151; but 512, gamma 3,
 // V = 32000 float 92 -> 100.
@@ -323,24 +324,30 @@ __device__ __forceinline__ RowResult process_row(const T* __restrict__ p, const 
             for (int k0 = 0; k0 < nslabs; k0 += NB) {
                 float ss[NB];
                 if (NB > SLAB_BATCH && nfull > 0) {
-                    Raw<T> ra[NB], rb[NB];
+                    // a batch of slabs that all exist has no branch among its loads, in the row's last batch the others are passed over (194 sequences,
+                    // V = 128256 float 101.3 us with the branches, 99.2 without; 128, V = 100000 float, whose last batch has one slab, 84.2 and 82.5, passed over nothing 86.1)
+                    auto sums = [&](auto all) {
+                        Raw<T> ra[NB], rb[NB];
 #pragma unroll
-                    for (int j = 0; j < NB; ++j) {
-                        if (k0 + j >= nslabs) break; // uniform
-                        const int g = min(tid + (k0 + j) * ST, nfull - 1);
-                        ra[j] = load_full(p, g);
-                        rb[j] = residual ? load_full(q, g) : ra[j];
-                    }
+                        for (int j = 0; j < NB; ++j) {
+                            if (!all() && k0 + j >= nslabs) break;                   // uniform
+                            const int g = min(tid + (k0 + j) * ST, nfull - 1);
+                            ra[j] = load_full(p, g);
+                            rb[j] = residual ? load_full(q, g) : ra[j];
+                        }
 #pragma unroll
-                    for (int j = 0; j < NB; ++j) {
-                        const int g = tid + (k0 + j) * ST;
-                        ss[j] = 0.f;
-                        if (k0 + j >= nslabs) continue;
-                        float w[GE];
-                        weights(ra[j], rb[j], w);
-                        ss[j] = g < nfull ? sum8(w) : 0.f;
-                        if (g >= nfull && g < ngroups) ss[j] = group_sum(g);     // the row's last tokens: one lane
-                    }
+                        for (int j = 0; j < NB; ++j) {
+                            const int g = tid + (k0 + j) * ST;
+                            ss[j] = 0.f;
+                            if (!all() && k0 + j >= nslabs) continue;
+                            float w[GE];
+                            weights(ra[j], rb[j], w);
+                            ss[j] = g < nfull ? sum8(w) : 0.f;
+                            if (g >= nfull && g < ngroups) ss[j] = group_sum(g);     // the row's last tokens: one lane
+                        }
+                    };
+                    if (k0 + NB <= nslabs) sums(std::true_type());
+                    else sums(std::false_type());
 #pragma unroll
                     for (int j = 0; j < NB; ++j) ss[j] = wave_sum(ss[j]);
                 } else {
